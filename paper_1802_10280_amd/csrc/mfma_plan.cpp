@@ -1,0 +1,89 @@
+// Host side of the matrix-core form: which layers have one, and its section of the plan.
+#include <math.h>
+#include <string.h>
+
+#include <vector>
+
+#include "mfma.h"
+
+namespace escoin {
+
+// Microseconds the matrix-core kernel takes for a batch of N images: a workgroup alone on its compute
+// unit spends 1.6 us on a chunk (staging, barrier, the first wait) and 0.46 us on each of its taps; two
+// that share one take 1.72 times as long for both.
+static double mfma_us(const Dims& d, double N) {
+    const double jobs = ceil(N * (d.H + d.pad) * (d.W + d.pad) / kMfmaTP) * (double)(mfma_row_blocks(d) / kMfmaWM);
+    const double job = 6.0 + (double)mfma_chunks(d) * (1.6 + 0.46 * d.R * d.S);
+    return jobs <= 256 ? job : ceil(jobs / 512) * 1.72 * job;
+}
+
+// The tiled kernel at its better: 36 TFLOP/s on the nonzeros (41 measured on a large layer at 50 %
+// sparsity, 32 on 13x13 maps at 65 %, less the fewer nonzeros or positions there are).
+static double tiled_us(const Dims& d, double N, long long nnz) { return 2e-6 * (double)nnz * N * d.E * d.F / 36.0; }
+
+// Whether a plan carries the section: shapes the kernel takes, and pruned so little that a large batch
+// is faster on the matrix cores.
+bool mfma_planned(const Dims& d, long long nnz) {
+    if (d.stride != 1 || d.R <= d.pad || d.S <= d.pad || mfma_window(d) > kMfmaMaxWindow) return false;
+    if (d.C < 16 || d.M < 32 || mfma_weight_bytes(d) > (64ull << 20)) return false;
+    const double many = 512.0 * 64 * kMfmaTP / ((double)(d.H + d.pad) * (d.W + d.pad));
+    return mfma_us(d, many) < 0.9 * tiled_us(d, many, nnz);
+}
+
+// Whether a forward call on this batch takes it: offsets inside the kernel are 32 bits, and the batch
+// has to fill the compute units.
+bool mfma_chosen(const Dims& d, long long nnz) {
+    const long long total = (long long)d.N * (d.H + d.pad) * (d.W + d.pad);
+    const long long groups = (long long)mfma_row_blocks(d) / kMfmaWM;
+    if (total > (1ll << 30) || (long long)d.N * d.C * d.H * d.W > (1ll << 30) || total / kMfmaTP * groups > (1ll << 30)) return false;
+    return mfma_us(d, d.N) < 0.9 * tiled_us(d, d.N, nnz);
+}
+
+static float to_bf16(float x, uint16_t* bits) {  // rounds to nearest even; x is finite
+    uint32_t u;
+    memcpy(&u, &x, 4);
+    u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+    *bits = (uint16_t)(u >> 16);
+    float r;
+    memcpy(&r, &u, 4);
+    return r;
+}
+
+// Writes the section into `out` (zeroed).  False where it cannot stand for the CSR: a value that is
+// not finite in bf16, or a repeated column, whose values would have to be added up first.
+bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value, char* out) {
+    const size_t RS = (size_t)d.R * d.S, chunks = mfma_chunks(d);
+    uint16_t* w = (uint16_t*)out;
+    int32_t* rp = (int32_t*)(out + mfma_weight_bytes(d));
+    MfmaNz* nz = (MfmaNz*)(out + mfma_weight_bytes(d) + mfma_rowptr_bytes(d));
+    std::vector<int32_t> seen((size_t)d.C * RS, -1);
+    const int32_t plane = d.Hp * d.Wp;
+    int32_t at = 0;
+    for (int m = 0; m < d.M; ++m) {
+        rp[m] = at;
+        for (int j = rowptr[m]; j < rowptr[m + 1]; ++j) {
+            if (value[j] == 0.0f) continue;
+            const int c = stretched[j] / plane, rem = stretched[j] - c * plane, r = rem / d.Wp, s = rem - r * d.Wp;
+            int32_t& was = seen[(size_t)c * RS + (size_t)r * d.S + s];
+            if (was == m) return false;
+            was = m;
+            uint16_t part[3];
+            if (!(fabsf(value[j]) < 3.38e38f)) return false;
+            const float rest = value[j] - to_bf16(value[j], &part[0]);
+            to_bf16(rest - to_bf16(rest, &part[1]), &part[2]);
+            // lane: channel m % 32, and which 8 of the 16 input channels; 8 of them per lane
+            const size_t step = ((size_t)(m / 32) * chunks + c / 16) * RS + (size_t)r * d.S + s;
+            const size_t lane = m % 32 + 32 * (size_t)(c % 16 / 8);
+            for (int k = 0; k < 3; ++k) w[((step * 3 + k) * 64 + lane) * 8 + c % 8] = part[k];
+            nz[at].c = c;
+            nz[at].r = (uint16_t)r;
+            nz[at].s = (uint16_t)s;
+            nz[at].val = value[j];
+            ++at;
+        }
+    }
+    rp[d.M] = at;
+    return true;
+}
+
+}  // namespace escoin

@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "common.h"
+#include "mfma.h"
 #include "plan.h"
 
 namespace escoin {
@@ -309,7 +310,7 @@ struct RowNz {
 
 // One attempt with the knobs in `h`.
 int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value,
-                    PlanHeader h, void* out, size_t out_bytes, size_t* bytes) {
+                    PlanHeader h, bool tuned, void* out, size_t out_bytes, size_t* bytes) {
     const int nnz = rowptr[d.M];
     Geometry g;
     int rc = derive(d, &h, &g);
@@ -684,6 +685,11 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
     if (dma_room) off = align_up64(off + (uint64_t)h.n_tiles * dma_copies * 64 * sizeof(DmaSlot), 256);
     h.off_zero = off;
     off = align_up64(off + 64, 256);
+    // A plan whose tiling the caller fixed is for the tiled kernel alone.
+    const bool with_mfma = !tuned && mfma_planned(d, rowptr[d.M]);
+    h.mfma = 0;
+    h.off_mfma = off;
+    if (with_mfma) off = align_up64(off + mfma_bytes(d, rowptr[d.M]), 256);
     h.total_bytes = off;
     *bytes = (size_t)off;
     if (!out) return ESCOIN_OK;
@@ -771,7 +777,8 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
                     ds.chan = (int32_t)(q.key >> kKeyOffsetBits);
                 }
     }
-    std::memcpy(base, &h, sizeof(h));  // the header once more, now with WW and n_dma
+    h.mfma = with_mfma && mfma_write(d, rowptr, stretched, value, base + h.off_mfma) ? 1 : 0;
+    std::memcpy(base, &h, sizeof(h));  // the header once more, now with WW, n_dma and mfma
     std::memcpy(base + h.off_lanes, lanes.data(), lanes.size() * sizeof(LaneSlot));
     std::memcpy(base + h.off_perm, slot.data(), slot.size() * sizeof(RowSlot));
     std::memcpy(base + h.off_perm + slot.size() * sizeof(RowSlot), group_regions.data(), (size_t)h.n_mgroups * 4);
@@ -835,10 +842,13 @@ int build_plan(const escoin_conv_desc* desc, const int32_t* rowptr, const int32_
         if (rowptr[m + 1] < rowptr[m]) return ESCOIN_EINVAL;
     const int nnz = rowptr[d.M];
     if (nnz > 0 && (!stretched || (out && !value))) return ESCOIN_EINVAL;
+    bool tuned = false;
     if (tuning) {
         const int32_t* f = &tuning->K;
-        for (int i = 0; i < 10; ++i)
+        for (int i = 0; i < 10; ++i) {
             if (f[i] < 0) return ESCOIN_EINVAL;
+            tuned = tuned || f[i] > 0;
+        }
     }
 
     PlanHeader h;
@@ -869,7 +879,7 @@ int build_plan(const escoin_conv_desc* desc, const int32_t* rowptr, const int32_
             trial.CC = ceil_div(d.C, ceil_div(d.C, cap));
             if (quads) trial.CC = std::min(cap, round_up(trial.CC, 4));
         }
-        rc = build_plan_once(d, rowptr, stretched, value, trial, out, out_bytes, bytes);
+        rc = build_plan_once(d, rowptr, stretched, value, trial, tuned, out, out_bytes, bytes);
         if (rc != ESCOIN_ERANGE) return rc;
         if (auto_cc && h.CC > 1) {
             h.CC = std::max(1, h.CC - std::max(1, h.CC / 8));

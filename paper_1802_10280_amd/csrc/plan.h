@@ -98,7 +98,12 @@ struct PlanHeader {
                          // buffer is a run of four input words or zeros); 0: no such table
     uint64_t off_dma;    // DmaSlot [n_tiles][n_dma][64]
     uint64_t off_zero;   // 64 zero bytes: what the copy of a slot without input reads
+    int32_t mfma;        // 1: the section for the matrix cores is there (mfma.h); a plan without it,
+                         // or one saved before there was such a section, holds 0 here
+    int32_t reserved;
+    uint64_t off_mfma;   // split weights, row pointers, nonzeros
 };
+static_assert(sizeof(PlanHeader) <= 512, "the sections start 512 bytes into the blob");
 
 // One 16-byte slot of a window buffer as the global -> LDS staging sees it: lane l of copy j
 // fills slot 64*j + l.

@@ -1,0 +1,234 @@
+// sconv on the matrix cores, for filter banks pruned so little that multiplying the zeros too costs
+// less than walking the nonzeros.
+//
+// The layer is one product per filter tap: out[m, p] += W[m, c, tap] * in[c, p + shift(tap)], with the
+// output positions p of the WHOLE batch numbered through one flat padded array (the 1-D array of
+// Section 3.1, the padding between neighbouring rows and images shared: pitch W + pad, H + pad rows),
+// so that a workgroup takes any kTP consecutive positions and small maps waste no lanes.
+//
+// fp32 is kept by splitting every operand into three bf16 parts, x = h + m + l, each the rounded rest
+// of the one before: 8 + 8 + 8 significant bits, so the split of an fp32 number is exact.  Six of
+// the nine partial products are formed (hh, hm, mh, mm, hl, lh); the three left out are below 2^-25
+// of |x*w|, less than the rounding of a single fp32 product.  hh has an accumulator of its own, so
+// that the running sum is rounded once per 16 channels, the five small ones share another.
+//
+// A finite input whose h rounds to infinity, an Inf or a NaN would spread to outputs that only meet
+// it under a zero weight.  Staging notices them; a workgroup that has seen one computes its
+// outputs again from the nonzeros alone.
+//
+// Bound by the matrix cores: per wave and (tap, 16 channels) 12 MFMAs of 32 clk against 6 LDS reads
+// and 3 KB of weights from L1/L2, which all the position waves of a workgroup share.  The weights
+// lie in the plan in the order the lanes read them.
+#include "common.h"
+#include "mfma.h"
+#include "plan.h"
+
+namespace escoin {
+namespace {
+
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+struct MfmaArgs {
+    const float* in;
+    float* out;
+    const float* bias;
+    const b8* w;              // [32-row block][chunk of 16 channels][tap][split][lane]
+    const int32_t* rowptr;    // the nonzeros once more, for windows that hold Inf or NaN
+    const MfmaNz* nz;
+    int N, C, H, W, M, E, F, R, S, pad;
+    int pitch, plane;         // of the flat padded array: columns per row, positions per image
+    int total;                // positions of the batch
+    int n_chunks, n_mgroups, n_tiles;
+    uint32_t flags;
+};
+
+constexpr int kThreads = 64 * kMfmaWM * kMfmaWP;
+constexpr int kTM = 32 * kMfmaWM;
+
+// WR: window positions held in LDS (kTP and the reach of the taps, see mfma_window).
+template <int WR>
+__global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs a) {
+    extern __shared__ __attribute__((aligned(16))) b8 win[];  // [buffer][split][8-channel half][WR]
+    constexpr int kBuf = 6 * WR;
+    constexpr int kTasks = (2 * WR + kThreads - 1) / kThreads;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wp = wave % kMfmaWP, wm = wave / kMfmaWP;
+
+    // Workgroup ids land on the XCDs in turn (id mod 8): each XCD gets a contiguous range of the
+    // tile-major order, so the channel groups of one tile read its input through one L2.
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int jobs = a.n_tiles * a.n_mgroups, jq = jobs >> 3, jr = jobs & 7;
+    if (slot >= jq + (xcd < jr ? 1 : 0)) return;  // the whole workgroup, before any barrier
+    const int job = xcd * jq + min(xcd, jr) + slot;
+    const int tile = job / a.n_mgroups, mg = job - tile * a.n_mgroups;
+    const int t0 = tile * kMfmaTP;
+    const int HW = a.H * a.W;
+
+    // ---- staging: a task is one window position and 8 channels; which half is wave-uniform
+    // because WR is a multiple of 64
+    int src[kTasks];
+#pragma unroll
+    for (int i = 0; i < kTasks; ++i) {
+        const int task = tid + i * kThreads;
+        const int u = t0 + (task >= WR ? task - WR : task);
+        const int n = u / a.plane, rem = u - n * a.plane;
+        const int y = rem / a.pitch - a.pad, x = rem % a.pitch - a.pad;
+        src[i] = (task < 2 * WR && n < a.N && y >= 0 && x >= 0) ? n * a.C * HW + y * a.W + x : -1;
+    }
+    float st[kTasks][8];
+    auto fetch = [&](int kc) {
+#pragma unroll
+        for (int i = 0; i < kTasks; ++i) {
+            const int half = (wave * 64 + i * kThreads) >= WR ? 1 : 0;  // wave-uniform
+            const int c0 = kc * 16 + half * 8;
+            const float* __restrict__ p = a.in + (size_t)c0 * HW;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                st[i][j] = 0.0f;
+                if (c0 + j < a.C && src[i] >= 0) st[i][j] = p[(size_t)j * HW + src[i]];
+            }
+        }
+    };
+    uint32_t largest = 0;  // of |x| as an integer: Inf and NaN are the largest
+    auto commit = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < kTasks; ++i) {
+            const int task = tid + i * kThreads;
+            b8 h, m, l;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float x = st[i][j];
+                largest = max(largest, __float_as_uint(x) & 0x7fffffffu);
+                h[j] = (__bf16)x;
+                const float r = x - (float)h[j];
+                m[j] = (__bf16)r;
+                l[j] = (__bf16)(r - (float)m[j]);
+            }
+            if (2 * WR % kThreads == 0 || task < 2 * WR) {
+                b8* const o = win + buf * kBuf + (task >= WR ? task - WR + WR : task);
+                o[0] = h;
+                o[2 * WR] = m;
+                o[4 * WR] = l;
+            }
+        }
+    };
+
+    f16v big[2], small[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) { big[q] = (f16v)(0.0f); small[q] = (f16v)(0.0f); }
+
+    const int RS = a.R * a.S;
+    const int row_blk = mg * kMfmaWM + wm;
+    const b8* __restrict__ w = a.w + (size_t)row_blk * a.n_chunks * RS * 192 + lane;
+    b8 wa[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) wa[s] = w[64 * s];
+    fetch(0);
+    commit(0);
+    __syncthreads();
+    for (int kc = 0; kc < a.n_chunks; ++kc) {
+        const bool more = kc + 1 < a.n_chunks;
+        if (more) fetch(kc + 1);
+        const b8* row = win + (kc & 1) * kBuf + (lane >> 5) * WR + wp * 64 + (lane & 31);
+        for (int r = 0; r < a.R; ++r, row += a.pitch - a.S)
+#pragma unroll 1
+            for (int s = 0; s < a.S; ++s, ++row) {
+                b8 x[2][3];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) x[q][k] = row[32 * q + 2 * WR * k];
+                const b8 c0 = wa[0], c1 = wa[1], c2 = wa[2];
+                w += 192;  // the table ends with one spare step
+#pragma unroll
+                for (int k = 0; k < 3; ++k) wa[k] = w[64 * k];
+#define ESCOIN_MFMA(ACC, A, B)                                                                            \
+    _Pragma("unroll") for (int q = 0; q < 2; ++q) ACC[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, x[q][B], ACC[q], 0, 0, 0);
+                ESCOIN_MFMA(big, c0, 0)
+                ESCOIN_MFMA(small, c2, 0)
+                ESCOIN_MFMA(small, c0, 2)
+                ESCOIN_MFMA(small, c1, 1)
+                ESCOIN_MFMA(small, c1, 0)
+                ESCOIN_MFMA(small, c0, 1)
+#undef ESCOIN_MFMA
+            }
+        if (more) commit((kc + 1) & 1);  // that buffer was last read before the previous barrier
+        __syncthreads();
+    }
+
+    const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
+    const int EF = a.E * a.F;
+    if (__syncthreads_or(largest >= 0x7f7f8000u)) {  // rounds to infinity in bf16
+        for (int i = tid; i < kTM * kMfmaTP; i += kThreads) {
+            const int m = mg * kTM + i / kMfmaTP, u = t0 + i % kMfmaTP;
+            const int n = u / a.plane, rem = u - n * a.plane, h = rem / a.pitch, x = rem % a.pitch;
+            if (m >= a.M || n >= a.N || h >= a.E || x >= a.F) continue;
+            float acc = 0.0f;
+            for (int j = a.rowptr[m]; j < a.rowptr[m + 1]; ++j) {
+                const MfmaNz z = a.nz[j];
+                const int c = z.c, yy = h + z.r - a.pad, xx = x + z.s - a.pad;
+                if ((unsigned)yy < (unsigned)a.H && (unsigned)xx < (unsigned)a.W)
+                    acc = fmaf(z.val, a.in[((size_t)n * a.C + c) * HW + yy * a.W + xx], acc);
+            }
+            acc += has_bias ? a.bias[m] : 0.0f;
+            if (relu) acc = acc > 0.0f ? acc : 0.0f;
+            a.out[((size_t)n * a.M + m) * EF + h * a.F + x] = acc;
+        }
+        return;
+    }
+    // A lane holds, per 32 positions, 16 output channels of one position: 8*(i/4) + 4*(lane/32) + i%4.
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int u = t0 + wp * 64 + q * 32 + (lane & 31);
+        const int n = u / a.plane, rem = u - n * a.plane, h = rem / a.pitch, x = rem % a.pitch;
+        if (n >= a.N || h >= a.E || x >= a.F) continue;
+        const int m0 = row_blk * 32 + 4 * (lane >> 5);
+        float* __restrict__ o = a.out + ((size_t)n * a.M + m0) * EF + h * a.F + x;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int dm = 8 * (i / 4) + i % 4;
+            if (m0 + dm >= a.M) continue;
+            float v = big[q][i] + small[q][i] + (has_bias ? a.bias[m0 + dm] : 0.0f);
+            if (relu) v = v > 0.0f ? v : 0.0f;
+            o[(size_t)dm * EF] = v;
+        }
+    }
+}
+
+template <int WR>
+int start(const MfmaArgs& a, unsigned blocks, hipStream_t stream) {
+    // Two workgroups fit a compute unit and share its matrix cores.  A launch that has no more than one
+    // for each compute unit asks for so much LDS that they do not double up beside idle ones.
+    constexpr int two = 2 * 6 * WR * 16;
+    const int lds = blocks <= 256 ? std::max(two, 84 * 1024) : two;
+    int rc = allow_dynamic_lds((const void*)sconv_mfma_kernel<WR>, lds);
+    if (rc != ESCOIN_OK) return rc;
+    return launch(sconv_mfma_kernel<WR>, dim3(blocks), dim3(kThreads), (size_t)lds, stream, a);
+}
+
+}  // namespace
+
+int launch_sconv_mfma(const Dims& d, const PlanHeader& h, const char* d_plan, const float* d_in, float* d_out,
+                      const float* d_bias, uint32_t flags, hipStream_t stream) {
+    MfmaArgs a;
+    a.in = d_in; a.out = d_out; a.bias = d_bias; a.flags = flags;
+    a.w = (const b8*)(d_plan + h.off_mfma);
+    a.rowptr = (const int32_t*)(d_plan + h.off_mfma + mfma_weight_bytes(d));
+    a.nz = (const MfmaNz*)(d_plan + h.off_mfma + mfma_weight_bytes(d) + mfma_rowptr_bytes(d));
+    a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad;
+    a.pitch = d.W + d.pad;
+    a.plane = (d.H + d.pad) * a.pitch;
+    a.total = d.N * a.plane;
+    a.n_chunks = (d.C + 15) / 16;
+    a.n_mgroups = (d.M + kTM - 1) / kTM;
+    a.n_tiles = (a.total + kMfmaTP - 1) / kMfmaTP;
+    const unsigned blocks = (unsigned)((long long)a.n_tiles * a.n_mgroups + 7) / 8 * 8;
+    const int window = mfma_window(d);
+    if (window <= 320) return start<320>(a, blocks, stream);
+    if (window <= 384) return start<384>(a, blocks, stream);
+    return start<512>(a, blocks, stream);
+}
+
+}  // namespace escoin

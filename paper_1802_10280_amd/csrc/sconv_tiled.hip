@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "common.h"
+#include "mfma.h"
 #include "plan.h"
 
 namespace escoin {
@@ -557,27 +558,6 @@ __global__ __launch_bounds__(256) void relu_kernel(float* __restrict__ p, size_t
 
 typedef void (*TiledKernel)(const TiledArgs);
 
-// A kernel that wants more than 64 KB of dynamic LDS has to be told so once per device; the
-// largest size granted so far is remembered, so that later launches skip the runtime call.
-int allow_dynamic_lds(const void* kernel, int bytes) {
-    struct Granted { int device; const void* kernel; int bytes; };
-    static std::mutex mu;
-    static std::vector<Granted> granted;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return ESCOIN_EHIP;
-    std::lock_guard<std::mutex> lock(mu);
-    for (Granted& gr : granted)
-        if (gr.device == dev && gr.kernel == kernel) {
-            if (gr.bytes >= bytes) return ESCOIN_OK;
-            if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return ESCOIN_EHIP;
-            gr.bytes = bytes;
-            return ESCOIN_OK;
-        }
-    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return ESCOIN_EHIP;
-    granted.push_back({dev, kernel, bytes});
-    return ESCOIN_OK;
-}
-
 // (K, Q, B) instantiations: the ones that fit 128 VGPRs (four waves per SIMD) without spilling.
 #define ESCOIN_TILED_VARIANTS(X) \
     X(1, 1, 2) X(1, 2, 2) X(2, 1, 2) X(2, 1, 4) X(2, 2, 2) X(2, 2, 4) X(4, 1, 2) X(4, 1, 4) X(4, 2, 2) X(8, 1, 2) X(8, 1, 4)
@@ -607,6 +587,27 @@ TiledKernel pick(int K, int Q, int B, bool wide_staging, bool dma_staging) {
 }
 
 }  // namespace
+
+// A kernel that wants more than 64 KB of dynamic LDS has to be told so once per device; the
+// largest size granted so far is remembered, so that later launches skip the runtime call.
+int allow_dynamic_lds(const void* kernel, int bytes) {
+    struct Granted { int device; const void* kernel; int bytes; };
+    static std::mutex mu;
+    static std::vector<Granted> granted;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return ESCOIN_EHIP;
+    std::lock_guard<std::mutex> lock(mu);
+    for (Granted& gr : granted)
+        if (gr.device == dev && gr.kernel == kernel) {
+            if (gr.bytes >= bytes) return ESCOIN_OK;
+            if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return ESCOIN_EHIP;
+            gr.bytes = bytes;
+            return ESCOIN_OK;
+        }
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return ESCOIN_EHIP;
+    granted.push_back({dev, kernel, bytes});
+    return ESCOIN_OK;
+}
 
 bool tiled_wide_staging_exists(int K, int Q, int B) {
 #define ESCOIN_HAS(KK, QQ, BB) \
@@ -667,6 +668,9 @@ extern "C" int escoin_sconv_forward_tiled(const escoin_conv_desc* desc, const vo
                                 h.max_regions * region_bytes) ||
         h.lds_bytes > 160 * 1024)
         return ESCOIN_EINVAL;
+
+    if (h.mfma == 1 && ((uintptr_t)d_plan & 15) == 0 && mfma_planned(d, h.nnz) && mfma_chosen(d, h.nnz))
+        return launch_sconv_mfma(d, h, (const char*)d_plan, d_in, d_out, d_bias, flags, (hipStream_t)hip_stream);
 
     const char* base = (const char*)d_plan;
     TiledArgs a;

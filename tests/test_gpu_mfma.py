@@ -1,0 +1,104 @@
+"""The matrix-core form of the tiled entry point against the oracle, where its tiling can go wrong: channel counts off
+the blocks of 16 and 64, batches whose flat padded array ends inside a tile, every filter shape, one tile and many."""
+import numpy as np
+import pytest
+
+import paper_1802_10280_amd as esc
+from helpers import DeviceLayer, assert_within_bound, oracle_full
+from paper_1802_10280_amd import workloads as wl
+
+gpu = pytest.mark.gpu
+
+# N, C, H, W, M, R, S, pad, sparsity
+SHAPES = [
+    (96, 64, 16, 16, 64, 3, 3, 1, 0.0),      # whole blocks of channels
+    (105, 49, 15, 17, 65, 3, 3, 1, 0.0),     # one channel over on both sides, an odd batch
+    (301, 47, 7, 7, 129, 3, 3, 1, 0.0),      # small maps, channels short of a block
+    (80, 17, 33, 20, 60, 5, 5, 2, 0.2),
+    (120, 33, 18, 13, 112, 3, 4, 0, 0.0),    # no padding: taps reach the end of a row, not past it
+    (90, 24, 13, 18, 120, 5, 3, 1, 0.0),     # padding smaller than the reach
+    (23, 48, 60, 61, 64, 3, 3, 1, 0.3),      # the widest rows
+]
+
+
+def chosen(L):
+    """The rule that sends a call to the matrix cores, written out once more."""
+    s = L.spec
+    groups, chunks = -(-s.M // 64), -(-s.C // 16)
+    jobs = -(-s.N * (s.H + s.pad) * (s.W + s.pad) // 256) * groups
+    job = 6.0 + chunks * (1.6 + 0.46 * s.R * s.S)
+    us = job if jobs <= 256 else -(-jobs // 512) * 1.72 * job
+    return us < 0.9 * 2e-6 * L.nnz * s.N * s.E * s.F / 36.0
+
+
+@gpu
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_against_the_oracle(oracle, shape):
+    print("mfma", shape, flush=True)
+    N, C, H, W, M, R, S, pad, sparsity = shape
+    L = wl.custom_layer(N, C, H, W, M, R, S, 1, pad, sparsity, seed=71, dist="normal")
+    assert chosen(L)
+    dl = DeviceLayer(esc, L)
+    for flags in (0, esc.F_BIAS | esc.F_RELU):
+        got = dl.forward_tiled(flags)
+        assert esc.plan_header(dl.plan)["mfma"] == 1
+        ref, bound = oracle_full(oracle, L, flags)
+        assert np.isfinite(got).all()
+        worst = assert_within_bound(got, ref, bound, (shape, flags))
+        # the split is exact and the products left out are below 2^-24 of |x*w|: a sum of at most C*R*S fp32
+        # roundings, of which a random walk's share shows
+        assert worst <= 2.0 ** -24 * 4 * np.sqrt(C * R * S), worst
+
+
+@gpu
+def test_non_finite_inputs_reach_only_nonzero_weights(oracle):
+    print("mfma non-finite", flush=True)
+    L = wl.custom_layer(200, 50, 12, 13, 98, 3, 3, 1, 1, 0.05, seed=72, dist="normal")
+    L.input[1, 2, 5, 6] = np.inf
+    L.input[2, 0, 0, 0] = np.nan
+    L.input[199, 49, 11, 12] = -np.inf
+    L.input[20, 3, 4, 4] = 3.4e38            # finite, but not in bf16
+    assert chosen(L)
+    for flags in (0, esc.F_BIAS):
+        dl = DeviceLayer(esc, L)
+        got = dl.forward_tiled(flags)
+        assert esc.plan_header(dl.plan)["mfma"] == 1
+        with np.errstate(invalid="ignore", over="ignore"):
+            ref, bound = oracle_full(oracle, L, flags)
+        bad = ~np.isfinite(ref)
+        assert bad.any() and (bad == ~np.isfinite(got)).all()
+        assert (np.abs(got[~bad] - ref[~bad]) <= 1e-4 * bound[~bad]).all()
+
+
+def test_what_the_form_cannot_hold_stays_with_the_tiled_kernel():
+    """A repeated column and a weight that is not finite in bf16 leave the plan without the section."""
+    L = wl.custom_layer(40, 64, 12, 12, 64, 3, 3, 1, 1, 0.0, seed=73, dist="normal")
+    d = esc.desc_of(L.spec)
+    st = esc.escoin_sconv_pack(d, L.rowptr, L.colidx)
+    assert esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, st, L.value))["mfma"] == 1
+    twice = st.copy()
+    twice[1] = twice[0]
+    assert esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, twice, L.value))["mfma"] == 0
+    for v in (np.inf, np.nan, 3.4e38):
+        value = L.value.copy()
+        value[5] = v
+        assert esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, st, value))["mfma"] == 0
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_split_weights_add_up_to_the_csr(shape):
+    N, C, H, W, M, R, S, pad, sparsity = shape
+    L = wl.custom_layer(1, C, H, W, M, R, S, 1, pad, sparsity, seed=74, dist="normal")
+    d = esc.desc_of(L.spec)
+    plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+    h = esc.plan_header(plan)
+    blocks, chunks = -(-M // 64) * 2, -(-C // 16)
+    raw = plan[h["off_mfma"]:h["off_mfma"] + blocks * chunks * R * S * 3072].view(np.uint16)
+    w = (raw.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    w = w.reshape(blocks, chunks, R * S, 3, 2, 32, 8).sum(3)        # the three parts add up exactly
+    w = w.transpose(0, 4, 1, 3, 5, 2).reshape(blocks * 32, chunks * 16, R * S)
+    want = np.zeros((blocks * 32, chunks * 16 * R * S))
+    for m in range(M):
+        row = slice(L.rowptr[m], L.rowptr[m + 1])
+        want[m, L.colidx[row]] = L.value[row]
+    assert (w.reshape(want.shape) == want).all()
