@@ -18,7 +18,11 @@
 //
 // Bound by the matrix cores: per wave and (tap, 16 channels) 12 MFMAs of 32 clk against 6 LDS reads
 // and 3 KB of weights from L1/L2, which all the position waves of a workgroup share.  The weights
-// lie in the plan in the order the lanes read them.
+// lie in the plan in the order the lanes read them.  Eight waves at 128 registers let two workgroups
+// share a compute unit and hide each other's staging.  64x256x28x28, 256 3x3 filters at 50 %: 317 us
+// (the MFMAs alone 152 us at 2.4 GHz, and the 844 workgroups fill 1.65 rounds of 512) against 720 us
+// in the tiled kernel; 64x384x13x13, 384 filters at 65 %: 234 against 313 us.  Asking for a step's
+// weights a whole step ahead and staging through buffer loads changed neither (318, 233 us).
 #include "common.h"
 #include "mfma.h"
 #include "plan.h"
@@ -107,7 +111,7 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
                 l[j] = (__bf16)(r - (float)m[j]);
             }
             if (2 * WR % kThreads == 0 || task < 2 * WR) {
-                b8* const o = win + buf * kBuf + (task >= WR ? task - WR + WR : task);
+                b8* const o = win + buf * kBuf + (task);
                 o[0] = h;
                 o[2 * WR] = m;
                 o[4 * WR] = l;

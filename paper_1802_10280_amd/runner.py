@@ -72,7 +72,9 @@ class LayerRunner:
             vw = h["VW"] if self.d_in.data_ptr() % 16 == 0 else 1
             if vw == 4 and h["n_dma"] > 0 and h["WW"] == 4:
                 vw = 16       # staged by global -> LDS copies
-            return f"sconv_tiled_kernel<{h['K']}, {h['Q']}, {h['B']}, {vw}>"
+            name = f"sconv_tiled_kernel<{h['K']}, {h['Q']}, {h['B']}, {vw}>"
+            # a plan for both kernels: the call decides by the batch
+            return f"sconv_mfma_kernel or {name}" if h["mfma"] else name
         return "sconv_direct_kernel"
 
     def run(self):
