@@ -13,8 +13,9 @@
 // that the running sum is rounded once per 16 channels, the five small ones share another.
 //
 // A finite input whose h rounds to infinity, an Inf or a NaN would spread to outputs that only meet
-// it under a zero weight.  Staging notices them; a workgroup that has seen one computes its
-// outputs again from the nonzeros alone.
+// it under a zero weight; and where a product passes the largest float, so may its parts, with both
+// signs.  Either way the two sums hold an Inf or a NaN: an output whose sum is not finite is
+// computed again, from the nonzeros alone.
 //
 // Bound by the matrix cores: per wave and (tap, 16 channels) 12 MFMAs of 32 clk against 6 LDS reads
 // and 3 KB of weights from L1/L2, which all the position waves of a workgroup share.  The weights
@@ -23,6 +24,8 @@
 // (the MFMAs alone 152 us at 2.4 GHz, and the 844 workgroups fill 1.65 rounds of 512) against 720 us
 // in the tiled kernel; 64x384x13x13, 384 filters at 65 %: 234 against 313 us.  Asking for a step's
 // weights a whole step ahead and staging through buffer loads changed neither (318, 233 us).
+#include <float.h>
+
 #include "common.h"
 #include "mfma.h"
 #include "plan.h"
@@ -95,7 +98,6 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
             }
         }
     };
-    uint32_t largest = 0;  // of |x| as an integer: Inf and NaN are the largest
     auto commit = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < kTasks; ++i) {
@@ -104,7 +106,6 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float x = st[i][j];
-                largest = max(largest, __float_as_uint(x) & 0x7fffffffu);
                 h[j] = (__bf16)x;
                 const float r = x - (float)h[j];
                 m[j] = (__bf16)r;
@@ -164,40 +165,42 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
 
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
     const int EF = a.E * a.F;
-    if (__syncthreads_or(largest >= 0x7f7f8000u)) {  // rounds to infinity in bf16
-        for (int i = tid; i < kTM * kMfmaTP; i += kThreads) {
-            const int m = mg * kTM + i / kMfmaTP, u = t0 + i % kMfmaTP;
-            const int n = u / a.plane, rem = u - n * a.plane, h = rem / a.pitch, x = rem % a.pitch;
-            if (m >= a.M || n >= a.N || h >= a.E || x >= a.F) continue;
-            float acc = 0.0f;
-            for (int j = a.rowptr[m]; j < a.rowptr[m + 1]; ++j) {
-                const MfmaNz z = a.nz[j];
-                const int c = z.c, yy = h + z.r - a.pad, xx = x + z.s - a.pad;
-                if ((unsigned)yy < (unsigned)a.H && (unsigned)xx < (unsigned)a.W)
-                    acc = fmaf(z.val, a.in[((size_t)n * a.C + c) * HW + yy * a.W + xx], acc);
-            }
-            acc += has_bias ? a.bias[m] : 0.0f;
-            if (relu) acc = acc > 0.0f ? acc : 0.0f;
-            a.out[((size_t)n * a.M + m) * EF + h * a.F + x] = acc;
-        }
-        return;
-    }
     // A lane holds, per 32 positions, 16 output channels of one position: 8*(i/4) + 4*(lane/32) + i%4.
+    const int m0 = row_blk * 32 + 4 * (lane >> 5);
+    uint32_t again = 0;  // bit 16*q + i: that sum cannot be used
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int u = t0 + wp * 64 + q * 32 + (lane & 31);
         const int n = u / a.plane, rem = u - n * a.plane, h = rem / a.pitch, x = rem % a.pitch;
         if (n >= a.N || h >= a.E || x >= a.F) continue;
-        const int m0 = row_blk * 32 + 4 * (lane >> 5);
         float* __restrict__ o = a.out + ((size_t)n * a.M + m0) * EF + h * a.F + x;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int dm = 8 * (i / 4) + i % 4;
             if (m0 + dm >= a.M) continue;
-            float v = big[q][i] + small[q][i] + (has_bias ? a.bias[m0 + dm] : 0.0f);
+            const float sum = big[q][i] + small[q][i];
+            if (!(fabsf(sum) <= FLT_MAX)) again |= 1u << (16 * q + i);
+            float v = sum + (has_bias ? a.bias[m0 + dm] : 0.0f);
             if (relu) v = v > 0.0f ? v : 0.0f;
             o[(size_t)dm * EF] = v;
         }
+    }
+    // From the nonzeros, one output of the lane after the other (stored once more, by the same lane).
+    while (again) {
+        const int bit = __builtin_ctz(again), q = bit >> 4, i = bit & 15, m = m0 + 8 * (i / 4) + i % 4;
+        again &= again - 1;
+        const int u = t0 + wp * 64 + q * 32 + (lane & 31);
+        const int n = u / a.plane, rem = u - n * a.plane, h = rem / a.pitch, x = rem % a.pitch;
+        float v = 0.0f;
+        for (int j = a.rowptr[m]; j < a.rowptr[m + 1]; ++j) {
+            const MfmaNz z = a.nz[j];
+            const int y = h + z.r - a.pad, xx = x + z.s - a.pad;
+            if ((unsigned)y < (unsigned)a.H && (unsigned)xx < (unsigned)a.W)
+                v = fmaf(z.val, a.in[((size_t)n * a.C + z.c) * HW + y * a.W + xx], v);
+        }
+        v += has_bias ? a.bias[m] : 0.0f;
+        if (relu) v = v > 0.0f ? v : 0.0f;
+        a.out[((size_t)n * a.M + m) * EF + h * a.F + x] = v;
     }
 }
 

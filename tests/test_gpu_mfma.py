@@ -50,6 +50,38 @@ def test_against_the_oracle(oracle, shape):
         assert worst <= 2.0 ** -24 * 4 * np.sqrt(C * R * S), worst
 
 
+def set_weight(L, m, c, tap, value):
+    """The weight of channel m at (input channel c, tap); the CSR has to hold it."""
+    row = slice(L.rowptr[m], L.rowptr[m + 1])
+    at = np.flatnonzero(L.colidx[row] == c * L.spec.R * L.spec.S + tap)
+    assert len(at) == 1
+    L.value[L.rowptr[m] + at[0]] = value
+
+
+@gpu
+def test_products_around_the_largest_float(oracle):
+    """Finite operands whose product overflows: Inf with its sign, never NaN (the parts of such a product overflow
+    with both signs); a product just below the largest float stays finite (the leading parts' product is above it)."""
+    print("mfma overflow", flush=True)
+    L = wl.custom_layer(105, 49, 15, 17, 65, 3, 3, 1, 1, 0.0, seed=75, dist="normal")
+    L.value *= np.float32(0.2)               # every other product of these inputs stays far below the limit
+    L.input[:] = 0
+    near = np.float32(1.00391 * 2.0 ** 20)
+    for image, c, m, x, w in ((3, 4, 2, 1e38, 2057.0), (9, 7, 33, 3e38, 4117.0), (17, 20, 64, -3e38, 4117.0),
+                              (104, 48, 0, 1e38, 2057.0), (50, 30, 40, 3.4028e38 / float(near), near)):
+        L.input[image, c, 5, 6] = x
+        set_weight(L, m, c, 4, w)
+    assert chosen(L)
+    with np.errstate(over="ignore"):
+        ref, bound = oracle_full(oracle, L)
+    dl = DeviceLayer(esc, L)
+    got = dl.forward_tiled()
+    assert esc.plan_header(dl.plan)["mfma"] == 1
+    over = np.isinf(ref)
+    assert over.sum() == 4 and (got[over] == ref[over]).all()
+    assert_within_bound(got[~over], ref[~over], bound[~over])
+
+
 @gpu
 def test_non_finite_inputs_reach_only_nonzero_weights(oracle):
     print("mfma non-finite", flush=True)
