@@ -213,7 +213,7 @@ class _PlanHeader(ctypes.Structure):
                 + [(k, ctypes.c_int32) for k in (
                     "CS", "pitch1", "VW", "WW", "WS", "CC0", "zero_floats", "max_regions", "MB", "n_dma")]
                 + [("off_dma", ctypes.c_uint64), ("off_zero", ctypes.c_uint64),
-                   ("mfma", ctypes.c_int32), ("reserved", ctypes.c_int32), ("off_mfma", ctypes.c_uint64)])
+                   ("mfma", ctypes.c_int32), ("mfma_nnz", ctypes.c_int32), ("off_mfma", ctypes.c_uint64)])
 
 
 def plan_header(plan: np.ndarray) -> dict:

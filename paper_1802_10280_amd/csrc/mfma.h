@@ -9,7 +9,12 @@ constexpr int kMfmaWM = 2, kMfmaWP = 4;      // waves of a workgroup over channe
 constexpr int kMfmaTP = 64 * kMfmaWP;        // output positions of a workgroup
 constexpr int kMfmaMaxWindow = 512;          // window positions it can stage (two tasks a thread)
 
-// A nonzero, for the workgroups that meet an Inf or a NaN.
+// The weights the section can hold.  Below 2^-110 the three bf16 parts are no longer exact (bf16 ends at
+// 2^-133, fp32 at 2^-149).  The limits lie well inside that, so that the parts of the products stay inside
+// the normal numbers too, with inputs down to 2^-40.
+constexpr float kMfmaLeastWeight = 0x1p-50f, kMfmaMostWeight = 0x1p30f;
+
+// A nonzero, for the outputs whose sums cannot be used.
 struct MfmaNz {
     int32_t c;
     uint16_t r, s;

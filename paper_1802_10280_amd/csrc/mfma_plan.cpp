@@ -49,8 +49,9 @@ static float to_bf16(float x, uint16_t* bits) {  // rounds to nearest even; x is
     return r;
 }
 
-// Writes the section into `out` (zeroed).  False where it cannot stand for the CSR: a value that is
-// not finite in bf16, or a repeated column, whose values would have to be added up first.
+// Writes the section into `out` (zeroed).  False where it cannot stand for the CSR: a value outside the
+// range whose split keeps fp32 (Inf and NaN too), or a repeated column, whose values would have to be
+// added up first.
 bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value, char* out) {
     const size_t RS = (size_t)d.R * d.S, chunks = mfma_chunks(d);
     uint16_t* w = (uint16_t*)out;
@@ -68,7 +69,7 @@ bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, 
             if (was == m) return false;
             was = m;
             uint16_t part[3];
-            if (!(fabsf(value[j]) < 3.38e38f)) return false;
+            if (!(fabsf(value[j]) >= kMfmaLeastWeight && fabsf(value[j]) <= kMfmaMostWeight)) return false;
             const float rest = value[j] - to_bf16(value[j], &part[0]);
             to_bf16(rest - to_bf16(rest, &part[1]), &part[2]);
             // lane: channel m % 32, and which 8 of the 16 input channels; 8 of them per lane

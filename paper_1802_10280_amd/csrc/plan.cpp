@@ -687,7 +687,7 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
     off = align_up64(off + 64, 256);
     // A plan whose tiling the caller fixed is for the tiled kernel alone.
     const bool with_mfma = !tuned && mfma_planned(d, rowptr[d.M]);
-    h.mfma = 0;
+    h.mfma = h.mfma_nnz = 0;
     h.off_mfma = off;
     if (with_mfma) off = align_up64(off + mfma_bytes(d, rowptr[d.M]), 256);
     h.total_bytes = off;
@@ -778,6 +778,7 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
                 }
     }
     h.mfma = with_mfma && mfma_write(d, rowptr, stretched, value, base + h.off_mfma) ? 1 : 0;
+    if (h.mfma) h.mfma_nnz = (int32_t)nnz_total;
     std::memcpy(base, &h, sizeof(h));  // the header once more, now with WW, n_dma and mfma
     std::memcpy(base + h.off_lanes, lanes.data(), lanes.size() * sizeof(LaneSlot));
     std::memcpy(base + h.off_perm, slot.data(), slot.size() * sizeof(RowSlot));

@@ -100,7 +100,8 @@ struct PlanHeader {
     uint64_t off_zero;   // 64 zero bytes: what the copy of a slot without input reads
     int32_t mfma;        // 1: the section for the matrix cores is there (mfma.h); a plan without it,
                          // or one saved before there was such a section, holds 0 here
-    int32_t reserved;
+    int32_t mfma_nnz;    // nonzero values in that section; 0 in plans from before their range was
+                         // checked, which stay with the tiled kernel
     uint64_t off_mfma;   // split weights, row pointers, nonzeros
 };
 static_assert(sizeof(PlanHeader) <= 512, "the sections start 512 bytes into the blob");

@@ -117,6 +117,35 @@ def test_what_the_form_cannot_hold_stays_with_the_tiled_kernel():
         assert esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, st, value))["mfma"] == 0
 
 
+def test_weights_out_of_the_range_that_splits_exactly_stay_with_the_tiled_kernel():
+    L = wl.custom_layer(40, 64, 12, 12, 64, 3, 3, 1, 1, 0.0, seed=73, dist="normal")
+    d = esc.desc_of(L.spec)
+    st = esc.escoin_sconv_pack(d, L.rowptr, L.colidx)
+    least, most = np.float32(2.0 ** -50), np.float32(2.0 ** 30)
+    for v, kept in ((least, 1), (np.nextafter(least, np.float32(0)), 0), (np.float32(2.0 ** -118), 0), (np.float32(1e-45), 0),
+                    (most, 1), (np.nextafter(most, np.float32(np.inf)), 0)):
+        for sign in (1, -1):
+            value = L.value.copy()
+            value[5] = sign * v
+            h = esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, st, value))
+            assert h["mfma"] == kept and h["mfma_nnz"] == kept * L.nnz, v
+
+
+@gpu
+@pytest.mark.parametrize("power", [-60, -100, -112, -118, -123])
+def test_small_weights(oracle, power):
+    print("mfma small weights", power, flush=True)
+    L = wl.custom_layer(105, 49, 15, 17, 65, 3, 3, 1, 1, 0.0, seed=76, dist="normal")
+    L.value *= np.float32(2.0 ** power)
+    L.input *= np.float32(1024)
+    dl = DeviceLayer(esc, L)
+    got = dl.forward_tiled()
+    ref, bound = oracle_full(oracle, L)
+    # fp32: every one of the C*R*S products and sums rounds by 2^-24 of sum|w*x|, or by half a subnormal's 2^-149
+    n = L.spec.C * L.spec.R * L.spec.S
+    assert (np.abs(got - ref) <= 2.0 ** -24 * 4 * np.sqrt(n) * bound + n * 2.0 ** -150).all()
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_split_weights_add_up_to_the_csr(shape):
     N, C, H, W, M, R, S, pad, sparsity = shape
