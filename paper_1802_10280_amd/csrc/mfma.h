@@ -10,8 +10,8 @@ constexpr int kMfmaTP = 64 * kMfmaWP;        // output positions of a workgroup
 constexpr int kMfmaMaxWindow = 512;          // window positions it can stage (two tasks a thread)
 
 // The weights the section can hold.  Below 2^-110 the three bf16 parts are no longer exact (bf16 ends at
-// 2^-133, fp32 at 2^-149).  The limits lie well inside that, so that the parts of the products stay inside
-// the normal numbers too, with inputs down to 2^-40.
+// 2^-133, fp32 at 2^-149).  The limits lie well inside that, so that the products keep their bits with
+// inputs down to 2^-70 (the kernel looks for smaller ones).
 constexpr float kMfmaLeastWeight = 0x1p-50f, kMfmaMostWeight = 0x1p30f;
 
 // A nonzero, for the outputs whose sums cannot be used.

@@ -17,6 +17,11 @@
 // signs.  Either way the two sums hold an Inf or a NaN: an output whose sum is not finite is
 // computed again, from the nonzeros alone.
 //
+// bf16 ends at 2^-133, so the parts of an input below 2^-110 lose bits, and those of a product below
+// 2^-120 too.  Staging notes whether it met a nonzero |x| below 2^-70 (weights are 2^-50 at least); if so,
+// sums below 2^-58 are computed again as well.  In the others, what such inputs lose (3 * 2^-134 * 2^30 a
+// product, fewer than 2^18 products) is below 2^-25 of the sum.
+//
 // Bound by the matrix cores: per wave and (tap, 16 channels) 12 MFMAs of 32 clk against 6 LDS reads
 // and 3 KB of weights from L1/L2, which all the position waves of a workgroup share.  The weights
 // lie in the plan in the order the lanes read them.  Eight waves at 128 registers let two workgroups
@@ -52,6 +57,7 @@ struct MfmaArgs {
 
 constexpr int kThreads = 64 * kMfmaWM * kMfmaWP;
 constexpr int kTM = 32 * kMfmaWM;
+constexpr float kTinyInput = 0x1p-70f, kTinySum = 0x1p-58f;
 
 // WR: window positions held in LDS (kTP and the reach of the taps, see mfma_window).
 template <int WR>
@@ -98,6 +104,7 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
             }
         }
     };
+    uint32_t least = 0xffffffffu;  // of the nonzero |x|, as 2 * bits - 1 (a zero becomes the largest)
     auto commit = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < kTasks; ++i) {
@@ -106,6 +113,7 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float x = st[i][j];
+                least = min(least, (__float_as_uint(x) << 1) - 1u);
                 h[j] = (__bf16)x;
                 const float r = x - (float)h[j];
                 m[j] = (__bf16)r;
@@ -163,6 +171,7 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
         __syncthreads();
     }
 
+    const bool tiny = __syncthreads_or(least < 2u * __float_as_uint(kTinyInput) - 1u);
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
     const int EF = a.E * a.F;
     // A lane holds, per 32 positions, 16 output channels of one position: 8*(i/4) + 4*(lane/32) + i%4.
@@ -179,7 +188,7 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
             const int dm = 8 * (i / 4) + i % 4;
             if (m0 + dm >= a.M) continue;
             const float sum = big[q][i] + small[q][i];
-            if (!(fabsf(sum) <= FLT_MAX)) again |= 1u << (16 * q + i);
+            if (!(fabsf(sum) <= FLT_MAX) || (tiny && fabsf(sum) < kTinySum)) again |= 1u << (16 * q + i);
             float v = sum + (has_bias ? a.bias[m0 + dm] : 0.0f);
             if (relu) v = v > 0.0f ? v : 0.0f;
             o[(size_t)dm * EF] = v;

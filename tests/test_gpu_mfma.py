@@ -146,6 +146,30 @@ def test_small_weights(oracle, power):
     assert (np.abs(got - ref) <= 2.0 ** -24 * 4 * np.sqrt(n) * bound + n * 2.0 ** -150).all()
 
 
+@gpu
+@pytest.mark.parametrize("power", [-72, -100, -112, -123, -134, -145])
+@pytest.mark.parametrize("everywhere", [True, False])
+def test_small_inputs(oracle, power, everywhere):
+    """Inputs too small for three bf16 parts, everywhere or in one channel of some images beside zeros."""
+    print("mfma small inputs", power, everywhere, flush=True)
+    L = wl.custom_layer(105, 49, 15, 17, 65, 3, 3, 1, 1, 0.0, seed=77, dist="normal")
+    small = L.input * np.float32(2.0 ** power)
+    if everywhere:
+        L.input[:] = small
+    else:
+        L.input[::5] = 0
+        L.input[::5, 7] = small[::5, 7]
+    L.value *= np.float32(16)
+    assert chosen(L)
+    dl = DeviceLayer(esc, L)
+    got = dl.forward_tiled()
+    assert esc.plan_header(dl.plan)["mfma"] == 1
+    ref, bound = oracle_full(oracle, L)
+    # as above: fp32 rounding of C*R*S products and sums, or half a subnormal's step each
+    n = L.spec.C * L.spec.R * L.spec.S
+    assert (np.abs(got - ref) <= 2.0 ** -24 * 4 * np.sqrt(n) * bound + n * 2.0 ** -150).all()
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_split_weights_add_up_to_the_csr(shape):
     N, C, H, W, M, R, S, pad, sparsity = shape
