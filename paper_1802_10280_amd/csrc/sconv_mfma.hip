@@ -14,7 +14,7 @@
 //
 // A finite input whose h rounds to infinity, an Inf or a NaN would spread to outputs that only meet
 // it under a zero weight; and where a product passes the largest float, so may its parts, with both
-// signs.  Either way the two sums hold an Inf or a NaN: an output whose sum is not finite is
+// signs.  Either way the two sums hold an Inf or a NaN: a position with a sum that is not finite is
 // computed again, from the nonzeros alone.
 //
 // bf16 ends at 2^-133, so the parts of an input below 2^-110 lose bits, and those of a product below
@@ -58,6 +58,45 @@ struct MfmaArgs {
 constexpr int kThreads = 64 * kMfmaWM * kMfmaWP;
 constexpr int kTM = 32 * kMfmaWM;
 constexpr float kTinyInput = 0x1p-70f, kTinySum = 0x1p-58f;
+
+// An output's place in its image: row and column of its first tap.
+struct Place {
+    const uint32_t* image;
+    int y, x, first, H, W;  // first: y * W + x
+};
+
+// Every step-th nonzero of one output from `j` on.  Eight at a time and no branches, so that their loads are
+// on their way together: past the end the last one is read again, beside the image its first word, and
+// neither counts.  Words: the nonzeros as MfmaNz is laid out; in the constant address space, where `j` is the
+// same for the whole wave, they come through scalar loads.
+template <class Words>
+__device__ inline float walk(Words nz, int j, int end, int step, const Place at) {
+    float v = 0.0f;
+    for (; j < end; j += 8 * step) {
+        uint32_t c[8], rs[8], w[8], keep[8], x[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const auto p = nz + 3 * min(j + t * step, end - 1);
+            c[t] = p[0];
+            rs[t] = p[1];
+            w[t] = p[2];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int r = rs[t] & 0xffffu, s = rs[t] >> 16;
+            const bool in = (uint32_t)(at.y + r) < (uint32_t)at.H & (uint32_t)(at.x + s) < (uint32_t)at.W & j + t * step < end;
+            keep[t] = in ? ~0u : 0u;
+            c[t] = (((int)c[t] * at.H + r) * at.W + s + at.first) & keep[t];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) x[t] = at.image[c[t]];
+        __builtin_amdgcn_sched_barrier(0);  // all eight on their way before the first is waited for
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v = fmaf(__uint_as_float(w[t]), __uint_as_float(x[t] & keep[t]), v);
+    }
+    return v;
+}
+static_assert(sizeof(MfmaNz) == 12, "walk() reads three words a nonzero");
 
 // WR: window positions held in LDS (kTP and the reach of the taps, see mfma_window).
 template <int WR>
@@ -175,41 +214,67 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
     const int EF = a.E * a.F;
     // A lane holds, per 32 positions, 16 output channels of one position: 8*(i/4) + 4*(lane/32) + i%4.
-    const int m0 = row_blk * 32 + 4 * (lane >> 5);
-    uint32_t again = 0;  // bit 16*q + i: that sum cannot be used
+    uint64_t again = 0;  // the wave's positions that have a sum that cannot be used
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int u = t0 + wp * 64 + q * 32 + (lane & 31);
         const int n = u / a.plane, rem = u - n * a.plane, h = rem / a.pitch, x = rem % a.pitch;
-        if (n >= a.N || h >= a.E || x >= a.F) continue;
-        float* __restrict__ o = a.out + ((size_t)n * a.M + m0) * EF + h * a.F + x;
+        const int m0 = row_blk * 32 + 4 * (lane >> 5);
+        bool bad = false;
+        if (n < a.N && h < a.E && x < a.F) {
+            float* __restrict__ o = a.out + ((size_t)n * a.M + m0) * EF + h * a.F + x;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int dm = 8 * (i / 4) + i % 4;
-            if (m0 + dm >= a.M) continue;
-            const float sum = big[q][i] + small[q][i];
-            if (!(fabsf(sum) <= FLT_MAX) || (tiny && fabsf(sum) < kTinySum)) again |= 1u << (16 * q + i);
-            float v = sum + (has_bias ? a.bias[m0 + dm] : 0.0f);
-            if (relu) v = v > 0.0f ? v : 0.0f;
-            o[(size_t)dm * EF] = v;
+            for (int i = 0; i < 16; ++i) {
+                const int dm = 8 * (i / 4) + i % 4;
+                if (m0 + dm >= a.M) continue;
+                const float sum = big[q][i] + small[q][i];
+                bad |= !(fabsf(sum) <= FLT_MAX) || (tiny && fabsf(sum) < kTinySum);
+                float v = sum + (has_bias ? a.bias[m0 + dm] : 0.0f);
+                if (relu) v = v > 0.0f ? v : 0.0f;
+                o[(size_t)dm * EF] = v;
+            }
         }
+        const uint64_t lanes = __ballot(bad);
+        again |= ((lanes | lanes >> 32) & 0xffffffffu) << (32 * q);
     }
-    // From the nonzeros, one output of the lane after the other (stored once more, by the same lane).
-    while (again) {
-        const int bit = __builtin_ctz(again), q = bit >> 4, i = bit & 15, m = m0 + 8 * (i / 4) + i % 4;
-        again &= again - 1;
-        const int u = t0 + wp * 64 + q * 32 + (lane & 31);
+    if (!__syncthreads_or(again != 0)) return;
+
+    // Those positions once more from the nonzeros, all channels of the workgroup: its waves share the
+    // channels, and where a 64-position run has few such positions several lanes share an output's
+    // nonzeros.  (A position of one wave belongs to the waves of the other channels as well, so the
+    // lists meet in LDS; the barriers also order these stores after the ones above.)
+    // Bound by the gathers' latency where few workgroups come here and by their address arithmetic where all
+    // do.  64x256x28x28 at 50 %, when each lane redid its own outputs -> now: one NaN in the batch 6.4 -> 0.5 ms,
+    // one image of them 11.6 -> 4.3, nothing else 32 -> 12.5 (the tiled kernel takes 0.72 whatever the input).
+    uint64_t* const lists = (uint64_t*)win;  // every wave is past its last read of the windows
+    if (lane == 0) lists[wave] = again;
+    __syncthreads();
+    for (int run = 0; run < kMfmaWP; ++run) {
+        uint64_t list = 0;
+#pragma unroll
+        for (int k = 0; k < kMfmaWM; ++k) list |= lists[k * kMfmaWP + run];
+        const int count = __popcll(list);
+        if (count == 0) continue;
+        const int shift = count > 1 ? __clz(count - 1) - 26 : 6;  // 64 >> shift is at least count
+        const int mine = lane >> shift, step = 1 << shift, part = lane & (step - 1);
+        const bool active = mine < count;  // the other lanes go along with the first position
+        uint64_t rest = list;
+        for (int k = 0; active && k < mine; ++k) rest &= rest - 1;
+        const int u = t0 + run * 64 + __ffsll((unsigned long long)rest) - 1;
         const int n = u / a.plane, rem = u - n * a.plane, h = rem / a.pitch, x = rem % a.pitch;
-        float v = 0.0f;
-        for (int j = a.rowptr[m]; j < a.rowptr[m + 1]; ++j) {
-            const MfmaNz z = a.nz[j];
-            const int y = h + z.r - a.pad, xx = x + z.s - a.pad;
-            if ((unsigned)y < (unsigned)a.H && (unsigned)xx < (unsigned)a.W)
-                v = fmaf(z.val, a.in[((size_t)n * a.C + z.c) * HW + y * a.W + xx], v);
+        const Place at = {(const uint32_t*)(a.in + (size_t)n * a.C * HW), h - a.pad, x - a.pad, (h - a.pad) * a.W + x - a.pad, a.H, a.W};
+        for (int k = wave; k < kTM; k += kMfmaWM * kMfmaWP) {
+            const int m = mg * kTM + k;
+            if (m >= a.M) break;
+            const int begin = __builtin_amdgcn_readfirstlane(a.rowptr[m]), end = __builtin_amdgcn_readfirstlane(a.rowptr[m + 1]);
+            float v = step == 1 ? walk((const __attribute__((address_space(4))) uint32_t*)a.nz, begin, end, 1, at)
+                                : walk((const uint32_t*)a.nz, begin + part, end, step, at);
+            for (int s = 1; s < step; s <<= 1) v += __shfl_xor(v, s);
+            if (!active || part != 0) continue;
+            v += has_bias ? a.bias[m] : 0.0f;
+            if (relu) v = v > 0.0f ? v : 0.0f;
+            a.out[((size_t)n * a.M + m) * EF + h * a.F + x] = v;
         }
-        v += has_bias ? a.bias[m] : 0.0f;
-        if (relu) v = v > 0.0f ? v : 0.0f;
-        a.out[((size_t)n * a.M + m) * EF + h * a.F + x] = v;
     }
 }
 

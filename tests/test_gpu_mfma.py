@@ -170,6 +170,28 @@ def test_small_inputs(oracle, power, everywhere):
     assert (np.abs(got - ref) <= 2.0 ** -24 * 4 * np.sqrt(n) * bound + n * 2.0 ** -150).all()
 
 
+@gpu
+@pytest.mark.parametrize("where", ["a row", "a column", "an image", "every image"])
+def test_many_non_finite_inputs(oracle, where):
+    """From a few positions of a workgroup to all of them are computed from the nonzeros: several lanes to an output,
+    one, full and part-filled runs of positions, a ragged last group of channels."""
+    print("mfma many non-finite", where, flush=True)
+    L = wl.custom_layer(105, 49, 15, 17, 65, 3, 3, 1, 1, 0.2, seed=78, dist="normal")
+    place = {"a row": np.s_[3, 7, 4], "a column": np.s_[104, 7, :, 16], "an image": np.s_[50, 11], "every image": np.s_[:, 48]}
+    L.input[place[where]] = np.inf
+    L.input[1, 0, 0, 0] = np.nan
+    assert chosen(L)
+    dl = DeviceLayer(esc, L)
+    for flags in (0, esc.F_BIAS | esc.F_RELU):
+        got = dl.forward_tiled(flags)
+        assert esc.plan_header(dl.plan)["mfma"] == 1
+        with np.errstate(invalid="ignore"):
+            ref, bound = oracle_full(oracle, L, flags)
+        bad = ~np.isfinite(bound)            # an output that met one; ReLU may have made it finite
+        assert bad.any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
+        assert (np.abs(got[~bad] - ref[~bad]) <= 1e-4 * bound[~bad]).all()
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_split_weights_add_up_to_the_csr(shape):
     N, C, H, W, M, R, S, pad, sparsity = shape
