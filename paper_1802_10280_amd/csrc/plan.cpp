@@ -777,7 +777,9 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
                     ds.chan = (int32_t)(q.key >> kKeyOffsetBits);
                 }
     }
-    h.mfma = with_mfma && mfma_write(d, rowptr, stretched, value, base + h.off_mfma) ? 1 : 0;
+    // room is made by the stored entries (the size query has no values); explicit zeros cost the tiled
+    // kernel nothing, so whether the section is worth having is asked again without them
+    h.mfma = with_mfma && mfma_planned(d, nnz_total) && mfma_write(d, rowptr, stretched, value, base + h.off_mfma) ? 1 : 0;
     if (h.mfma) h.mfma_nnz = (int32_t)nnz_total;
     std::memcpy(base, &h, sizeof(h));  // the header once more, now with WW, n_dma and mfma
     std::memcpy(base + h.off_lanes, lanes.data(), lanes.size() * sizeof(LaneSlot));

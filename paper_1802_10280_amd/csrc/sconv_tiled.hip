@@ -669,7 +669,7 @@ extern "C" int escoin_sconv_forward_tiled(const escoin_conv_desc* desc, const vo
         h.lds_bytes > 160 * 1024)
         return ESCOIN_EINVAL;
 
-    if (h.mfma == 1 && h.mfma_nnz > 0 && ((uintptr_t)d_plan & 15) == 0 && mfma_planned(d, h.nnz) && mfma_chosen(d, h.nnz))
+    if (h.mfma == 1 && h.mfma_nnz > 0 && ((uintptr_t)d_plan & 15) == 0 && mfma_planned(d, h.mfma_nnz) && mfma_chosen(d, h.mfma_nnz))
         return launch_sconv_mfma(d, h, (const char*)d_plan, d_in, d_out, d_bias, flags, (hipStream_t)hip_stream);
 
     const char* base = (const char*)d_plan;

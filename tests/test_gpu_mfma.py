@@ -117,6 +117,18 @@ def test_what_the_form_cannot_hold_stays_with_the_tiled_kernel():
         assert esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, st, value))["mfma"] == 0
 
 
+def test_explicit_zeros_do_not_count_as_nonzeros():
+    """A layer that keeps a full pattern with most values zero is a heavily pruned one."""
+    L = wl.custom_layer(40, 64, 12, 12, 64, 3, 3, 1, 1, 0.0, seed=79, dist="normal")
+    d = esc.desc_of(L.spec)
+    st = esc.escoin_sconv_pack(d, L.rowptr, L.colidx)
+    kept = np.random.default_rng(79).random(L.nnz)
+    for share, held in ((1.0, 1), (0.6, 1), (0.1, 0)):
+        value = np.where(kept < share, L.value, np.float32(0))
+        h = esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, st, value))
+        assert h["mfma"] == held and h["mfma_nnz"] == held * np.count_nonzero(value), share
+
+
 def test_weights_out_of_the_range_that_splits_exactly_stay_with_the_tiled_kernel():
     L = wl.custom_layer(40, 64, 12, 12, 64, 3, 3, 1, 1, 0.0, seed=73, dist="normal")
     d = esc.desc_of(L.spec)
