@@ -173,12 +173,16 @@ int escoin_sconv_plan_build(const escoin_conv_desc *desc, const int32_t *rowptr,
  * its weights for the matrix cores, split so that fp32 is kept; a call on a batch large enough to be
  * faster there takes them.  Same results within fp32 rounding, Inf and NaN included.
  *
+ * escoin_sconv_tiled_on_matrix_cores (host) tells which kernel a call with this descriptor and a 16-byte
+ * aligned d_plan takes: 1, 0 for the tiled kernel, or an error code as the call itself would return.
+ *
  * d_in and d_plan that are 16-byte aligned let the kernel stage with 16-byte loads (or with
  * global -> LDS copies); any 4-byte aligned pointer is accepted.
  */
 int escoin_sconv_forward_tiled(const escoin_conv_desc *desc, const void *plan_host,
                                const void *d_plan, const float *d_in, float *d_out,
                                const float *d_bias, uint32_t flags, void *hip_stream);
+int escoin_sconv_tiled_on_matrix_cores(const escoin_conv_desc *desc, const void *plan_host);
 
 #ifdef __cplusplus
 }

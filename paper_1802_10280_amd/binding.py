@@ -61,6 +61,7 @@ def lib() -> ctypes.CDLL:
         L.escoin_sconv_plan_size.argtypes = [D, vp, vp, T, ctypes.POINTER(ctypes.c_size_t)]
         L.escoin_sconv_plan_build.argtypes = [D, vp, vp, vp, T, vp, ctypes.c_size_t]
         L.escoin_sconv_forward_tiled.argtypes = [D, vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
+        L.escoin_sconv_tiled_on_matrix_cores.argtypes = [D, vp]
         _lib = L
     return _lib
 
@@ -197,6 +198,13 @@ def escoin_sconv_forward_tiled(desc, plan_host: np.ndarray, d_plan, d_in, d_out,
                                             _dptr(d_plan, torch.uint8), _dptr(d_in, torch.float32),
                                             _dptr(d_out, torch.float32), _dptr(d_bias, torch.float32),
                                             flags, _stream(stream)), "escoin_sconv_forward_tiled")
+
+
+def escoin_sconv_tiled_on_matrix_cores(desc, plan_host: np.ndarray) -> bool:
+    rc = lib().escoin_sconv_tiled_on_matrix_cores(ctypes.byref(desc), _hptr(plan_host, np.uint8))
+    if rc < 0:
+        _check(rc, "escoin_sconv_tiled_on_matrix_cores")
+    return rc == 1
 
 
 class _PlanHeader(ctypes.Structure):

@@ -37,7 +37,7 @@ inline uint64_t mfma_bytes(const Dims& d, int nnz) {
 }
 
 bool mfma_planned(const Dims& d, long long nnz);
-bool mfma_chosen(const Dims& d, long long nnz);
+bool mfma_taken(const Dims& d, const PlanHeader& h);
 bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value, char* out);
 int launch_sconv_mfma(const Dims& d, const PlanHeader& h, const char* d_plan, const float* d_in, float* d_out,
                       const float* d_bias, uint32_t flags, hipStream_t stream);

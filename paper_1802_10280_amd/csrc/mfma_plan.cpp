@@ -30,13 +30,14 @@ bool mfma_planned(const Dims& d, long long nnz) {
     return mfma_us(d, many) < 0.9 * tiled_us(d, many, nnz);
 }
 
-// Whether a forward call on this batch takes it: offsets inside the kernel are 32 bits, and the batch
-// has to fill the compute units.
-bool mfma_chosen(const Dims& d, long long nnz) {
+// Whether a forward call on this batch takes the section of a plan made for this layer: offsets inside the
+// kernel are 32 bits, and the batch has to fill the compute units.
+bool mfma_taken(const Dims& d, const PlanHeader& h) {
+    if (h.mfma != 1 || h.mfma_nnz <= 0 || !mfma_planned(d, h.mfma_nnz)) return false;
     const long long total = (long long)d.N * (d.H + d.pad) * (d.W + d.pad);
     const long long groups = (long long)mfma_row_blocks(d) / kMfmaWM;
     if (total > (1ll << 30) || (long long)d.N * d.C * d.H * d.W > (1ll << 30) || total / kMfmaTP * groups > (1ll << 30)) return false;
-    return mfma_us(d, d.N) < 0.9 * tiled_us(d, d.N, nnz);
+    return mfma_us(d, d.N) < 0.9 * tiled_us(d, d.N, h.mfma_nnz);
 }
 
 static float to_bf16(float x, uint16_t* bits) {  // rounds to nearest even; x is finite

@@ -628,7 +628,27 @@ bool tiled_variant_exists(int K, int Q, int B) {
     return false;
 }
 
+// The plan's header, if it was made for this layer.
+static int read_header(const Dims& d, const void* plan_host, PlanHeader* h) {
+    if (!plan_host) return ESCOIN_EINVAL;
+    *h = *(const PlanHeader*)plan_host;
+    if (h->magic != kPlanMagic || h->version != kPlanVersion) return ESCOIN_EINVAL;
+    if (h->C != d.C || h->H != d.H || h->W != d.W || h->M != d.M || h->R != d.R || h->S != d.S ||
+        h->stride != d.stride || h->pad != d.pad || h->E != d.E || h->F != d.F)
+        return ESCOIN_EINVAL;
+    return ESCOIN_OK;
+}
+
 }  // namespace escoin
+
+extern "C" int escoin_sconv_tiled_on_matrix_cores(const escoin_conv_desc* desc, const void* plan_host) {
+    using namespace escoin;
+    Dims d;
+    PlanHeader h;
+    int rc = make_dims(desc, &d);
+    if (rc == ESCOIN_OK) rc = read_header(d, plan_host, &h);
+    return rc != ESCOIN_OK ? rc : mfma_taken(d, h) ? 1 : 0;
+}
 
 extern "C" int escoin_sconv_forward_tiled(const escoin_conv_desc* desc, const void* plan_host,
                                           const void* d_plan, const float* d_in, float* d_out,
@@ -641,11 +661,8 @@ extern "C" int escoin_sconv_forward_tiled(const escoin_conv_desc* desc, const vo
     if (flags & ~(uint32_t)(ESCOIN_F_BIAS | ESCOIN_F_RELU)) return ESCOIN_EINVAL;
     if ((flags & ESCOIN_F_BIAS) && !d_bias) return ESCOIN_EINVAL;
     PlanHeader h;
-    h = *(const PlanHeader*)plan_host;
-    if (h.magic != kPlanMagic || h.version != kPlanVersion) return ESCOIN_EINVAL;
-    if (h.C != d.C || h.H != d.H || h.W != d.W || h.M != d.M || h.R != d.R || h.S != d.S ||
-        h.stride != d.stride || h.pad != d.pad || h.E != d.E || h.F != d.F)
-        return ESCOIN_EINVAL;
+    rc = read_header(d, plan_host, &h);
+    if (rc != ESCOIN_OK) return rc;
     // 16-byte staging loads need the plan's runs of four words and a 16-byte aligned input
     const bool aligned_in = ((uintptr_t)d_in & 15) == 0 && ((uintptr_t)d_plan & 15) == 0;
     TiledKernel kern = pick(h.K, h.Q, h.B, h.VW == 4 && aligned_in, h.n_dma > 0 && h.VW == 4 && h.WW == 4 && aligned_in);
@@ -669,7 +686,7 @@ extern "C" int escoin_sconv_forward_tiled(const escoin_conv_desc* desc, const vo
         h.lds_bytes > 160 * 1024)
         return ESCOIN_EINVAL;
 
-    if (h.mfma == 1 && h.mfma_nnz > 0 && ((uintptr_t)d_plan & 15) == 0 && mfma_planned(d, h.mfma_nnz) && mfma_chosen(d, h.mfma_nnz))
+    if (((uintptr_t)d_plan & 15) == 0 && mfma_taken(d, h))
         return launch_sconv_mfma(d, h, (const char*)d_plan, d_in, d_out, d_bias, flags, (hipStream_t)hip_stream);
 
     const char* base = (const char*)d_plan;

@@ -68,13 +68,13 @@ class LayerRunner:
 
     def sconv_kernel_name(self):
         if self.path == "tiled":
+            if B.escoin_sconv_tiled_on_matrix_cores(self.desc, self.plan) and self.d_plan.data_ptr() % 16 == 0:
+                return "sconv_mfma_kernel"
             h = self.plan_info
             vw = h["VW"] if self.d_in.data_ptr() % 16 == 0 else 1
             if vw == 4 and h["n_dma"] > 0 and h["WW"] == 4:
                 vw = 16       # staged by global -> LDS copies
-            name = f"sconv_tiled_kernel<{h['K']}, {h['Q']}, {h['B']}, {vw}>"
-            # a plan for both kernels: the call decides by the batch
-            return f"sconv_mfma_kernel or {name}" if h["mfma"] else name
+            return f"sconv_tiled_kernel<{h['K']}, {h['Q']}, {h['B']}, {vw}>"
         return "sconv_direct_kernel"
 
     def run(self):

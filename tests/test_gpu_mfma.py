@@ -17,18 +17,33 @@ SHAPES = [
     (80, 17, 33, 20, 60, 5, 5, 2, 0.2),
     (120, 33, 18, 13, 112, 3, 4, 0, 0.0),    # no padding: taps reach the end of a row, not past it
     (90, 24, 13, 18, 120, 5, 3, 1, 0.0),     # padding smaller than the reach
-    (23, 48, 60, 61, 64, 3, 3, 1, 0.3),      # the widest rows
+    (23, 48, 60, 61, 64, 3, 3, 1, 0.3),      # windows of 382 positions,
+    (24, 33, 40, 63, 96, 3, 3, 1, 0.0),      # of 386: one workgroup to a compute unit from here on,
+    (29, 40, 31, 30, 72, 5, 5, 2, 0.3),      # of 388,
+    (13, 65, 20, 126, 64, 3, 3, 1, 0.0),     # of 512, the most there is
+    (150, 250, 14, 14, 120, 1, 1, 0, 0.0),   # one tap
 ]
 
 
-def chosen(L):
-    """The rule that sends a call to the matrix cores, written out once more."""
-    s = L.spec
-    groups, chunks = -(-s.M // 64), -(-s.C // 16)
-    jobs = -(-s.N * (s.H + s.pad) * (s.W + s.pad) // 256) * groups
-    job = 6.0 + chunks * (1.6 + 0.46 * s.R * s.S)
-    us = job if jobs <= 256 else -(-jobs // 512) * 1.72 * job
-    return us < 0.9 * 2e-6 * L.nnz * s.N * s.E * s.F / 36.0
+def mfma_layer(L):
+    """The layer on the device with its default plan; a forward_tiled on it takes the matrix-core kernel."""
+    dl = DeviceLayer(esc, L)
+    dl.forward_tiled()
+    assert esc.escoin_sconv_tiled_on_matrix_cores(dl.desc, dl.plan) and dl.d_plan.data_ptr() % 16 == 0
+    return dl
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_shapes_take_the_matrix_cores(shape):
+    N, C, H, W, M, R, S, pad, sparsity = shape
+    L = wl.custom_layer(N, C, H, W, M, R, S, 1, pad, sparsity, seed=71, dist="normal")
+    d = esc.desc_of(L.spec)
+    plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+    assert esc.escoin_sconv_tiled_on_matrix_cores(d, plan)
+    one = esc.make_desc(1, C, H, W, M, R, S, 1, pad)
+    assert not esc.escoin_sconv_tiled_on_matrix_cores(one, plan)
+    with pytest.raises(esc.EscoinError):
+        esc.escoin_sconv_tiled_on_matrix_cores(esc.make_desc(N, C, H, W, M + 1, R, S, 1, pad), plan)
 
 
 @gpu
@@ -37,17 +52,42 @@ def test_against_the_oracle(oracle, shape):
     print("mfma", shape, flush=True)
     N, C, H, W, M, R, S, pad, sparsity = shape
     L = wl.custom_layer(N, C, H, W, M, R, S, 1, pad, sparsity, seed=71, dist="normal")
-    assert chosen(L)
-    dl = DeviceLayer(esc, L)
+    dl = mfma_layer(L)
     for flags in (0, esc.F_BIAS | esc.F_RELU):
         got = dl.forward_tiled(flags)
-        assert esc.plan_header(dl.plan)["mfma"] == 1
         ref, bound = oracle_full(oracle, L, flags)
         assert np.isfinite(got).all()
         worst = assert_within_bound(got, ref, bound, (shape, flags))
         # the split is exact and the products left out are below 2^-24 of |x*w|: a sum of at most C*R*S fp32
         # roundings, of which a random walk's share shows
         assert worst <= 2.0 ** -24 * 4 * np.sqrt(C * R * S), worst
+
+
+@gpu
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[9]], ids=str)
+def test_unaligned_buffers_guards_and_one_plan_for_two_batches(oracle, shape):
+    """Input and output one word off alignment, NaN around the output; then the same plan at batch 1 (tiled kernel)."""
+    import torch
+    print("mfma unaligned", shape, flush=True)
+    N, C, H, W, M, R, S, pad, sparsity = shape
+    L = wl.custom_layer(N, C, H, W, M, R, S, 1, pad, sparsity, seed=80, dist="normal")
+    dl = mfma_layer(L)
+    ref, bound = oracle_full(oracle, L)
+    n_in, n_out, guard = L.input.size, ref.size, 1 << 16
+    room = torch.full((n_in + 4,), float("nan"), device="cuda")
+    d_in = room[1:1 + n_in].copy_(dl.d_in.flatten())
+    out = torch.full((guard + 1 + n_out + guard,), float("nan"), device="cuda")
+    d_out = out[guard + 1:guard + 1 + n_out]
+    assert d_in.data_ptr() % 16 == 4 and d_out.data_ptr() % 16 == 4
+    esc.escoin_sconv_forward_tiled(dl.desc, dl.plan, dl.d_plan, d_in, d_out)
+    assert_within_bound(d_out.cpu().numpy().reshape(ref.shape), ref, bound, shape)
+    assert bool(out[:guard + 1].isnan().all()) and bool(out[guard + 1 + n_out:].isnan().all())
+    one = esc.make_desc(1, C, H, W, M, R, S, 1, pad)
+    assert not esc.escoin_sconv_tiled_on_matrix_cores(one, dl.plan)
+    dl.d_out.fill_(float("nan"))
+    esc.escoin_sconv_forward_tiled(one, dl.plan, dl.d_plan, dl.d_in[:1], dl.d_out[:1])
+    assert_within_bound(dl.d_out[:1].cpu().numpy(), ref[:1], bound[:1], shape)
+    assert bool(dl.d_out[1:].isnan().all())
 
 
 def set_weight(L, m, c, tap, value):
@@ -71,12 +111,10 @@ def test_products_around_the_largest_float(oracle):
                               (104, 48, 0, 1e38, 2057.0), (50, 30, 40, 3.4028e38 / float(near), near)):
         L.input[image, c, 5, 6] = x
         set_weight(L, m, c, 4, w)
-    assert chosen(L)
     with np.errstate(over="ignore"):
         ref, bound = oracle_full(oracle, L)
-    dl = DeviceLayer(esc, L)
+    dl = mfma_layer(L)
     got = dl.forward_tiled()
-    assert esc.plan_header(dl.plan)["mfma"] == 1
     over = np.isinf(ref)
     assert over.sum() == 4 and (got[over] == ref[over]).all()
     assert_within_bound(got[~over], ref[~over], bound[~over])
@@ -90,11 +128,9 @@ def test_non_finite_inputs_reach_only_nonzero_weights(oracle):
     L.input[2, 0, 0, 0] = np.nan
     L.input[199, 49, 11, 12] = -np.inf
     L.input[20, 3, 4, 4] = 3.4e38            # finite, but not in bf16
-    assert chosen(L)
     for flags in (0, esc.F_BIAS):
-        dl = DeviceLayer(esc, L)
+        dl = mfma_layer(L)
         got = dl.forward_tiled(flags)
-        assert esc.plan_header(dl.plan)["mfma"] == 1
         with np.errstate(invalid="ignore", over="ignore"):
             ref, bound = oracle_full(oracle, L, flags)
         bad = ~np.isfinite(ref)
@@ -150,7 +186,7 @@ def test_small_weights(oracle, power):
     L = wl.custom_layer(105, 49, 15, 17, 65, 3, 3, 1, 1, 0.0, seed=76, dist="normal")
     L.value *= np.float32(2.0 ** power)
     L.input *= np.float32(1024)
-    dl = DeviceLayer(esc, L)
+    dl = DeviceLayer(esc, L)  # the tiled kernel, down to 2^-50
     got = dl.forward_tiled()
     ref, bound = oracle_full(oracle, L)
     # fp32: every one of the C*R*S products and sums rounds by 2^-24 of sum|w*x|, or by half a subnormal's 2^-149
@@ -172,10 +208,8 @@ def test_small_inputs(oracle, power, everywhere):
         L.input[::5] = 0
         L.input[::5, 7] = small[::5, 7]
     L.value *= np.float32(16)
-    assert chosen(L)
-    dl = DeviceLayer(esc, L)
+    dl = mfma_layer(L)
     got = dl.forward_tiled()
-    assert esc.plan_header(dl.plan)["mfma"] == 1
     ref, bound = oracle_full(oracle, L)
     # as above: fp32 rounding of C*R*S products and sums, or half a subnormal's step each
     n = L.spec.C * L.spec.R * L.spec.S
@@ -192,11 +226,9 @@ def test_many_non_finite_inputs(oracle, where):
     place = {"a row": np.s_[3, 7, 4], "a column": np.s_[104, 7, :, 16], "an image": np.s_[50, 11], "every image": np.s_[:, 48]}
     L.input[place[where]] = np.inf
     L.input[1, 0, 0, 0] = np.nan
-    assert chosen(L)
-    dl = DeviceLayer(esc, L)
+    dl = mfma_layer(L)
     for flags in (0, esc.F_BIAS | esc.F_RELU):
         got = dl.forward_tiled(flags)
-        assert esc.plan_header(dl.plan)["mfma"] == 1
         with np.errstate(invalid="ignore"):
             ref, bound = oracle_full(oracle, L, flags)
         bad = ~np.isfinite(bound)            # an output that met one; ReLU may have made it finite
