@@ -8,6 +8,7 @@ namespace escoin {
 constexpr int kMfmaWM = 2, kMfmaWP = 4;      // waves of a workgroup over channels (32 each) and positions (64 each)
 constexpr int kMfmaTP = 64 * kMfmaWP;        // output positions of a workgroup
 constexpr int kMfmaMaxWindow = 512;          // window positions it can stage (two tasks a thread)
+constexpr int kMfmaPairWindow = 384;         // up to here two workgroups fit the LDS of a compute unit
 
 // The weights the section can hold.  Below 2^-110 the three bf16 parts are no longer exact (bf16 ends at
 // 2^-133, fp32 at 2^-149).  The limits lie well inside that, so that the products keep their bits with

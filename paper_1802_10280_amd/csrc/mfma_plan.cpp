@@ -8,26 +8,32 @@
 
 namespace escoin {
 
-// Microseconds the matrix-core kernel takes for a batch of N images: a workgroup alone on its compute
-// unit spends 1.6 us on a chunk (staging, barrier, the first wait) and 0.46 us on each of its taps; two
-// that share one take 1.72 times as long for both.
-static double mfma_us(const Dims& d, double N) {
+// Whether the matrix-core kernel is faster on a batch of N images, by estimates of both kernels in
+// microseconds.  A workgroup alone on its compute unit spends 1.6 us on a chunk (staging, barrier, the first
+// wait) and 0.46 us on each of its taps; two that share one take 1.72 times as long for both.  The tiled
+// kernel is taken at its better: 36 TFLOP/s on the nonzeros (41 measured on a large layer at 50 % sparsity, 32
+// on 13x13 maps at 65 %, less the fewer nonzeros or positions there are).
+// Windows above kMfmaPairWindow leave no LDS for a second workgroup: rounds are of 256, each as long as one.
+// That is 57.9, 86.9, 115.8 and 332 us where 56-58, 85, 115 and 341 were measured (64 channels, 25, 35 and 62
+// images of 63x63; 128 channels, 5x5, 64 of 32x32), so the margin can go; on such layers the tiled kernel was
+// 4-25 % slower than its estimate (67, 118, 158, 393 us at 71-75 and 65 % sparsity).
+static bool mfma_faster(const Dims& d, double N, long long nnz) {
     const double jobs = ceil(N * (d.H + d.pad) * (d.W + d.pad) / kMfmaTP) * (double)(mfma_row_blocks(d) / kMfmaWM);
     const double job = 6.0 + (double)mfma_chunks(d) * (1.6 + 0.46 * d.R * d.S);
-    return jobs <= 256 ? job : ceil(jobs / 512) * 1.72 * job;
+    const double tiled = 2e-6 * (double)nnz * N * d.E * d.F / 36.0;
+    if (jobs <= 256) return job < 0.9 * tiled;
+    if (mfma_window(d) <= kMfmaPairWindow) return ceil(jobs / 512) * 1.72 * job < 0.9 * tiled;
+    return ceil(jobs / 256) * job < 1.04 * tiled;
 }
 
-// The tiled kernel at its better: 36 TFLOP/s on the nonzeros (41 measured on a large layer at 50 %
-// sparsity, 32 on 13x13 maps at 65 %, less the fewer nonzeros or positions there are).
-static double tiled_us(const Dims& d, double N, long long nnz) { return 2e-6 * (double)nnz * N * d.E * d.F / 36.0; }
-
-// Whether a plan carries the section: shapes the kernel takes, and pruned so little that a large batch
-// is faster on the matrix cores.
+// Whether a plan carries the section: shapes the kernel takes, and pruned so little that a batch that
+// suits it is faster on the matrix cores: one of many workgroups, or of two full rounds where they do not pair.
 bool mfma_planned(const Dims& d, long long nnz) {
     if (d.stride != 1 || d.R <= d.pad || d.S <= d.pad || mfma_window(d) > kMfmaMaxWindow) return false;
     if (d.C < 16 || d.M < 32 || mfma_weight_bytes(d) > (64ull << 20)) return false;
-    const double many = 512.0 * 64 * kMfmaTP / ((double)(d.H + d.pad) * (d.W + d.pad));
-    return mfma_us(d, many) < 0.9 * tiled_us(d, many, nnz);
+    const double groups = (double)(mfma_row_blocks(d) / kMfmaWM);
+    const double tiles = mfma_window(d) <= kMfmaPairWindow ? 512.0 * 64 : floor(512.0 / groups);
+    return mfma_faster(d, tiles * kMfmaTP / ((double)(d.H + d.pad) * (d.W + d.pad)), nnz);
 }
 
 // Whether a forward call on this batch takes the section of a plan made for this layer: offsets inside the
@@ -37,7 +43,7 @@ bool mfma_taken(const Dims& d, const PlanHeader& h) {
     const long long total = (long long)d.N * (d.H + d.pad) * (d.W + d.pad);
     const long long groups = (long long)mfma_row_blocks(d) / kMfmaWM;
     if (total > (1ll << 30) || (long long)d.N * d.C * d.H * d.W > (1ll << 30) || total / kMfmaTP * groups > (1ll << 30)) return false;
-    return mfma_us(d, d.N) < 0.9 * tiled_us(d, d.N, h.mfma_nnz);
+    return mfma_faster(d, d.N, h.mfma_nnz);
 }
 
 static float to_bf16(float x, uint16_t* bits) {  // rounds to nearest even; x is finite

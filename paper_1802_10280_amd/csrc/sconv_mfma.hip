@@ -25,7 +25,8 @@
 // Bound by the matrix cores: per wave and (tap, 16 channels) 12 MFMAs of 32 clk against 6 LDS reads
 // and 3 KB of weights from L1/L2, which all the position waves of a workgroup share.  The weights
 // lie in the plan in the order the lanes read them.  Eight waves at 128 registers let two workgroups
-// share a compute unit and hide each other's staging.  64x256x28x28, 256 3x3 filters at 50 %: 317 us
+// share a compute unit and hide each other's staging, up to windows of 384 positions (the 96 KB of LDS a
+// longer one takes fit once).  64x256x28x28, 256 3x3 filters at 50 %: 317 us
 // (the MFMAs alone 152 us at 2.4 GHz, and the 844 workgroups fill 1.65 rounds of 512) against 720 us
 // in the tiled kernel; 64x384x13x13, 384 filters at 65 %: 234 against 313 us.  Asking for a step's
 // weights a whole step ahead and staging through buffer loads changed neither (318, 233 us).
@@ -280,12 +281,16 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
 
 template <int WR>
 int start(const MfmaArgs& a, unsigned blocks, hipStream_t stream) {
-    // Two workgroups fit a compute unit and share its matrix cores.  A launch that has no more than one
-    // for each compute unit asks for so much LDS that they do not double up beside idle ones.
+    // Two workgroups fit a compute unit (one, with the longest windows) and share its matrix cores.  A launch
+    // that has no more than one for each compute unit asks for so much LDS that they do not double up
+    // beside idle ones.
     constexpr int two = 2 * 6 * WR * 16;
+    static_assert((2 * two <= 160 * 1024) == (WR <= kMfmaPairWindow), "the rule counts on this");
     const int lds = blocks <= 256 ? std::max(two, 84 * 1024) : two;
-    int rc = allow_dynamic_lds((const void*)sconv_mfma_kernel<WR>, lds);
-    if (rc != ESCOIN_OK) return rc;
+    if (lds > 64 * 1024) {
+        const int rc = allow_dynamic_lds((const void*)sconv_mfma_kernel<WR>, lds);
+        if (rc != ESCOIN_OK) return rc;
+    }
     return launch(sconv_mfma_kernel<WR>, dim3(blocks), dim3(kThreads), (size_t)lds, stream, a);
 }
 
@@ -308,7 +313,7 @@ int launch_sconv_mfma(const Dims& d, const PlanHeader& h, const char* d_plan, co
     const unsigned blocks = (unsigned)((long long)a.n_tiles * a.n_mgroups + 7) / 8 * 8;
     const int window = mfma_window(d);
     if (window <= 320) return start<320>(a, blocks, stream);
-    if (window <= 384) return start<384>(a, blocks, stream);
+    if (window <= kMfmaPairWindow) return start<kMfmaPairWindow>(a, blocks, stream);
     return start<512>(a, blocks, stream);
 }
 

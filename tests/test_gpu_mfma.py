@@ -90,6 +90,26 @@ def test_unaligned_buffers_guards_and_one_plan_for_two_batches(oracle, shape):
     assert bool(dl.d_out[1:].isnan().all())
 
 
+@pytest.mark.parametrize("W, N, tiled_us, taken", [
+    (62, 35, 95.0, False),     # windows of 384: two workgroups share a compute unit, 552 take two rounds of 49.8 us
+    (63, 35, 95.0, True),      # 386: they cannot, and 560 take three of 29.0
+    (63, 35, 80.0, False),
+    (63, 62, 108.0, False),    # 992 take four
+    (63, 62, 115.0, True),
+    (63, 64, 115.0, True),     # 1024
+    (63, 65, 120.0, False),    # 1040: five
+])
+def test_wide_windows_count_as_one_workgroup_to_a_compute_unit(W, N, tiled_us, taken):
+    """64 channels, 3x3, as many nonzeros as the tiled kernel is put at that time for."""
+    L = wl.custom_layer(1, 64, 63, W, 64, 3, 3, 1, 1, 0.0, seed=81, dist="normal")
+    per_row = int(tiled_us * 36e6 / (2 * N * 63 * W) / 64)
+    rowptr = np.arange(65, dtype=np.int32) * np.int32(per_row)
+    colidx = np.concatenate([L.colidx[L.rowptr[m]:L.rowptr[m] + per_row] for m in range(64)])
+    d = esc.make_desc(N, 64, 63, W, 64, 3, 3, 1, 1)
+    plan = esc.escoin_sconv_plan_build(d, rowptr, esc.escoin_sconv_pack(d, rowptr, colidx), np.ones(64 * per_row, dtype=np.float32))
+    assert esc.escoin_sconv_tiled_on_matrix_cores(d, plan) == taken
+
+
 def set_weight(L, m, c, tap, value):
     """The weight of channel m at (input channel c, tap); the CSR has to hold it."""
     row = slice(L.rowptr[m], L.rowptr[m + 1])
