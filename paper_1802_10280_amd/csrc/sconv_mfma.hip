@@ -181,6 +181,9 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
     fetch(0);
     commit(0);
     __syncthreads();
+    // what the waves tell each other at the end, in the buffer the last chunk leaves free
+    struct Notes { uint32_t tiny[kMfmaWM * kMfmaWP]; uint64_t again[kMfmaWM * kMfmaWP]; };
+    Notes* const notes = (Notes*)(win + (a.n_chunks & 1) * kBuf);
     for (int kc = 0; kc < a.n_chunks; ++kc) {
         const bool more = kc + 1 < a.n_chunks;
         if (more) fetch(kc + 1);
@@ -207,11 +210,19 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
                 ESCOIN_MFMA(small, c0, 1)
 #undef ESCOIN_MFMA
             }
-        if (more) commit((kc + 1) & 1);  // that buffer was last read before the previous barrier
+        // the other buffer was last read before the previous barrier
+        if (more) {
+            commit((kc + 1) & 1);
+        } else {
+            const bool met = __any(least < 2u * __float_as_uint(kTinyInput) - 1u);
+            if (lane == 0) notes->tiny[wave] = met;
+        }
         __syncthreads();
     }
 
-    const bool tiny = __syncthreads_or(least < 2u * __float_as_uint(kTinyInput) - 1u);
+    uint32_t tiny = 0;
+#pragma unroll
+    for (int k = 0; k < kMfmaWM * kMfmaWP; ++k) tiny |= notes->tiny[k];
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
     const int EF = a.E * a.F;
     // A lane holds, per 32 positions, 16 output channels of one position: 8*(i/4) + 4*(lane/32) + i%4.
@@ -238,22 +249,24 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
         const uint64_t lanes = __ballot(bad);
         again |= ((lanes | lanes >> 32) & 0xffffffffu) << (32 * q);
     }
-    if (!__syncthreads_or(again != 0)) return;
+    if (lane == 0) notes->again[wave] = again;
+    __syncthreads();
+    uint64_t any = 0;
+#pragma unroll
+    for (int k = 0; k < kMfmaWM * kMfmaWP; ++k) any |= notes->again[k];
+    if (any == 0) return;
 
     // Those positions once more from the nonzeros, all channels of the workgroup: its waves share the
     // channels, and where a 64-position run has few such positions several lanes share an output's
     // nonzeros.  (A position of one wave belongs to the waves of the other channels as well, so the
-    // lists meet in LDS; the barriers also order these stores after the ones above.)
+    // lists meet in LDS; the barrier also orders these stores after the ones above.)
     // Bound by the gathers' latency where few workgroups come here and by their address arithmetic where all
     // do.  64x256x28x28 at 50 %, when each lane redid its own outputs -> now: one NaN in the batch 6.4 -> 0.5 ms,
     // one image of them 11.6 -> 4.3, nothing else 32 -> 12.5 (the tiled kernel takes 0.72 whatever the input).
-    uint64_t* const lists = (uint64_t*)win;  // every wave is past its last read of the windows
-    if (lane == 0) lists[wave] = again;
-    __syncthreads();
     for (int run = 0; run < kMfmaWP; ++run) {
         uint64_t list = 0;
 #pragma unroll
-        for (int k = 0; k < kMfmaWM; ++k) list |= lists[k * kMfmaWP + run];
+        for (int k = 0; k < kMfmaWM; ++k) list |= notes->again[k * kMfmaWP + run];
         const int count = __popcll(list);
         if (count == 0) continue;
         const int shift = count > 1 ? __clz(count - 1) - 26 : 6;  // 64 >> shift is at least count
