@@ -30,6 +30,7 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E
 FP32_VECTOR_PEAK_TFLOPS = 157.3  # 256 CU x 128 FMA/clk x 2.4 GHz x 2
+BF16_MATRIX_PEAK_TFLOPS = 2500.0  # dense; the matrix-core kernel makes six bf16 products of every fp32 one
 FLUSH_BYTES = 1 << 30            # written before every cold step: four times the Infinity Cache
 
 
@@ -71,7 +72,7 @@ def algorithmic_bytes(L, two_kernel: bool) -> int:
 def kernel_source_hash() -> str:
     """Identifies the code the recorded HBM counters were taken with."""
     h = hashlib.sha256()
-    for f in ("sconv_tiled.hip", "plan.cpp", "plan.h"):
+    for f in ("sconv_tiled.hip", "sconv_mfma.hip", "plan.cpp", "mfma_plan.cpp", "plan.h", "mfma.h"):
         h.update(open(os.path.join(ROOT, "paper_1802_10280_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -80,10 +81,10 @@ TRAFFIC_KEYS = ("K", "Q", "B", "WM", "WS", "CC", "CC0", "NB", "TH", "CS", "VW", 
 
 
 def measured_traffic(runner):
-    """HBM bytes one launch of this layer's tiled kernel moved, read plus written, as the
+    """HBM bytes one launch of this layer's kernel (tiled or matrix-core) moved, read plus written, as the
     rocprofv3 FETCH_SIZE / WRITE_SIZE counters recorded it (profiles/hbm_traffic.json, written
     from the counter runs summarised beside it).  None unless a record matches this layer,
-    batch size, every tiling knob and the kernel sources exactly."""
+    batch size, kernel, every tiling knob and the kernel sources exactly."""
     table = os.path.join(ROOT, "profiles", "hbm_traffic.json")
     if runner.path != "tiled" or not os.path.exists(table):
         return None
@@ -92,7 +93,7 @@ def measured_traffic(runner):
         return None
     h, s = runner.plan_info, runner.layer.spec
     for rec in doc["records"]:
-        if (rec["layer"] == s.name and rec["N"] == s.N and rec["nnz"] == runner.layer.nnz
+        if (rec["layer"] == s.name and rec["kernel"] == runner.sconv_kernel_name() and rec["N"] == s.N and rec["nnz"] == runner.layer.nnz
                 and all(rec["plan"].get(k) == h[k] for k in TRAFFIC_KEYS)):
             return rec["read_bytes"] + rec["written_bytes"]
     return None
@@ -249,6 +250,11 @@ def main():
             "binding": "alu" if t_alu >= t_hbm else "hbm",
             "binding_frac": round(max(t_alu, t_hbm) / t_all, 4),
         }
+        if row["kernel"] == "sconv_mfma_kernel":
+            # it multiplies the zeros too: alu_frac, on the nonzeros, is not its limit
+            s = L.spec
+            dense = 2.0 * s.N * s.M * s.C * s.R * s.S * s.E * s.F
+            row["matrix_frac"] = round(6 * dense / t_sconv / 1e9 / BF16_MATRIX_PEAK_TFLOPS, 4)
         if tc:
             row["hbm_frac_cold"] = round(comp / sum(tc.values()) / 1e6 / HBM_PEAK_GBPS, 4)
         if two is not None:
@@ -271,7 +277,10 @@ def main():
 
     dom = max(range(len(rows)), key=lambda k: rows[k]["us_sconv"])
     Ld, rd = layers[dom], rows[dom]
-    if rd["binding"] == "alu":
+    if "matrix_frac" in rd:
+        roofline = {"bound": "mfma", "achieved": round(rd["matrix_frac"] * BF16_MATRIX_PEAK_TFLOPS, 1),
+                    "peak": BF16_MATRIX_PEAK_TFLOPS, "unit": "TFLOP/s (bf16, zeros included)", "frac": rd["matrix_frac"]}
+    elif rd["binding"] == "alu":
         achieved = flops[dom] / (rd["us_sconv"] * 1e-6) / 1e12
         roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP32_VECTOR_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": round(achieved / FP32_VECTOR_PEAK_TFLOPS, 4)}

@@ -8,9 +8,11 @@
 //
 // fp32 is kept by splitting every operand into three bf16 parts, x = h + m + l, each the rounded rest
 // of the one before: 8 + 8 + 8 significant bits, so the split of an fp32 number is exact.  Six of
-// the nine partial products are formed (hh, hm, mh, mm, hl, lh); the three left out are below 2^-25
-// of |x*w|, less than the rounding of a single fp32 product.  hh has an accumulator of its own, so
-// that the running sum is rounded once per 16 channels, the five small ones share another.
+// the nine partial products are formed (hh, hm, mh, mm, hl, lh); the three left out are below 2^-24
+// of |x*w|, about the rounding of one fp32 product.  hh has an accumulator of its own, so that the
+// running sum is rounded once per 16 channels, the five small ones share another.  An output of a single
+// product is off by at most 9.7e-8 of it (fp32: 6.0e-8; root mean square 2.6e-8 and 2.5e-8), a sum of some
+// hundred by a third of what the tiled kernel's chain of roundings gives.
 //
 // A finite input whose h rounds to infinity, an Inf or a NaN would spread to outputs that only meet
 // it under a zero weight; and where a product passes the largest float, so may its parts, with both
@@ -22,12 +24,13 @@
 // sums below 2^-58 are computed again as well.  In the others, what such inputs lose (3 * 2^-134 * 2^30 a
 // product, fewer than 2^18 products) is below 2^-25 of the sum.
 //
-// Bound by the matrix cores: per wave and (tap, 16 channels) 12 MFMAs of 32 clk against 6 LDS reads
-// and 3 KB of weights from L1/L2, which all the position waves of a workgroup share.  The weights
-// lie in the plan in the order the lanes read them.  Eight waves at 128 registers let two workgroups
+// Per wave and (tap, 16 channels) 12 MFMAs of 32 clk stand against 6 LDS reads and 3 KB of weights from
+// L1/L2, which all the position waves of a workgroup share.  The MFMAs are about half of a full
+// round's time (two workgroups of 16 chunks and 9 taps: 92 of 168 us at 2.4 GHz); the rest goes to staging,
+// barriers and first waits, and to the last round, which is rarely full.  The weights lie in the plan in the order the lanes read them.  Eight waves at 128 registers let two workgroups
 // share a compute unit and hide each other's staging, up to windows of 384 positions (the 96 KB of LDS a
-// longer one takes fit once).  64x256x28x28, 256 3x3 filters at 50 %: 317 us
-// (the MFMAs alone 152 us at 2.4 GHz, and the 844 workgroups fill 1.65 rounds of 512) against 720 us
+// longer one takes fit once).  64x256x28x28, 256 3x3 filters at 50 %: 324 us
+// (the MFMAs alone 152 us at 2.4 GHz; the 844 workgroups fill 1.65 rounds of 512) against 720 us
 // in the tiled kernel; 64x384x13x13, 384 filters at 65 %: 234 against 313 us.  Asking for a step's
 // weights a whole step ahead and staging through buffer loads changed neither (318, 233 us).
 #include <float.h>
@@ -47,11 +50,10 @@ struct MfmaArgs {
     float* out;
     const float* bias;
     const b8* w;              // [32-row block][chunk of 16 channels][tap][split][lane]
-    const int32_t* rowptr;    // the nonzeros once more, for windows that hold Inf or NaN
+    const int32_t* rowptr;    // the nonzeros once more, for sums that cannot be used
     const MfmaNz* nz;
     int N, C, H, W, M, E, F, R, S, pad;
     int pitch, plane;         // of the flat padded array: columns per row, positions per image
-    int total;                // positions of the batch
     int n_chunks, n_mgroups, n_tiles;
     uint32_t flags;
 };
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(kThreads, 4) void sconv_mfma_kernel(const MfmaArgs 
                 l[j] = (__bf16)(r - (float)m[j]);
             }
             if (2 * WR % kThreads == 0 || task < 2 * WR) {
-                b8* const o = win + buf * kBuf + (task);
+                b8* const o = win + buf * kBuf + task;
                 o[0] = h;
                 o[2 * WR] = m;
                 o[4 * WR] = l;
@@ -319,10 +321,9 @@ int launch_sconv_mfma(const Dims& d, const PlanHeader& h, const char* d_plan, co
     a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad;
     a.pitch = d.W + d.pad;
     a.plane = (d.H + d.pad) * a.pitch;
-    a.total = d.N * a.plane;
     a.n_chunks = (d.C + 15) / 16;
     a.n_mgroups = (d.M + kTM - 1) / kTM;
-    a.n_tiles = (a.total + kMfmaTP - 1) / kMfmaTP;
+    a.n_tiles = (d.N * a.plane + kMfmaTP - 1) / kMfmaTP;
     const unsigned blocks = (unsigned)((long long)a.n_tiles * a.n_mgroups + 7) / 8 * 8;
     const int window = mfma_window(d);
     if (window <= 320) return start<320>(a, blocks, stream);
