@@ -72,7 +72,8 @@ def algorithmic_bytes(L, two_kernel: bool) -> int:
 def kernel_source_hash() -> str:
     """Identifies the code the recorded HBM counters were taken with."""
     h = hashlib.sha256()
-    for f in ("sconv_tiled.hip", "sconv_mfma.hip", "plan.cpp", "mfma_plan.cpp", "plan.h", "mfma.h"):
+    for f in ("sconv_tiled.hip", "sconv_mfma.hip", "sconv_pair.hip", "plan.cpp", "mfma_plan.cpp", "pair_plan.cpp", "plan.h", "mfma.h",
+              "mfma_device.h", "pair.h"):
         h.update(open(os.path.join(ROOT, "paper_1802_10280_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -250,11 +251,13 @@ def main():
             "binding": "alu" if t_alu >= t_hbm else "hbm",
             "binding_frac": round(max(t_alu, t_hbm) / t_all, 4),
         }
-        if row["kernel"] == "sconv_mfma_kernel":
+        # matrix products per multiply-add: three bf16 parts an operand, or two fp16 parts
+        products = 6 if row["kernel"].startswith("sconv_mfma") else 3 if row["kernel"].startswith("sconv_pair") else 0
+        if products:
             # it multiplies the zeros too: alu_frac, on the nonzeros, is not its limit
             s = L.spec
             dense = 2.0 * s.N * s.M * s.C * s.R * s.S * s.E * s.F
-            row["matrix_frac"] = round(6 * dense / t_sconv / 1e9 / BF16_MATRIX_PEAK_TFLOPS, 4)
+            row["matrix_frac"] = round(products * dense / t_sconv / 1e9 / BF16_MATRIX_PEAK_TFLOPS, 4)
         if tc:
             row["hbm_frac_cold"] = round(comp / sum(tc.values()) / 1e6 / HBM_PEAK_GBPS, 4)
         if two is not None:
@@ -279,7 +282,7 @@ def main():
     Ld, rd = layers[dom], rows[dom]
     if "matrix_frac" in rd:
         roofline = {"bound": "mfma", "achieved": round(rd["matrix_frac"] * BF16_MATRIX_PEAK_TFLOPS, 1),
-                    "peak": BF16_MATRIX_PEAK_TFLOPS, "unit": "TFLOP/s (bf16, zeros included)", "frac": rd["matrix_frac"]}
+                    "peak": BF16_MATRIX_PEAK_TFLOPS, "unit": "TFLOP/s (16-bit, zeros included)", "frac": rd["matrix_frac"]}
     elif rd["binding"] == "alu":
         achieved = flops[dom] / (rd["us_sconv"] * 1e-6) / 1e12
         roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP32_VECTOR_PEAK_TFLOPS,

@@ -169,17 +169,27 @@ int escoin_sconv_plan_build(const escoin_conv_desc *desc, const int32_t *rowptr,
  * additions, and with it the last bits of the result, may differ from run to run), and, with
  * ESCOIN_F_RELU, the clamp as a pass of its own.
  *
- * A plan made without tuning for a layer of stride 1 that is pruned little (roughly 50-70 %) also holds
- * its weights for the matrix cores, each as three bf16 parts; a call on a batch large enough to be
- * faster there multiplies all of them, zeros too.  Results stay within fp32 rounding of the sums over the
- * nonzeros, tiny inputs, Inf and NaN included (outputs that meet an Inf or a NaN, or inputs below 2^-70
- * alone, are computed from the nonzeros and slow such a call down).  Repeated columns or weights outside
- * 2^-50 .. 2^30 keep a layer on the other kernel.  The section adds 6 bytes per weight of the unpruned filter
- * bank (channels rounded up to 64 and 16) and 12 per nonzero to the plan, whatever batch it is for: 18 MB
- * instead of 4.5 for 384 3x3 filters on 384 channels at 65 %.
+ * A plan made without tuning for a layer of stride 1 may also hold its weights for the matrix cores, and a call on a
+ * batch large enough to be faster there multiplies all of them, zeros too.  Two forms:
+ *   - pairs of fp16 numbers, for layers of up to some 90 % sparsity whose rows have 32 nonzeros or more, 60 to some hundred on
+ *     the average, and whose filters reach at most 127 positions of the flat padded map (two rows of 62, four of 30).  Inputs are scaled by a
+ *     power of two, the same for a workgroup's window, weights by one a row.  A pair holds 22 to 23 bits: an output of n
+ *     products is off by up to 2^-21 of sum|w*x| and, in the mean, by less than a chain of fp32 sums would be from about
+ *     50 products on.  Weights of a row more than 2^27 apart keep a layer from it;
+ *   - three bf16 parts each, for layers pruned little (roughly 50-70 %) where the sums are too short for the pairs or the filters
+ *     reach further.  Results stay within fp32 rounding of the sums over the nonzeros.  Weights outside 2^-50 .. 2^30 keep a layer
+ *     from it.
+ * In both, tiny inputs, Inf and NaN behave as in the sums over the nonzeros: outputs that meet an Inf or a NaN, or whose
+ * inputs are all far smaller than others of their window (2^-70 in the second form), are computed from the nonzeros
+ * and slow such a call down.  Repeated columns keep a layer on the tiled kernel.  The sections add 4 and 6 bytes
+ * per weight of the unpruned filter bank (channels rounded up to 64 and 16) and 12 per nonzero to the plan, whatever
+ * batch it is for.
  *
  * escoin_sconv_tiled_on_matrix_cores (host) tells which kernel a call with this descriptor and a 16-byte
- * aligned d_plan takes: 1, 0 for the tiled kernel, or an error code as the call itself would return.
+ * aligned d_plan takes: 1 for the matrix cores, 0 for the tiled kernel, or an error code as the call itself would return.
+ * escoin_sconv_tiled_kernel tells it further: 0 for the tiled kernel, 1 for the one of three bf16 parts,
+ * 100*a + 10*b + c for the one of pairs with workgroups of a*b*c waves over a*64 output channels, b*64 positions and c
+ * shares of the input channels.
  *
  * d_in and d_plan that are 16-byte aligned let the kernel stage with 16-byte loads (or with
  * global -> LDS copies); any 4-byte aligned pointer is accepted.
@@ -188,6 +198,7 @@ int escoin_sconv_forward_tiled(const escoin_conv_desc *desc, const void *plan_ho
                                const void *d_plan, const float *d_in, float *d_out,
                                const float *d_bias, uint32_t flags, void *hip_stream);
 int escoin_sconv_tiled_on_matrix_cores(const escoin_conv_desc *desc, const void *plan_host);
+int escoin_sconv_tiled_kernel(const escoin_conv_desc *desc, const void *plan_host);
 
 #ifdef __cplusplus
 }

@@ -62,6 +62,7 @@ def lib() -> ctypes.CDLL:
         L.escoin_sconv_plan_build.argtypes = [D, vp, vp, vp, T, vp, ctypes.c_size_t]
         L.escoin_sconv_forward_tiled.argtypes = [D, vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
         L.escoin_sconv_tiled_on_matrix_cores.argtypes = [D, vp]
+        L.escoin_sconv_tiled_kernel.argtypes = [D, vp]
         _lib = L
     return _lib
 
@@ -207,6 +208,13 @@ def escoin_sconv_tiled_on_matrix_cores(desc, plan_host: np.ndarray) -> bool:
     return rc == 1
 
 
+def escoin_sconv_tiled_kernel(desc, plan_host: np.ndarray) -> int:
+    rc = lib().escoin_sconv_tiled_kernel(ctypes.byref(desc), _hptr(plan_host, np.uint8))
+    if rc < 0:
+        _check(rc, "escoin_sconv_tiled_kernel")
+    return rc
+
+
 class _PlanHeader(ctypes.Structure):
     """Mirror of the plan blob's header (csrc/plan.h), for diagnostics, tests and the bench."""
     _fields_ = ([("magic", ctypes.c_uint32), ("version", ctypes.c_uint32)]
@@ -221,7 +229,8 @@ class _PlanHeader(ctypes.Structure):
                 + [(k, ctypes.c_int32) for k in (
                     "CS", "pitch1", "VW", "WW", "WS", "CC0", "zero_floats", "max_regions", "MB", "n_dma")]
                 + [("off_dma", ctypes.c_uint64), ("off_zero", ctypes.c_uint64),
-                   ("mfma", ctypes.c_int32), ("mfma_nnz", ctypes.c_int32), ("off_mfma", ctypes.c_uint64)])
+                   ("mfma", ctypes.c_int32), ("mfma_nnz", ctypes.c_int32), ("off_mfma", ctypes.c_uint64),
+                   ("pair", ctypes.c_int32), ("pair_nnz", ctypes.c_int32), ("off_pair", ctypes.c_uint64), ("off_nz", ctypes.c_uint64)])
 
 
 def plan_header(plan: np.ndarray) -> dict:

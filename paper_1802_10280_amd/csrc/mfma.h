@@ -33,13 +33,13 @@ inline uint64_t mfma_weight_bytes(const Dims& d) {
     return (mfma_row_blocks(d) * mfma_chunks(d) * d.R * d.S + 1) * 3072;
 }
 inline uint64_t mfma_rowptr_bytes(const Dims& d) { return ((uint64_t)(d.M + 1) * 4 + 255) / 256 * 256; }
-inline uint64_t mfma_bytes(const Dims& d, int nnz) {
-    return mfma_weight_bytes(d) + mfma_rowptr_bytes(d) + (uint64_t)nnz * sizeof(MfmaNz);
-}
+inline uint64_t nz_bytes(const Dims& d, int nnz) { return mfma_rowptr_bytes(d) + (uint64_t)nnz * sizeof(MfmaNz); }
 
+double mfma_time(const Dims& d, double N);
 bool mfma_planned(const Dims& d, long long nnz);
 bool mfma_taken(const Dims& d, const PlanHeader& h);
-bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value, char* out);
+bool nz_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value, char* out);
+bool mfma_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out);
 int launch_sconv_mfma(const Dims& d, const PlanHeader& h, const char* d_plan, const float* d_in, float* d_out,
                       const float* d_bias, uint32_t flags, hipStream_t stream);
 int allow_dynamic_lds(const void* kernel, int bytes);

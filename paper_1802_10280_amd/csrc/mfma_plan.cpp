@@ -8,8 +8,7 @@
 
 namespace escoin {
 
-// Whether the matrix-core kernel is faster on a batch of N images, by estimates of both kernels in
-// microseconds.  A workgroup alone on its compute unit spends 1.6 us on a chunk (staging, barrier, the first
+// Microseconds for a batch of N images, and whether that is faster than the tiled kernel.  A workgroup alone on its compute unit spends 1.6 us on a chunk (staging, barrier, the first
 // wait) and 0.46 us on each of its taps; two that share one take 1.72 times as long for both.  The tiled
 // kernel is taken at its better: 36 TFLOP/s on the nonzeros (41 measured on a large layer at 50 % sparsity, 32
 // on 13x13 maps at 65 %, less the fewer nonzeros or positions there are).
@@ -17,13 +16,17 @@ namespace escoin {
 // That is 57.9, 86.9, 115.8 and 332 us where 56-58, 85, 115 and 341 were measured (64 channels, 25, 35 and 62
 // images of 63x63; 128 channels, 5x5, 64 of 32x32), so the margin can go; on such layers the tiled kernel was
 // 4-25 % slower than its estimate (67, 118, 158, 393 us at 71-75 and 65 % sparsity).
-static bool mfma_faster(const Dims& d, double N, long long nnz) {
+double mfma_time(const Dims& d, double N) {
     const double jobs = ceil(N * (d.H + d.pad) * (d.W + d.pad) / kMfmaTP) * (double)(mfma_row_blocks(d) / kMfmaWM);
     const double job = 6.0 + (double)mfma_chunks(d) * (1.6 + 0.46 * d.R * d.S);
+    if (jobs <= 256) return job;
+    if (mfma_window(d) <= kMfmaPairWindow) return ceil(jobs / 512) * 1.72 * job;
+    return ceil(jobs / 256) * job;
+}
+static bool mfma_faster(const Dims& d, double N, long long nnz) {
+    const double jobs = ceil(N * (d.H + d.pad) * (d.W + d.pad) / kMfmaTP) * (double)(mfma_row_blocks(d) / kMfmaWM);
     const double tiled = 2e-6 * (double)nnz * N * d.E * d.F / 36.0;
-    if (jobs <= 256) return job < 0.9 * tiled;
-    if (mfma_window(d) <= kMfmaPairWindow) return ceil(jobs / 512) * 1.72 * job < 0.9 * tiled;
-    return ceil(jobs / 256) * job < 1.04 * tiled;
+    return mfma_time(d, N) < (jobs <= 256 || mfma_window(d) <= kMfmaPairWindow ? 0.9 : 1.04) * tiled;
 }
 
 // Whether a plan carries the section: shapes the kernel takes, and pruned so little that a batch that
@@ -56,14 +59,12 @@ static float to_bf16(float x, uint16_t* bits) {  // rounds to nearest even; x is
     return r;
 }
 
-// Writes the section into `out` (zeroed).  False where it cannot stand for the CSR: a value outside the
-// range whose split keeps fp32 (Inf and NaN too), or a repeated column, whose values would have to be
-// added up first.
-bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value, char* out) {
-    const size_t RS = (size_t)d.R * d.S, chunks = mfma_chunks(d);
-    uint16_t* w = (uint16_t*)out;
-    int32_t* rp = (int32_t*)(out + mfma_weight_bytes(d));
-    MfmaNz* nz = (MfmaNz*)(out + mfma_weight_bytes(d) + mfma_rowptr_bytes(d));
+// Writes the row pointers and the nonzero values, decoded, into `out`.  False where a column is repeated: its
+// values would have to be added up first.
+bool nz_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, const float* value, char* out) {
+    const size_t RS = (size_t)d.R * d.S;
+    int32_t* rp = (int32_t*)out;
+    MfmaNz* nz = (MfmaNz*)(out + mfma_rowptr_bytes(d));
     std::vector<int32_t> seen((size_t)d.C * RS, -1);
     const int32_t plane = d.Hp * d.Wp;
     int32_t at = 0;
@@ -75,14 +76,6 @@ bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, 
             int32_t& was = seen[(size_t)c * RS + (size_t)r * d.S + s];
             if (was == m) return false;
             was = m;
-            uint16_t part[3];
-            if (!(fabsf(value[j]) >= kMfmaLeastWeight && fabsf(value[j]) <= kMfmaMostWeight)) return false;
-            const float rest = value[j] - to_bf16(value[j], &part[0]);
-            to_bf16(rest - to_bf16(rest, &part[1]), &part[2]);
-            // lane: channel m % 32, and which 8 of the 16 input channels; 8 of them per lane
-            const size_t step = ((size_t)(m / 32) * chunks + c / 16) * RS + (size_t)r * d.S + s;
-            const size_t lane = m % 32 + 32 * (size_t)(c % 16 / 8);
-            for (int k = 0; k < 3; ++k) w[((step * 3 + k) * 64 + lane) * 8 + c % 8] = part[k];
             nz[at].c = c;
             nz[at].r = (uint16_t)r;
             nz[at].s = (uint16_t)s;
@@ -91,6 +84,27 @@ bool mfma_write(const Dims& d, const int32_t* rowptr, const int32_t* stretched, 
         }
     }
     rp[d.M] = at;
+    return true;
+}
+
+// Writes the split weights into `out` (zeroed).  False where one is outside the range whose split keeps fp32
+// (Inf and NaN too).
+bool mfma_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out) {
+    const size_t RS = (size_t)d.R * d.S, chunks = mfma_chunks(d);
+    uint16_t* w = (uint16_t*)out;
+    for (int m = 0; m < d.M; ++m)
+        for (int j = rp[m]; j < rp[m + 1]; ++j) {
+            const float v = nz[j].val;
+            const int c = nz[j].c;
+            uint16_t part[3];
+            if (!(fabsf(v) >= kMfmaLeastWeight && fabsf(v) <= kMfmaMostWeight)) return false;
+            const float rest = v - to_bf16(v, &part[0]);
+            to_bf16(rest - to_bf16(rest, &part[1]), &part[2]);
+            // lane: channel m % 32, and which 8 of the 16 input channels; 8 of them per lane
+            const size_t step = ((size_t)(m / 32) * chunks + c / 16) * RS + (size_t)nz[j].r * d.S + nz[j].s;
+            const size_t lane = m % 32 + 32 * (size_t)(c % 16 / 8);
+            for (int k = 0; k < 3; ++k) w[((step * 3 + k) * 64 + lane) * 8 + c % 8] = part[k];
+        }
     return true;
 }
 

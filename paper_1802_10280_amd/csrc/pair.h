@@ -1,0 +1,43 @@
+// The layer on the matrix cores with fp32 operands as pairs of fp16 numbers: what its plan section holds and
+// which layers have one.
+#pragma once
+#include "common.h"
+#include "mfma.h"
+#include "plan.h"
+
+namespace escoin {
+
+constexpr int kPairReach = 127;            // taps reach at most so many window positions past a workgroup's own
+constexpr int kPairStepBytes = 2048;       // of 32 channels' weights for one tap of 16 input channels: two parts of 1024
+constexpr int kPairLdsBytes = 160 * 1024;
+
+// How a workgroup's waves are laid out: over 64 output channels each, 64 positions each, 16 input channels each.
+struct PairShape {
+    int MW, PW, KW;
+};
+
+// window positions a channel takes in LDS
+inline int pair_window(const Dims& d, const PairShape& s) {
+    return (64 * s.PW + (d.R - 1) * (d.W + d.pad) + d.S - 1 + 3) / 4 * 4;
+}
+// LDS: notes, the channels' exponents and biases, the positions' outputs and the window's words (head); then one
+// window buffer, or two where there is more than one round of channels; the waves' sums meet in the same place.
+inline int pair_head_bytes(const PairShape& s) { return 64 + 8 * 64 * s.MW + 4 * 64 * s.PW; }
+inline int pair_lds_bytes(const Dims& d, const PairShape& s) {
+    const int WR = pair_window(d, s), buffers = (int)mfma_chunks(d) > s.KW ? 2 : 1;
+    return pair_head_bytes(s) + 4 * WR + std::max(buffers * s.KW * 64 * WR, s.MW * s.PW * (s.KW - 1) * 64 * 256);
+}
+
+// two steps to ask for ahead
+inline uint64_t pair_weight_bytes(const Dims& d) {
+    return (mfma_row_blocks(d) * mfma_chunks(d) * d.R * d.S + 2) * kPairStepBytes;
+}
+inline uint64_t pair_bytes(const Dims& d) { return pair_weight_bytes(d) + mfma_rowptr_bytes(d); }  // with the rows' exponents
+
+bool pair_planned(const Dims& d, long long nnz, int WS);
+bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape);
+bool pair_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out);
+int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& shape, const char* d_plan, const float* d_in, float* d_out,
+                      const float* d_bias, uint32_t flags, hipStream_t stream);
+
+}  // namespace escoin

@@ -1,0 +1,157 @@
+// Host side of the fp16-pair form: which layers have one, and its section of the plan.
+#include <math.h>
+#include <string.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "pair.h"
+
+namespace escoin {
+
+// The layouts there are.  On a large layer (64x256x28x28, 256 3x3 filters) they take, in this order, 179, 245, 167 and
+// 162 us; on small ones the order turns round: 512 channels of 7x7, batch 32: 35, 33, 62, 57.
+static const PairShape kShapes[] = {{1, 1, 4}, {1, 1, 8}, {1, 2, 2}, {2, 1, 2}};
+
+// Fewer workgroups leave most compute units idle, where the tiled kernel has smaller ones.
+constexpr double kLeastJobs = 64;
+
+// Microseconds that a batch of N images takes in one of the layouts.  A workgroup takes 12000 clocks to begin and to
+// end (17000 in a launch of several rounds of them) and, with another one beside it or not, 900 a step (1180 with eight
+// waves) and 250 a staging task, where filters are three wide; with others 1400 and, staged without overlap, 2500.  The last workgroups to run count for more than their share.  2 GHz,
+// as measured over launches of this length.  That is 157, 33, 31, 26 and 96 us where 162, 37, 33, 30 and 100 were measured (28x28
+// with 256 channels, 56x56 with 64, 7x7 with 512, 14x14 with 256, 13x13 with 384) and 18, 10 and 12 where 19, 11 and 12
+// were (13 of 15x15 with 240, one of 41x44 with 24, 5 of 7x7 with 69).
+static double pair_time(const Dims& d, double N, const PairShape& s) {
+    const int waves = s.MW * s.PW * s.KW, lds = pair_lds_bytes(d, s), RS = d.R * d.S;
+    if (lds > kPairLdsBytes) return INFINITY;
+    const double jobs = ceil(N * (d.H + d.pad) * (d.W + d.pad) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW));
+    if (jobs < kLeastJobs) return INFINITY;
+    const double slots = waves == 4 && 2 * lds <= kPairLdsBytes ? 512 : 256;
+    const int chunks = (int)mfma_chunks(d), rounds = (chunks + s.KW - 1) / s.KW;
+    const double steps = ceil((double)chunks * RS / s.KW), tasks = ceil(2.0 * s.KW * ((pair_window(d, s) + 63) / 64) / waves);
+    double job = (jobs > slots ? 17000 : 12000) + steps * (d.S != 3 ? 1400 : waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * (d.S == 3 ? 250 : 2500);
+    const double full = floor(jobs / slots), rest = jobs / slots - full;
+    return 2.0 + std::max(1.0, full + (rest > 0 ? 0.5 + 0.5 * rest : 0.0)) * job / 2000.0;
+}
+
+// The tiled kernel's, at its better: 8 us and 36 TFLOP/s on the nonzeros.
+static double tiled_time(const Dims& d, double N, long long nnz) { return 8.0 + 2e-6 * (double)nnz * N * d.E * d.F / 36.0; }
+
+// How much faster it has to look: the tiled kernel beats its estimate by up to a seventh on small layers (32x16x28x28, 5x5:
+// 11.2 us, put at 13.4).
+constexpr double kMargin = 0.9;
+
+// The shapes the kernel takes.
+static bool pair_takes(const Dims& d) {
+    if (d.stride != 1 || d.R <= d.pad || d.S <= d.pad || d.C < 16 || d.M < 32) return false;
+    const long long pitch = d.W + d.pad, plane = (d.H + d.pad) * pitch;
+    if ((d.R - 1) * pitch + d.S - 1 > kPairReach || pair_weight_bytes(d) > (64ull << 20)) return false;
+    // positions, and the offsets inside the images that a workgroup's window may touch, in 32 bits
+    const long long images = (128 + kPairReach) / plane + 2;
+    return plane < (1 << 21) && images * d.C * d.H * d.W * 4 < (1ll << 31) && images * d.M * d.E * d.F < (1ll << 31);
+}
+
+// Relative errors against 64 bits, squared, times 1e14 (2-norm; n nonzeros a row, activations half zeros).  Two fp16
+// numbers hold 22 to 23 bits: with the product left out that makes 0.9e-7 whatever n is; the sums add to it, the less the more
+// waves share them.  The tiled kernel's chains of fp32 roundings are n / WS long, the kernel of three bf16 parts
+// rounds once per 16 channels.  Measured and (in brackets) by these, in 1e-7: pairs in two shares, n = 115: 1.15 (1.15), 461: 1.70
+// (1.68); in four, 461: 1.32 (1.32); in eight, 922: 1.37 (1.37), 1152: 1.39 (1.46).  Tiled, 115: 1.37 (1.33), 461: 2.64 (2.66).
+// bf16, 691: 1.16 (1.16), 1210: 1.55 (1.54).
+static double pair_error(double n, const PairShape& s) { return 0.81 + n * (s.KW == 2 ? 0.0044 : s.KW == 4 ? 0.0020 : 0.00116); }
+static double tiled_error(double n, int WS) { return 0.0154 * n / WS; }
+static double mfma_error(double n) { return 0.00195 * n; }
+
+// Whether a plan, whose tiled form splits rows over WS waves, carries the section: a layer that some batch is faster with,
+// and no less exact.
+bool pair_planned(const Dims& d, long long nnz, int WS) {
+    const double n = (double)nnz / d.M, N = 64.0 * 8192 / ((double)(d.H + d.pad) * (d.W + d.pad));
+    if (!pair_takes(d)) return false;
+    for (const PairShape& s : kShapes)
+        if (pair_error(n, s) < 0.95 * tiled_error(n, WS) && pair_time(d, N, s) < kMargin * tiled_time(d, N, nnz)) return true;
+    return false;
+}
+
+// Whether a forward call on this batch takes the section of a plan made for this layer, and in which layout: one that is
+// faster and no less exact than the kernel the call would take else.
+bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
+    if (h.pair != 1 || !pair_planned(d, h.pair_nnz, h.WS)) return false;
+    const long long total = (long long)d.N * (d.H + d.pad) * (d.W + d.pad);
+    if (total > (1ll << 30) || total / 64 * (long long)mfma_row_blocks(d) > (1ll << 30)) return false;
+    const bool bf16 = mfma_taken(d, h);
+    const double n = (double)h.pair_nnz / d.M, error = bf16 ? mfma_error(n) : 0.95 * tiled_error(n, h.WS);
+    double best = kMargin * (bf16 ? mfma_time(d, d.N) : tiled_time(d, d.N, h.pair_nnz));
+    bool taken = false;
+    for (const PairShape& s : kShapes) {
+        if (pair_error(n, s) > error) continue;
+        const double t = pair_time(d, d.N, s);
+        if (t < best) {
+            best = t;
+            *shape = s;
+            taken = true;
+        }
+    }
+    return taken;
+}
+
+// x, below 2^15 in size, to the nearest fp16 number (ties to even); *back is its value
+static uint16_t to_half(float x, float* back) {
+    uint32_t u, sign;
+    memcpy(&u, &x, 4);
+    sign = u >> 16 & 0x8000u;
+    u &= 0x7fffffffu;
+    uint32_t h;
+    float v;
+    if (u < 0x38800000u) {  // below 2^-14: multiples of 2^-24, as the last bits of a sum with 1/2
+        memcpy(&v, &u, 4);
+        v += 0.5f;
+        memcpy(&h, &v, 4);
+        h -= 0x3f000000u;
+        v -= 0.5f;
+    } else {
+        u += 0xfffu + (u >> 13 & 1u);
+        u &= 0xffffe000u;
+        h = (u >> 13) - (112u << 10);
+        memcpy(&v, &u, 4);
+    }
+    *back = sign ? -v : v;
+    return (uint16_t)(h | sign);
+}
+
+// Writes the weights and the rows' exponents into `out` (zeroed).  False where it cannot stand for the CSR: a value
+// that is not finite, a row whose values span more than 27 binades (each row is scaled so that its largest lies below
+// 2^15; the parts of one below 2^-13 would lose bits), or a row of fewer than 32 nonzeros, which fp32 rounds less often
+// than this form errs.
+bool pair_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out) {
+    const size_t RS = (size_t)d.R * d.S, chunks = mfma_chunks(d);
+    uint16_t* w = (uint16_t*)out;
+    int32_t* exps = (int32_t*)(out + pair_weight_bytes(d));
+    for (int m = 0; m < d.M; ++m) {
+        if (rp[m + 1] - rp[m] < 32) return false;
+        float most = 0.0f, least = INFINITY;
+        for (int j = rp[m]; j < rp[m + 1]; ++j) {
+            const float v = fabsf(nz[j].val);
+            if (!(v < INFINITY)) return false;
+            most = std::max(most, v);
+            least = std::min(least, v);
+        }
+        exps[m] = 14 - ilogbf(most);
+        if (ldexpf(least, exps[m]) < 0x1p-13f) return false;
+        // in two factors: either may be past the largest float, or below the least, but not both
+        const float up = ldexpf(1.0f, exps[m] / 2), up2 = ldexpf(1.0f, exps[m] - exps[m] / 2);
+        for (int j = rp[m]; j < rp[m + 1]; ++j) {
+            const float v = nz[j].val * up * up2;
+            float high, rest;
+            uint16_t part[2];
+            part[0] = to_half(v, &high);
+            part[1] = to_half((v - high) * 2048.0f, &rest);
+            const int c = nz[j].c;
+            const size_t step = ((size_t)(m / 32) * chunks + c / 16) * RS + (size_t)nz[j].r * d.S + nz[j].s;
+            const size_t lane = m % 32 + 32 * (size_t)(c % 16 / 8);
+            for (int k = 0; k < 2; ++k) w[((step * 2 + k) * 64 + lane) * 8 + c % 8] = part[k];
+        }
+    }
+    return true;
+}
+
+}  // namespace escoin

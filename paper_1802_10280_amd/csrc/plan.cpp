@@ -34,6 +34,7 @@
 
 #include "common.h"
 #include "mfma.h"
+#include "pair.h"
 #include "plan.h"
 
 namespace escoin {
@@ -689,7 +690,15 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
     const bool with_mfma = !tuned && mfma_planned(d, rowptr[d.M]);
     h.mfma = h.mfma_nnz = 0;
     h.off_mfma = off;
-    if (with_mfma) off = align_up64(off + mfma_bytes(d, rowptr[d.M]), 256);
+    // the split weights and, behind the first of the two kinds, the nonzeros
+    const bool with_pair = !tuned && pair_planned(d, rowptr[d.M], h.WS);
+    if (with_mfma) off += mfma_weight_bytes(d);
+    else if (with_pair) off += pair_bytes(d);
+    h.off_nz = off;
+    if (with_mfma || with_pair) off = align_up64(off + nz_bytes(d, rowptr[d.M]), 256);
+    h.pair = h.pair_nnz = 0;
+    h.off_pair = with_mfma ? off : h.off_mfma;
+    if (with_mfma && with_pair) off = align_up64(off + pair_bytes(d), 256);
     h.total_bytes = off;
     *bytes = (size_t)off;
     if (!out) return ESCOIN_OK;
@@ -779,9 +788,16 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
     }
     // room is made by the stored entries (the size query has no values); explicit zeros cost the tiled
     // kernel nothing, so whether the section is worth having is asked again without them
-    h.mfma = with_mfma && mfma_planned(d, nnz_total) && mfma_write(d, rowptr, stretched, value, base + h.off_mfma) ? 1 : 0;
-    if (h.mfma) h.mfma_nnz = (int32_t)nnz_total;
-    std::memcpy(base, &h, sizeof(h));  // the header once more, now with WW, n_dma and mfma
+    const bool mfma = with_mfma && mfma_planned(d, nnz_total), pair = with_pair && pair_planned(d, nnz_total, h.WS);
+    if ((mfma || pair) && nz_write(d, rowptr, stretched, value, base + h.off_nz)) {
+        const int32_t* rp = (const int32_t*)(base + h.off_nz);
+        const MfmaNz* nz = (const MfmaNz*)(base + h.off_nz + mfma_rowptr_bytes(d));
+        h.mfma = mfma && mfma_write(d, rp, nz, base + h.off_mfma) ? 1 : 0;
+        if (h.mfma) h.mfma_nnz = (int32_t)nnz_total;
+        h.pair = pair && pair_write(d, rp, nz, base + h.off_pair) ? 1 : 0;
+        if (h.pair) h.pair_nnz = (int32_t)nnz_total;
+    }
+    std::memcpy(base, &h, sizeof(h));  // the header once more, now with WW, n_dma, mfma and pair
     std::memcpy(base + h.off_lanes, lanes.data(), lanes.size() * sizeof(LaneSlot));
     std::memcpy(base + h.off_perm, slot.data(), slot.size() * sizeof(RowSlot));
     std::memcpy(base + h.off_perm + slot.size() * sizeof(RowSlot), group_regions.data(), (size_t)h.n_mgroups * 4);

@@ -103,6 +103,11 @@ struct PlanHeader {
     int32_t mfma_nnz;    // nonzero values in that section; 0 in plans from before their range was
                          // checked, which stay with the tiled kernel
     uint64_t off_mfma;   // split weights, row pointers, nonzeros
+    int32_t pair;        // 1: the section of weights as pairs of fp16 numbers is there (pair.h); 0 in plans
+                         // from before there was one
+    int32_t pair_nnz;    // nonzero values in that section
+    uint64_t off_pair;   // weights, row exponents
+    uint64_t off_nz;     // row pointers, nonzeros, for both sections
 };
 static_assert(sizeof(PlanHeader) <= 512, "the sections start 512 bytes into the blob");
 

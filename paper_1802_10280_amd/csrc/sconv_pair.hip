@@ -1,0 +1,627 @@
+// sconv on the matrix cores with fp32 operands as pairs of fp16 numbers, for all but the most heavily pruned layers of
+// stride 1.
+//
+// The layer is one product per filter tap over the flat padded positions of the whole batch, zeros included, as in
+// sconv_mfma.hip.  There an operand is three bf16 parts and a product six matrix instructions, here two fp16
+// parts and three:
+//   x = h + l / 2^11,  h = fp16(x), l = fp16((x - h) * 2^11),   x*w = hh + (hl + lh) / 2^11.
+// h and l hold 22 bits and l's sign; l is scaled so that its exponent ends where h's does.  The product left out and the bits
+// lost make a product uncertain by 2^-21 at most, 0.7e-7 in the mean: more than one fp32 rounding, less than a chain of
+// some fifty.  hh has an accumulator of its own, and the channels are shared by several waves, whose sums meet at the end: the
+// shorter chains are more exact (the rule in pair_plan.cpp weighs the forms' errors).
+//
+// fp16 ends at 2^16 and 2^-24, so inputs are scaled by a power of two, one for a workgroup: the first 32 channels or so that it
+// stages are put below 2^10, later ones have 2^6 of room.  If a sum is not finite in the end, the workgroup looks for
+// its largest finite input and goes through its channels again with the scale for that one; what is not finite then
+// met an Inf, a NaN or a sum past fp32, and is computed from the nonzeros (redo()).  Inputs below 2^-13, scaled, lose bits:
+// their number bounds what a sum may have lost, and sums too small for that go the same way.
+//
+// A wave takes 64 channels by 64 positions of one chunk of 16 input channels at a time: 12 matrix instructions of 32 clocks a
+// tap against four 16-byte LDS reads and 4 KB of weights from L1/L2, asked for two taps ahead.  One wave alone issues
+// too slowly to keep a matrix core busy (a tap took 1100 clocks where what lies around its instructions was in one
+// place): the rest of a step is strung out between them and, for filters three wide, a row of taps is one block without
+// address arithmetic.  Staging the next chunks goes along in the same way.
+// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312); 64x384x13x13, 384 filters, 65 %: 118 (three
+// bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy a third to a half of
+// the time (76 us of the first one's, at 2.4 GHz); the rest is the workgroups' beginnings and ends, 12000-17000 clocks each, which only
+// the other workgroup of a compute unit hides, and the first two rounds, when all of them ask for their inputs at once.
+#include <float.h>
+#include <algorithm>
+
+#include "common.h"
+#include "mfma_device.h"
+#include "pair.h"
+#include "plan.h"
+
+namespace escoin {
+namespace {
+
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef int i4 __attribute__((ext_vector_type(4)));
+
+// Loads through a buffer descriptor: what lies past its end reads as zero, and the scalar offset costs no vector
+// instruction.
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ inline Rsrc rsrc_of(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
+}
+constexpr uint32_t kNowhere = 0x80000000u;  // past the end of every descriptor here
+
+struct PairArgs : MfmaArgs {
+    const int32_t* exps;      // of the rows' weights: what they were scaled up by
+    int WR;          // window positions a channel takes in LDS
+    int groups;      // of 64 window positions
+    uint32_t w_bytes;
+};
+
+#define ESCOIN_INLINE __attribute__((always_inline))
+constexpr int kStepBytes = kPairStepBytes;
+
+// x / d and what is left, for x and d below 2^22 (one_over: 1 / d, rounded): the product is off by less than one.
+__device__ inline int divide(int x, int d, float one_over, int* rest) {
+    int q = (int)((float)x * one_over), r = x - q * d;
+    if (r < 0) { --q; r += d; }
+    if (r >= d) { ++q; r -= d; }
+    *rest = r;
+    return q;
+}
+
+// The largest of the wave's values, in lane 63: lane shifts of 1, 2, 4, 8 in rows of 16, then the rows' last lanes.
+__device__ inline uint32_t wave_max(uint32_t x) {
+#define ESCOIN_DPP(CTRL, ROWS) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false));
+    ESCOIN_DPP(0x111, 0xf) ESCOIN_DPP(0x112, 0xf) ESCOIN_DPP(0x114, 0xf) ESCOIN_DPP(0x118, 0xf) ESCOIN_DPP(0x142, 0xa) ESCOIN_DPP(0x143, 0xc)
+#undef ESCOIN_DPP
+    return x;
+}
+
+// What the waves of a workgroup tell each other.
+template <int PW>
+struct Notes {
+    uint64_t again[PW];  // positions that have a sum that cannot be used
+    int lost;            // eights of inputs with one that loses bits, zeros apart
+    uint32_t peak;       // bits of the largest finite |x| that the scale is made for
+};
+
+// The LDS of a workgroup.
+template <int MW, int PW>
+struct Room {
+    static constexpr int kHead = 64 + 8 * 64 * MW + 4 * 64 * PW;  // pair_head_bytes()
+    char* lds;
+    int WR;
+    __device__ Notes<PW>* notes() const { return (Notes<PW>*)lds; }
+    __device__ int* row_exp() const { return (int*)(lds + 64); }
+    __device__ float* row_bias() const { return (float*)(lds + 64 + 4 * 64 * MW); }
+    // offset of a position's output, channel 0 of image n_first being 0; -1 where it is none
+    __device__ int* out_at() const { return (int*)(lds + 64 + 8 * 64 * MW); }
+    __device__ uint32_t* tab() const { return (uint32_t*)(lds + kHead); }  // [WR]: byte offset of a window position in channel 0
+    __device__ char* win() const { return lds + kHead + 4 * WR; }          // [buffer][chunk of the round][part][8-channel half][WR] x 16 bytes
+};
+
+// One pass over all channels: the wave's share of the sums, scaled by 2^-(ex + the row's exponent) in `v`, and which
+// positions have one that cannot be used.  AGAIN: with the scale for notes.peak, not one guessed from the first inputs.
+template <int MW, int PW, int KW, bool AGAIN>
+__device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> room, Rsrc in, Rsrc wr, int lane, int wave, int mg, float (&v)[64 / KW],
+                                         int* scale) {
+    constexpr int kWaves = MW * PW * KW, TM = 64 * MW;
+    const int wp = wave % PW, kg = wave / PW % KW, wm = wave / (PW * KW);
+    const int WR = room.WR, sub_bytes = 4 * 16 * WR, buf_bytes = KW * sub_bytes;
+    char* const win = room.win();
+    const uint32_t* const tab = room.tab();
+    Notes<PW>* const notes = room.notes();
+    const int HW4 = a.H * a.W * 4, last_channel = (a.C - 1) * HW4, RS = a.R * a.S;
+    const int n_rounds = (a.n_chunks + KW - 1) / KW;
+    // a round's steps (chunk, tap) are shared evenly: whole chunks where every wave has one
+    auto first_step = [&](int round, int k) ESCOIN_INLINE { return min(KW, a.n_chunks - round * KW) * RS * k / KW; };
+
+    // ---- staging: a task is one 8-channel half of a chunk and 64 window positions (the last 64 overlap the ones
+    // before); one past the last stands for the last, so that every wave has the same number of them.  Channels past
+    // the end repeat the last one: their weights are zero.
+    const int n_tasks = 2 * KW * a.groups, my_tasks = (n_tasks + kWaves - 1) / kWaves, in_threes = my_tasks / 3 * 3;
+    struct Task { float x[8]; uint32_t src; int half, first; };
+    auto locate = [&](Task& t, int index) ESCOIN_INLINE {
+        const int task = min(wave + index * kWaves, n_tasks - 1);
+        t.half = task & (2 * KW - 1);
+        t.first = min(task / (2 * KW) * 64, WR - 64);
+        t.src = tab[t.first + lane];
+    };
+    auto fetch_four = [&](Task& t, int round, auto first) ESCOIN_INLINE {
+        constexpr int kFirst = decltype(first)::value;
+        const int from = (round * KW * 2 + t.half) * 8 * HW4;
+#pragma unroll
+        for (int j = kFirst; j < kFirst + 4; ++j)
+            t.x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in, t.src, min(from + j * HW4, last_channel), 0));
+    };
+    typedef std::integral_constant<int, 0> First;
+    typedef std::integral_constant<int, 4> Second;
+    auto fetch = [&](Task& t, int round) ESCOIN_INLINE {
+        fetch_four(t, round, First{});
+        fetch_four(t, round, Second{});
+    };
+    int ex = 0;         // inputs are taken times 2^ex
+    uint32_t low = 0;   // twice the bits of the least |x| of which that loses nothing
+    int lost = 0;
+    auto commit = [&](const Task& t, int buf) ESCOIN_INLINE {
+        h8 h, l;
+        uint32_t least = 0xffffffffu;  // as 2 * bits - 1: a zero becomes the largest
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) {
+            const float2v x = {ldexpf(t.x[j], ex), ldexpf(t.x[j + 1], ex)};
+            const h2 hh = __builtin_convertvector(x, h2);
+            h[j] = hh[0];
+            h[j + 1] = hh[1];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                least = min(least, (__float_as_uint(t.x[j + k]) << 1) - 1u);
+                l[j + k] = (_Float16)fmaf(-2048.0f, (float)hh[k], ldexpf(t.x[j + k], ex + 11));
+            }
+        }
+        lost += least < low ? 1 : 0;
+        h8* const o = (h8*)(win + buf * buf_bytes + (t.half >> 1) * sub_bytes) + (t.half & 1) * WR + t.first + lane;
+        o[0] = h;
+        o[2 * WR] = l;
+    };
+
+    f16v big[2][2], small[2][2];
+    struct Weights { u4 p[2][2]; } w0, w1, w2;
+    const int row_blk = (mg * MW + wm) * 2;
+    const int blk_bytes = a.n_chunks * RS * kStepBytes;
+    // What the steps ask for runs two steps ahead of them, through the rounds.
+    const int regular_at = ((n_rounds - 1) * KW + kg) * RS * kStepBytes;  // of the last round, were it a whole one
+    const int last_begin = first_step(n_rounds - 1, kg);
+    const int last_skip = ((n_rounds - 1) * KW * RS + last_begin) * kStepBytes - regular_at;
+    const int last_more = first_step(n_rounds - 1, kg + 1) - last_begin - RS;
+    const int only = n_rounds == 1 ? 1 : 0;
+    int pf_round = 0, pf_at = row_blk * blk_bytes + kg * RS * kStepBytes + only * last_skip, pf_left = RS + only * last_more;
+    auto weights = [&](Weights& o, int k, int p, int further = 0) ESCOIN_INLINE {
+        o.p[p][k] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16 + k * 1024 + further, p ? pf_at + blk_bytes : pf_at, 0);
+    };
+    auto weights_next = [&]() ESCOIN_INLINE {
+        const int turn = --pf_left <= 0 ? 1 : 0;
+        pf_round += turn;
+        const int last = pf_round >= n_rounds - 1 ? turn : 0;
+        pf_at += kStepBytes + turn * (KW - 1) * RS * kStepBytes + last * last_skip;
+        pf_left += turn * RS + last * last_more;
+    };
+    auto all_weights = [&](Weights& o) ESCOIN_INLINE {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) weights(o, k, p);
+        weights_next();
+    };
+
+    // Every round but the last gives each wave RS steps, so none is empty before the last; there, a wave without
+    // steps only helps with the staging.
+    Task ta, tb, tc;
+    {
+        Task t[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) locate(t[k], k);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) fetch(t[k], 0);
+        if (my_tasks > 4) {
+#pragma unroll
+            for (int k = 4; k < 8; ++k) locate(t[k], k);
+#pragma unroll
+            for (int k = 4; k < 8; ++k) fetch(t[k], 0);
+        }
+        all_weights(w0);
+        all_weights(w1);
+        if (!AGAIN) {
+            uint32_t most = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t b = __float_as_uint(t[k].x[j]) & 0x7fffffffu;
+                    most = max(most, b < 0x7f800000u ? +b : 0u);
+                }
+            most = wave_max(most);
+            if (lane == 63) atomicMax(&notes->peak, most);
+        }
+        __syncthreads();
+        const uint32_t peak = __builtin_amdgcn_readfirstlane(notes->peak);
+        // 2^7 of room above the first ones, where the second pass knows the largest
+        ex = (peak ? 127 - (int)(peak >> 23) : 0) + (AGAIN ? 14 : 9);
+        low = (uint32_t)max(0, 127 - 13 - ex) << 24;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) commit(t[k], 0);
+        if (my_tasks > 4) {
+#pragma unroll
+            for (int k = 4; k < 8; ++k) commit(t[k], 0);
+        }
+        for (int i = 8; i < my_tasks; ++i) {
+            locate(ta, i);
+            fetch(ta, 0);
+            commit(ta, 0);
+        }
+    }
+    locate(ta, 0);
+    locate(tb, 1);
+    locate(tc, 2);
+    if (n_rounds > 1) {
+        fetch(ta, 1);
+        fetch(tb, 1);
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) { big[p][q] = (f16v)(0.0f); small[p][q] = (f16v)(0.0f); }
+    __syncthreads();
+    for (int round = 0; round < n_rounds; ++round) {
+        const bool more = round + 1 < n_rounds;
+        const int buf = round & 1;
+        const int begin = first_step(round, kg), end = first_step(round, kg + 1);
+        int sub = begin / RS, tap = begin - sub * RS, r = tap / a.S, s = tap - r * a.S;
+        const char* row = win + buf * buf_bytes + sub * sub_bytes + ((lane >> 5) * WR + wp * 64 + (lane & 31) + r * a.pitch + s) * 16;
+        h8 xh0, xh1;
+        const auto read = [&](int k, int q) ESCOIN_INLINE -> h8 { return *(const h8*)(row + (32 * q + 2 * WR * k) * 16); };
+        int i = begin, task = 0;
+        auto step = [&](const Weights& c, Weights& cn) ESCOIN_INLINE {
+            __builtin_amdgcn_s_waitcnt(0x0f74);  // the step's weights were asked for two steps ago, the next one's are younger
+            // One wave issues too slowly to keep the matrix cores busy with what a step needs around them in one
+            // place: a little of it follows each matrix instruction.
+#define ESCOIN_FENCE __builtin_amdgcn_sched_barrier(0x6);
+#define ESCOIN_MFMA(ACC, A, B, P, Q)                                                                                    \
+    ESCOIN_FENCE                                                                                                        \
+    ACC[P][Q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, c.p[P][A]), B##Q, ACC[P][Q], 0, 0, 0); \
+    ESCOIN_FENCE
+            h8 xl0, xl1;
+            ESCOIN_MFMA(big, 0, xh, 0, 0)
+            xl0 = read(1, 0);
+            ESCOIN_MFMA(big, 0, xh, 0, 1)
+            xl1 = read(1, 1);
+            row += 16;
+            if (++s == a.S) {
+                s = 0;
+                row += (a.pitch - a.S) * 16;
+                if (++r == a.R) {
+                    r = 0;
+                    row += sub_bytes - a.R * a.pitch * 16;
+                }
+            }
+            ESCOIN_MFMA(big, 0, xh, 1, 0)
+            ESCOIN_MFMA(big, 0, xh, 1, 1)
+            ESCOIN_MFMA(small, 1, xh, 0, 0)
+            weights(cn, 0, 0);
+            ESCOIN_MFMA(small, 1, xh, 0, 1)
+            weights(cn, 0, 1);
+            ESCOIN_MFMA(small, 1, xh, 1, 0)
+            weights(cn, 1, 0);
+            ESCOIN_MFMA(small, 1, xh, 1, 1)
+            weights(cn, 1, 1);
+            weights_next();
+            xh0 = read(0, 0);  // the next step's; after the last one what lies behind is read and not used
+            xh1 = read(0, 1);
+            __builtin_amdgcn_sched_barrier(0);  // a task is not looked at before this
+            ESCOIN_MFMA(small, 0, xl, 0, 0)
+            ESCOIN_MFMA(small, 0, xl, 0, 1)
+            ESCOIN_MFMA(small, 0, xl, 1, 0)
+            ESCOIN_MFMA(small, 0, xl, 1, 1)
+            ESCOIN_FENCE
+#undef ESCOIN_MFMA
+#undef ESCOIN_FENCE
+            ++i;
+        };
+        // The three taps of a filter row at a time, where the filter is three wide: no addresses to work out between.
+        const int part = 2 * WR * 16;
+        auto three = [&](auto stage) ESCOIN_INLINE {
+            constexpr bool STAGE = decltype(stage)::value;
+#define ESCOIN_FENCE __builtin_amdgcn_sched_barrier(0x6);
+#define ESCOIN_MFMA(ACC, SET, A, B, P, Q)                                                                                    \
+    ESCOIN_FENCE                                                                                                        \
+    ACC[P][Q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, SET.p[P][A]), B##Q, ACC[P][Q], 0, 0, 0); \
+    ESCOIN_FENCE
+            // T: the tap; SET: its weights; CN: the set that the ones asked for now go to
+#define ESCOIN_STEP(T, SET, CN, FURTHER, NOW, NEXT, NEXT_ROW)                                                         \
+    __builtin_amdgcn_s_waitcnt(STAGE ? 0x4f74 : 0x0f74);                                                              \
+    ESCOIN_MFMA(big, SET, 0, xh, 0, 0)                                                                                \
+    xl0 = *(const h8*)(row + part + 16 * T);                                                                          \
+    ESCOIN_MFMA(big, SET, 0, xh, 0, 1)                                                                                \
+    xl1 = *(const h8*)(row + part + 16 * T + 512);                                                                    \
+    ESCOIN_MFMA(big, SET, 0, xh, 1, 0)                                                                                \
+    weights(CN, 0, 0, FURTHER);                                                                                       \
+    ESCOIN_MFMA(big, SET, 0, xh, 1, 1)                                                                                \
+    weights(CN, 0, 1, FURTHER);                                                                                       \
+    ESCOIN_MFMA(small, SET, 1, xh, 0, 0)                                                                              \
+    weights(CN, 1, 0, FURTHER);                                                                                       \
+    ESCOIN_MFMA(small, SET, 1, xh, 1, 0)                                                                              \
+    xh0 = *(const h8*)(NEXT_ROW);                                                                                     \
+    ESCOIN_MFMA(small, SET, 1, xh, 0, 1)                                                                              \
+    weights(CN, 1, 1, FURTHER);                                                                                       \
+    ESCOIN_MFMA(small, SET, 1, xh, 1, 1)                                                                              \
+    xh1 = *(const h8*)((NEXT_ROW) + 512);                                                                             \
+    __builtin_amdgcn_sched_barrier(0);                                                                                \
+    ESCOIN_MFMA(small, SET, 0, xl, 0, 0)                                                                              \
+    if (STAGE) fetch_four(NEXT, round + 1, First{});                                                                  \
+    ESCOIN_MFMA(small, SET, 0, xl, 1, 0)                                                                              \
+    if (STAGE) fetch_four(NEXT, round + 1, Second{});                                                                 \
+    ESCOIN_MFMA(small, SET, 0, xl, 0, 1)                                                                              \
+    ESCOIN_MFMA(small, SET, 0, xl, 1, 1)                                                                              \
+    if (STAGE) {                                                                                                      \
+        commit(NOW, buf ^ 1);                                                                                         \
+        locate(NOW, ++task + 2);                                                                                      \
+    }                                                                                                                 \
+    ESCOIN_FENCE
+            h8 xl0, xl1;
+            const char* const next_row = row + (++r == a.R ? sub_bytes - (a.R - 1) * a.pitch * 16 : a.pitch * 16);
+            if (r == a.R) r = 0;
+            ESCOIN_STEP(0, w0, w2, 0, ta, tc, row + 16)
+            weights_next();
+            ESCOIN_STEP(1, w1, w0, 0, tb, ta, row + 32)
+            ESCOIN_STEP(2, w2, w1, kStepBytes, tc, tb, next_row)
+            pf_at += 2 * kStepBytes;
+            pf_left -= 2;
+            row = next_row;
+            i += 3;
+#undef ESCOIN_STEP
+#undef ESCOIN_MFMA
+#undef ESCOIN_FENCE
+        };
+        const std::true_type with{};
+        const std::false_type plain{};
+        if (i < end) {
+            xh0 = read(0, 0);
+            xh1 = read(0, 1);
+            if (a.S == 3 && s == 0 && (end - begin) % 3 == 0) {
+                if (more && end - i >= in_threes)
+                    while (task < in_threes) three(with);
+                while (i < end) three(plain);
+            }
+            for (;;) {
+                if (i == end) break;
+                step(w0, w2);
+                if (i == end) {
+                    const Weights t = w0;
+                    w0 = w1; w1 = w2; w2 = t;
+                    break;
+                }
+                step(w1, w0);
+                if (i == end) {
+                    const Weights t = w0;
+                    w0 = w2; w2 = w1; w1 = t;
+                    break;
+                }
+                step(w2, w1);
+            }
+        }
+        if (more) {
+            // the one or two tasks left over have been asked for (all of them have not, where a round has few steps)
+            if (task < my_tasks) commit(ta, buf ^ 1);
+            if (task + 1 < my_tasks) commit(tb, buf ^ 1);
+            for (task += 2; task < my_tasks; ++task) {
+                locate(ta, task);
+                fetch(ta, round + 1);
+                commit(ta, buf ^ 1);
+            }
+            locate(ta, 0);
+            locate(tb, 1);
+            locate(tc, 2);
+            if (round + 2 < n_rounds) {
+                fetch(ta, round + 2);
+                fetch(tb, round + 2);
+            }
+        }
+        __syncthreads();
+    }
+    if (lost) atomicAdd(&notes->lost, lost);
+
+    // ---- the waves' sums over their channels meet in LDS (the window is dead): each finishes a share of the outputs
+    constexpr int kShare = 64 / KW;
+    auto part = [&](int i) ESCOIN_INLINE { return fmaf(0x1p-11f, small[i >> 5][i >> 4 & 1][i & 15], big[i >> 5][i >> 4 & 1][i & 15]); };
+    f4* const meet = (f4*)win + (wm * PW + wp) * KW * (KW - 1) * (kShare / 4) * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < KW; ++j) {
+        if (j == kg) {
+#pragma unroll
+            for (int i = 0; i < kShare; ++i) v[i] = part(j * kShare + i);
+        } else {
+            f4* const o = meet + (j * (KW - 1) + (kg > j ? kg - 1 : kg)) * (kShare / 4) * 64;
+#pragma unroll
+            for (int i = 0; i < kShare / 4; ++i) {
+                f4 s;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s[b] = part(j * kShare + 4 * i + b);
+                o[i * 64] = s;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < KW - 1; ++k) {
+        const f4* const o = meet + (kg * (KW - 1) + k) * (kShare / 4) * 64;
+#pragma unroll
+        for (int i = 0; i < kShare / 4; ++i) {
+            const f4 s = o[i * 64];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[4 * i + b] += s[b];
+        }
+    }
+
+    // an input below 2^-13 is off by 2^-36 at most, a weight below 2^15: they matter to sums this small
+    const float small_sum = 16.0f * (float)notes->lost;
+    constexpr int kTiles = kShare > 16 ? kShare / 16 : 1, kEach = kShare / kTiles;
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) {
+        const int tile = (kg * kShare + t * kEach) / 16;
+        const bool inside = room.out_at()[wp * 64 + (tile & 1) * 32 + (lane & 31)] >= 0;
+        const int m = mg * TM + wm * 64 + (tile >> 1) * 32 + 4 * (lane >> 5) + (kEach < 16 ? 2 * (kg * kShare % 16) : 0);
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < kEach; ++i)
+            bad |= m + 8 * (i / 4) + i % 4 < a.M && !(fabsf(v[t * kEach + i]) <= FLT_MAX && fabsf(v[t * kEach + i]) >= small_sum);
+        const uint64_t lanes = __ballot(bad && inside);
+        if (lanes != 0 && lane == 0)
+            atomicOr((unsigned long long*)&notes->again[wp], ((lanes | lanes >> 32) & 0xffffffffu) << (32 * (tile & 1)));
+    }
+    __syncthreads();  // before the stores: nothing waits for those unless some outputs are computed again
+    uint64_t any = 0;
+#pragma unroll
+    for (int run = 0; run < PW; ++run) any |= notes->again[run];
+    *scale = ex;
+    return any;
+}
+
+// MW, PW: waves over channels and positions, 64 each; KW: over the input channels, 16 each a round.
+template <int MW, int PW, int KW>
+__global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const PairArgs a) {
+    constexpr int kWaves = MW * PW * KW, kThreads = 64 * kWaves, TP = 64 * PW, TM = 64 * MW;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int jobs = a.n_tiles * a.n_mgroups, jq = jobs >> 3, jr = jobs & 7;
+    if (slot >= jq + (xcd < jr ? 1 : 0)) return;  // the whole workgroup, before any barrier
+    const int job = xcd * jq + min(xcd, jr) + slot;
+    const int tile = job / a.n_mgroups, mg = job - tile * a.n_mgroups;
+    const int t0 = tile * TP;
+    const int HW = a.H * a.W, CHW = a.C * HW, EF = a.E * a.F;
+    const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
+
+    const Room<MW, PW> room = {lds, a.WR};
+    Notes<PW>* const notes = room.notes();
+    const int row = min(mg * TM + tid, a.M - 1);
+    int row_exp = 0;
+    float row_bias = 0.0f;
+    if (tid < TM) {
+        row_exp = a.exps[row];
+        if (has_bias) row_bias = a.bias[row];
+    }
+    const int n_first = t0 / a.plane, u_first = t0 - n_first * a.plane;
+    const float one_over_plane = 1.0f / (float)a.plane, one_over_pitch = 1.0f / (float)a.pitch;
+    for (int i = tid; i < a.WR; i += kThreads) {
+        int rem, col;
+        const int n = divide(u_first + i, a.plane, one_over_plane, &rem), line = divide(rem, a.pitch, one_over_pitch, &col);
+        const int y = line - a.pad, x = col - a.pad;
+        const bool there = n_first + n < a.N;
+        room.tab()[i] = there && y >= 0 && x >= 0 ? (uint32_t)(n * CHW + y * a.W + x) * 4u : kNowhere;
+        if (i < TP) room.out_at()[i] = there && line < a.E && col < a.F ? n * a.M * EF + line * a.F + col : -1;
+    }
+    if (tid < TM) {
+        room.row_exp()[tid] = row_exp;
+        room.row_bias()[tid] = row_bias;
+    }
+    if (tid < PW) notes->again[tid] = 0;
+    if (tid == PW) notes->lost = 0;
+    if (tid == PW + 1) notes->peak = 0;
+    const size_t left = (size_t)(a.N - n_first) * CHW * 4;
+    const Rsrc in = rsrc_of(a.in + (size_t)n_first * CHW, (uint32_t)min(left, (size_t)kNowhere));
+    const Rsrc wr = rsrc_of(a.w, a.w_bytes);
+    __syncthreads();
+
+    constexpr int kShare = 64 / KW, kTiles = kShare > 16 ? kShare / 16 : 1, kEach = kShare / kTiles;
+    const auto store = [&](const float (&v)[kShare], int ex) ESCOIN_INLINE {
+        // A lane holds, per 32 positions, 16 output channels of one position: 8*(i/4) + 4*(lane/32) + i%4.
+        const int wp = wave % PW, kg = wave / PW % KW, wm = wave / (PW * KW);
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {
+            const int sub = (kg * kShare + t * kEach) / 16, i0 = (kg * kShare) % 16;  // 32x32 tile of the wave; its first value
+            const int at = room.out_at()[wp * 64 + (sub & 1) * 32 + (lane & 31)];
+            const int m0 = wm * 64 + (sub >> 1) * 32 + 4 * (lane >> 5) + (kEach < 16 ? 2 * i0 : 0);
+            if (at < 0) continue;
+            float* __restrict__ o = a.out + ((size_t)n_first * a.M + mg * TM + m0) * EF + at;
+            const int rows = a.M - mg * TM - m0;  // channels from this lane's first one on
+#pragma unroll
+            for (int i = 0; i < kEach; i += 4) {
+                const i4 e = *(const i4*)(room.row_exp() + m0 + 2 * i);
+                const f4 b = *(const f4*)(room.row_bias() + m0 + 2 * i);
+                f4 y;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    y[k] = ldexpf(v[t * kEach + i + k], -ex - e[k]) + b[k];
+                    if (relu) y[k] = y[k] > 0.0f ? y[k] : 0.0f;
+                }
+                if (2 * i + 4 <= rows) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) o[(size_t)(2 * i + k) * EF] = y[k];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        if (2 * i + k < rows) o[(size_t)(2 * i + k) * EF] = y[k];
+                }
+            }
+        }
+    };
+    {
+        float v[kShare];
+        int ex;
+        const uint64_t any = pass<MW, PW, KW, false>(a, room, in, wr, lane, wave, mg, v, &ex);
+        if (any == 0) {
+            store(v, ex);
+            return;
+        }
+    }
+    // Perhaps an input was past the scale that the first ones asked for: once more with the scale of the largest.
+    uint32_t most = 0;
+    for (int i = tid; i < a.C * a.WR; i += kThreads) {
+        const int c = i / a.WR;
+        const uint32_t src = room.tab()[i - c * a.WR];
+        const uint32_t b = __builtin_amdgcn_raw_buffer_load_b32(in, src == kNowhere ? src : src + (uint32_t)(c * HW) * 4u, 0, 0) & 0x7fffffffu;
+        most = max(most, b < 0x7f800000u ? +b : 0u);
+    }
+    __syncthreads();  // every wave has read the notes
+    if (tid < PW) notes->again[tid] = 0;
+    if (tid == PW) notes->lost = 0;
+    atomicMax(&notes->peak, most);
+    __syncthreads();
+    float v[kShare];
+    int ex, lane2 = lane, wave2 = wave;
+    asm volatile("" : "+v"(lane2));  // what the first pass made of it is not worth keeping for this one
+    const uint64_t any = pass<MW, PW, KW, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
+    store(v, ex);
+    if (any == 0) return;
+    uint64_t lists[PW];
+#pragma unroll
+    for (int run = 0; run < PW; ++run) lists[run] = notes->again[run];
+    __syncthreads();  // those stores before the ones of redo()
+    redo(a, lists, t0, mg * TM, TM, kWaves, wave, lane);
+}
+
+template <int MW, int PW, int KW>
+int start(PairArgs& a, const Dims& d, hipStream_t stream) {
+    constexpr PairShape shape = {MW, PW, KW};
+    static_assert(sizeof(Notes<PW>) <= 64, "");
+    a.n_mgroups = (d.M + 64 * MW - 1) / (64 * MW);
+    a.n_tiles = (int)(((long long)d.N * a.plane + 64 * PW - 1) / (64 * PW));
+    a.WR = pair_window(d, shape);
+    a.groups = (a.WR + 63) / 64;
+    const int lds = pair_lds_bytes(d, shape);
+    if (lds > kPairLdsBytes) return ESCOIN_ERANGE;
+    if (lds > 64 * 1024) {
+        const int rc = allow_dynamic_lds((const void*)sconv_pair_kernel<MW, PW, KW>, lds);
+        if (rc != ESCOIN_OK) return rc;
+    }
+    const unsigned blocks = (unsigned)(((long long)a.n_tiles * a.n_mgroups + 7) / 8 * 8);
+    return launch(sconv_pair_kernel<MW, PW, KW>, dim3(blocks), dim3(64 * MW * PW * KW), (size_t)lds, stream, a);
+}
+
+}  // namespace
+
+int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& s, const char* d_plan, const float* d_in, float* d_out,
+                      const float* d_bias, uint32_t flags, hipStream_t stream) {
+    PairArgs a;
+    const char* const section = d_plan + h.off_pair;
+    a.in = d_in; a.out = d_out; a.bias = d_bias; a.flags = flags;
+    a.w = (const b8*)section;
+    a.w_bytes = (uint32_t)pair_weight_bytes(d);
+    a.exps = (const int32_t*)(section + pair_weight_bytes(d));
+    a.rowptr = (const int32_t*)(d_plan + h.off_nz);
+    a.nz = (const MfmaNz*)(d_plan + h.off_nz + mfma_rowptr_bytes(d));
+    a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad;
+    a.pitch = d.W + d.pad;
+    a.plane = (d.H + d.pad) * a.pitch;
+    a.n_chunks = (int)mfma_chunks(d);
+    const int layout = 100 * s.MW + 10 * s.PW + s.KW;
+    if (layout == 114) return start<1, 1, 4>(a, d, stream);
+    if (layout == 118) return start<1, 1, 8>(a, d, stream);
+    if (layout == 122) return start<1, 2, 2>(a, d, stream);
+    if (layout == 212) return start<2, 1, 2>(a, d, stream);
+    return ESCOIN_EINVAL;
+}
+
+}  // namespace escoin

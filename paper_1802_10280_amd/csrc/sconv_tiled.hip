@@ -31,6 +31,7 @@
 
 #include "common.h"
 #include "mfma.h"
+#include "pair.h"
 #include "plan.h"
 
 namespace escoin {
@@ -641,13 +642,20 @@ static int read_header(const Dims& d, const void* plan_host, PlanHeader* h) {
 
 }  // namespace escoin
 
-extern "C" int escoin_sconv_tiled_on_matrix_cores(const escoin_conv_desc* desc, const void* plan_host) {
+extern "C" int escoin_sconv_tiled_kernel(const escoin_conv_desc* desc, const void* plan_host) {
     using namespace escoin;
     Dims d;
     PlanHeader h;
+    PairShape s;
     int rc = make_dims(desc, &d);
     if (rc == ESCOIN_OK) rc = read_header(d, plan_host, &h);
-    return rc != ESCOIN_OK ? rc : mfma_taken(d, h) ? 1 : 0;
+    if (rc != ESCOIN_OK) return rc;
+    return pair_taken(d, h, &s) ? 100 * s.MW + 10 * s.PW + s.KW : mfma_taken(d, h) ? 1 : 0;
+}
+
+extern "C" int escoin_sconv_tiled_on_matrix_cores(const escoin_conv_desc* desc, const void* plan_host) {
+    const int kernel = escoin_sconv_tiled_kernel(desc, plan_host);
+    return kernel > 0 ? 1 : kernel;
 }
 
 extern "C" int escoin_sconv_forward_tiled(const escoin_conv_desc* desc, const void* plan_host,
@@ -686,6 +694,9 @@ extern "C" int escoin_sconv_forward_tiled(const escoin_conv_desc* desc, const vo
         h.lds_bytes > 160 * 1024)
         return ESCOIN_EINVAL;
 
+    PairShape shape;
+    if (((uintptr_t)d_plan & 15) == 0 && pair_taken(d, h, &shape))
+        return launch_sconv_pair(d, h, shape, (const char*)d_plan, d_in, d_out, d_bias, flags, (hipStream_t)hip_stream);
     if (((uintptr_t)d_plan & 15) == 0 && mfma_taken(d, h))
         return launch_sconv_mfma(d, h, (const char*)d_plan, d_in, d_out, d_bias, flags, (hipStream_t)hip_stream);
 

@@ -68,8 +68,9 @@ class LayerRunner:
 
     def sconv_kernel_name(self):
         if self.path == "tiled":
-            if B.escoin_sconv_tiled_on_matrix_cores(self.desc, self.plan) and self.d_plan.data_ptr() % 16 == 0:
-                return "sconv_mfma_kernel"
+            k = B.escoin_sconv_tiled_kernel(self.desc, self.plan) if self.d_plan.data_ptr() % 16 == 0 else 0
+            if k:
+                return "sconv_mfma_kernel" if k == 1 else f"sconv_pair_kernel<{k // 100}, {k // 10 % 10}, {k % 10}>"
             h = self.plan_info
             vw = h["VW"] if self.d_in.data_ptr() % 16 == 0 else 1
             if vw == 4 and h["n_dma"] > 0 and h["WW"] == 4:

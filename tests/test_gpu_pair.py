@@ -1,0 +1,252 @@
+"""The fp16-pair form of the tiled entry point against the oracle, where its tiling and its scaling can go wrong: channel
+counts off the blocks of 16 and 64, ragged last tiles and rounds, filters three wide and not, inputs and weights of any size."""
+import numpy as np
+import pytest
+
+import paper_1802_10280_amd as esc
+from helpers import DeviceLayer, assert_within_bound, oracle_full
+from paper_1802_10280_amd import workloads as wl
+
+gpu = pytest.mark.gpu
+
+# N, C, H, W, M, R, S, pad, sparsity, workgroup layout
+SHAPES = [
+    (40, 64, 28, 28, 64, 3, 3, 1, 0.75, 122),      # whole blocks of channels
+    (48, 49, 19, 23, 100, 3, 3, 1, 0.70, 212),     # channels over on both sides; a last round of two chunks of which one is a channel
+    (37, 100, 25, 21, 90, 3, 3, 1, 0.70, 212),
+    (20, 64, 56, 56, 64, 3, 3, 1, 0.80, 122),      # taps that reach far: windows of 244
+    (30, 47, 18, 13, 112, 3, 4, 0, 0.60, 118),     # no padding, a filter four wide; three chunks for eight waves
+    (24, 64, 13, 18, 120, 5, 3, 1, 0.65, 118),     # padding smaller than the reach
+    (26, 384, 13, 13, 384, 3, 3, 1, 0.80, 114),    # many rounds
+    (10, 512, 13, 13, 384, 3, 3, 1, 0.50, 118),    # sums long enough to go before three bf16 parts
+    (16, 250, 14, 14, 250, 3, 3, 1, 0.80, 118),
+    (60, 90, 28, 28, 250, 2, 2, 0, 0.60, 212),     # fewer steps a round than staging tasks
+    (30, 100, 27, 31, 180, 3, 3, 1, 0.70, 122),
+]
+SMALL = SHAPES[1]
+
+
+def layer(shape, N=None, seed=91):
+    n, C, H, W, M, R, S, pad, sparsity, _ = shape
+    return wl.custom_layer(N or n, C, H, W, M, R, S, 1, pad, sparsity, seed=seed, dist="normal")
+
+
+def pair_layer(L, layout):
+    dl = DeviceLayer(esc, L)
+    dl.forward_tiled()
+    assert esc.escoin_sconv_tiled_kernel(dl.desc, dl.plan) == layout and dl.d_plan.data_ptr() % 16 == 0
+    return dl
+
+
+def limit(L, bound):
+    """The split and the product left out: 2^-21 of every |w*x| at most.  The matrix cores' sums: as fp32 roundings of
+    every product, of which a random walk's share shows.  Results below the least normal number: half its last bit."""
+    n = L.spec.C * L.spec.R * L.spec.S
+    return (2.0 ** -21 + 2.0 ** -24 * 4 * np.sqrt(n)) * bound + 2.0 ** -149
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_shapes_take_the_pairs(shape):
+    N, C, H, W, M, R, S, pad, sparsity, layout = shape
+    L = layer(shape, N=1)
+    d = esc.make_desc(N, C, H, W, M, R, S, 1, pad)
+    plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+    assert esc.escoin_sconv_tiled_kernel(d, plan) == layout and esc.escoin_sconv_tiled_on_matrix_cores(d, plan)
+    assert esc.escoin_sconv_tiled_kernel(esc.desc_of(L.spec), plan) == 0
+    with pytest.raises(esc.EscoinError):
+        esc.escoin_sconv_tiled_kernel(esc.make_desc(N, C, H, W, M + 1, R, S, 1, pad), plan)
+
+
+def test_pairs_add_up_to_the_csr():
+    for shape in SHAPES:
+        N, C, H, W, M, R, S, pad, sparsity, _ = shape
+        L = layer(shape, N=1)
+        d = esc.make_desc(N, C, H, W, M, R, S, 1, pad)
+        plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+        h = esc.plan_header(plan)
+        blocks, chunks = -(-M // 64) * 2, -(-C // 16)
+        size = (blocks * chunks * R * S + 2) * 2048
+        w = plan[h["off_pair"]:h["off_pair"] + size - 4096].view(np.float16).astype(np.float64)
+        w = w.reshape(blocks, chunks, R * S, 2, 2, 32, 8)
+        w = w[:, :, :, 0] + w[:, :, :, 1] / 2048
+        w = w.transpose(0, 4, 1, 3, 5, 2).reshape(blocks * 32, chunks * 16 * R * S)
+        exps = plan[h["off_pair"] + size:h["off_pair"] + size + 4 * M].view(np.int32)
+        want = np.zeros_like(w)
+        for m in range(M):
+            row = slice(L.rowptr[m], L.rowptr[m + 1])
+            want[m, L.colidx[row]] = L.value[row].astype(np.float64) * 2.0 ** exps[m]
+            assert 2.0 ** 14 <= np.abs(want[m]).max() < 2.0 ** 15
+        assert (np.abs(w - want) <= 2.0 ** -23 * np.abs(want)).all() and not w[M:].any()
+
+
+def test_what_the_pairs_cannot_hold_stays_off_them():
+    """A row that spans 28 binades, a short one, an Inf, a repeated column; explicit zeros are no nonzeros; a row of any size is fine."""
+    L = layer(SMALL, N=1)
+    N, C, H, W, M, R, S, pad, _, _ = SMALL
+    d = esc.make_desc(N, C, H, W, M, R, S, 1, pad)
+    st = esc.escoin_sconv_pack(d, L.rowptr, L.colidx)
+    held = lambda stretched, value: esc.plan_header(esc.escoin_sconv_plan_build(d, L.rowptr, stretched, value))["pair"]
+    assert held(st, L.value) == 1
+    row = slice(L.rowptr[7], L.rowptr[8])
+    most = np.abs(L.value[row]).max()
+    for v, kept in ((most * 2.0 ** -26, 1), (most * 2.0 ** -28, 0), (np.inf, 0), (np.nan, 0)):
+        value = L.value.copy()
+        value[L.rowptr[7] + np.argmin(np.abs(L.value[row]))] = v
+        assert held(st, value) == kept, v
+    for power, kept in ((-100, 1), (100, 1)):
+        value = L.value.copy()
+        value[row] = np.clip(np.abs(value[row]), most / 100, most) * np.float32(2.0 ** power)
+        assert held(st, value) == kept, power
+    for left, kept in ((32, 1), (31, 0)):
+        value = L.value.copy()
+        value[L.rowptr[7] + left:L.rowptr[8]] = 0
+        assert held(st, value) == kept, left
+    twice = st.copy()
+    twice[1] = twice[0]
+    assert held(twice, L.value) == 0
+
+
+@gpu
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_against_the_oracle(oracle, shape):
+    print("pair", shape, flush=True)
+    L = layer(shape)
+    dl = pair_layer(L, shape[-1])
+    for flags in (0, esc.F_BIAS | esc.F_RELU):
+        got = dl.forward_tiled(flags)
+        ref, bound = oracle_full(oracle, L, flags)
+        assert_within_bound(got, ref, bound, (shape, flags))
+        assert (np.abs(got - ref) <= limit(L, bound)).all()
+    # and as exact as the fp32 chain of the tiled kernel, in the mean
+    one = DeviceLayer(esc, L, tuning=dict(B=2))
+    got, chain = dl.forward_tiled(), one.forward_tiled()
+    ref, _ = oracle_full(oracle, L)
+    assert esc.escoin_sconv_tiled_kernel(one.desc, one.plan) == 0
+    assert np.linalg.norm(got - ref) <= np.linalg.norm(chain - ref)
+
+
+@gpu
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[4]], ids=str)
+def test_unaligned_buffers_guards_and_one_plan_for_two_batches(oracle, shape):
+    import torch
+    print("pair unaligned", shape, flush=True)
+    L = layer(shape)
+    dl = pair_layer(L, shape[-1])
+    ref, bound = oracle_full(oracle, L)
+    n_in, n_out, guard = L.input.size, ref.size, 1 << 16
+    room = torch.full((n_in + 4,), float("nan"), device="cuda")
+    d_in = room[1:1 + n_in].copy_(dl.d_in.flatten())
+    out = torch.full((guard + 1 + n_out + guard,), float("nan"), device="cuda")
+    d_out = out[guard + 1:guard + 1 + n_out]
+    assert d_in.data_ptr() % 16 == 4 and d_out.data_ptr() % 16 == 4
+    esc.escoin_sconv_forward_tiled(dl.desc, dl.plan, dl.d_plan, d_in, d_out)
+    assert_within_bound(d_out.cpu().numpy().reshape(ref.shape), ref, bound, shape)
+    assert bool(out[:guard + 1].isnan().all()) and bool(out[guard + 1 + n_out:].isnan().all())
+    s = L.spec
+    one = esc.make_desc(1, s.C, s.H, s.W, s.M, s.R, s.S, 1, s.pad)
+    assert not esc.escoin_sconv_tiled_on_matrix_cores(one, dl.plan)
+    dl.d_out.fill_(float("nan"))
+    esc.escoin_sconv_forward_tiled(one, dl.plan, dl.d_plan, dl.d_in[:1], dl.d_out[:1])
+    assert_within_bound(dl.d_out[:1].cpu().numpy(), ref[:1], bound[:1], shape)
+    assert bool(dl.d_out[1:].isnan().all())
+
+
+@gpu
+@pytest.mark.parametrize("power", [-146, -130, -100, -40, 60, 100, 120])
+def test_inputs_of_any_size(oracle, power):
+    """Everything scaled, down to subnormal inputs; the weights the other way where sums would leave fp32's range."""
+    print("pair input scale", power, flush=True)
+    L = layer(SMALL, seed=92)
+    L.input *= np.float32(2.0) ** np.float32(power / 2)
+    L.input *= np.float32(2.0) ** np.float32(power - power / 2)
+    L.value *= np.float32(2.0 ** (-20 if power > 0 else 20))
+    dl = pair_layer(L, SMALL[-1])
+    got = dl.forward_tiled()
+    ref, bound = oracle_full(oracle, L)
+    assert np.abs(ref).max() > 0 and (np.abs(got - ref) <= limit(L, bound)).all()
+
+
+@gpu
+@pytest.mark.parametrize("late, early", [(2.0 ** 10, 1.0), (2.0 ** 60, 1.0), (1.0, 2.0 ** 40), (1.0, 0.0), (2.0 ** -60, 0.0), (2.0 ** 90, 2.0 ** -60)])
+def test_channels_of_different_sizes(oracle, late, early):
+    """The scale is taken from the first channels: later ones are far larger or smaller, beside zeros, in some images."""
+    print("pair channel sizes", late, early, flush=True)
+    L = layer(SHAPES[2], seed=93)
+    L.input[::3, :40] *= np.float32(early)
+    L.input[::3, 40:] *= np.float32(late)
+    dl = pair_layer(L, SHAPES[2][-1])
+    for flags in (0, esc.F_BIAS):
+        got = dl.forward_tiled(flags)
+        ref, bound = oracle_full(oracle, L, flags)
+        assert (np.abs(got - ref) <= limit(L, bound)).all()
+
+
+@gpu
+def test_small_values_beside_large_ones(oracle):
+    """Outputs that meet only inputs 2^-40 to 2^-120 of others in their window, or zeros."""
+    print("pair small beside large", flush=True)
+    L = layer(SMALL, seed=94)
+    rng = np.random.default_rng(94)
+    L.input[:] *= np.float32(2.0) ** rng.integers(-120, -40, size=(L.spec.N, 1, 1, 1)).astype(np.float32)
+    L.input[:, :, 5, 7] = 1.0
+    L.input[3] = 0
+    dl = pair_layer(L, SMALL[-1])
+    got = dl.forward_tiled()
+    ref, bound = oracle_full(oracle, L)
+    assert (np.abs(got - ref) <= limit(L, bound)).all() and not got[3].any()
+
+
+@gpu
+def test_results_around_the_largest_float(oracle):
+    print("pair overflow", flush=True)
+    L = layer(SMALL, seed=95)
+    L.input[:] = 0
+    for image, x in ((3, 3e38), (9, 1e38), (32, -3e38)):
+        L.input[image, image, 5, 6] = x
+    L.value *= np.float32(40)
+    with np.errstate(over="ignore"):
+        ref, bound = oracle_full(oracle, L)
+        ref = ref.astype(np.float32).astype(np.float64)
+    got = pair_layer(L, SMALL[-1]).forward_tiled()
+    over = np.isinf(ref)
+    assert over.any() and (got[over] == ref[over]).all()
+    assert (np.abs(got[~over] - ref[~over]) <= limit(L, bound)[~over]).all()
+
+
+@gpu
+@pytest.mark.parametrize("where", ["a word", "a row", "a column", "an image", "every image"])
+def test_non_finite_inputs_reach_only_nonzero_weights(oracle, where):
+    print("pair non-finite", where, flush=True)
+    L = layer(SMALL, seed=96)
+    place = {"a word": np.s_[2, 0, 0, 0], "a row": np.s_[3, 7, 4], "a column": np.s_[32, 7, :, 16], "an image": np.s_[20, 11],
+             "every image": np.s_[:, 48]}
+    L.input[place[where]] = np.inf
+    L.input[1, 0, 0, 0] = np.nan
+    L.input[5, 48, 18, 22] = 3.4e38
+    dl = pair_layer(L, SMALL[-1])
+    for flags in (0, esc.F_BIAS | esc.F_RELU):
+        got = dl.forward_tiled(flags)
+        with np.errstate(invalid="ignore", over="ignore"):
+            ref, bound = oracle_full(oracle, L, flags)
+        bad = ~np.isfinite(bound)            # an output that met one; ReLU may have made it finite
+        assert bad.any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
+        assert (np.abs(got[~bad] - ref[~bad]) <= 1e-4 * bound[~bad]).all()
+
+
+@gpu
+def test_captured_calls_replay(oracle):
+    """One launch, no memset: replays give the same bits as eager calls, with eager work between them."""
+    import torch
+    print("pair capture", flush=True)
+    L = layer(SMALL, seed=97)
+    dl = pair_layer(L, SMALL[-1])
+    want = torch.from_numpy(dl.forward_tiled()).cuda()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        esc.escoin_sconv_forward_tiled(dl.desc, dl.plan, dl.d_plan, dl.d_in, dl.d_out, stream=torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        dl.d_out.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dl.d_out, want)
+        assert bool((dl.d_out * 2).isfinite().all())
