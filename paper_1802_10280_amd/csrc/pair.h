@@ -16,10 +16,14 @@ struct PairShape {
     int MW, PW, KW;
 };
 
+// The flat padded map whose positions are numbered through the batch, the padding between rows and images shared: columns a
+// row, positions an image, and how far the taps reach.
+inline int pair_pitch(const Dims& d) { return d.W + d.pad; }
+inline long long pair_plane(const Dims& d) { return (long long)(d.H + d.pad) * pair_pitch(d); }
+inline long long pair_reach(const Dims& d) { return (long long)(d.R - 1) * pair_pitch(d) + d.S - 1; }
+
 // window positions a channel takes in LDS
-inline int pair_window(const Dims& d, const PairShape& s) {
-    return (64 * s.PW + (d.R - 1) * (d.W + d.pad) + d.S - 1 + 3) / 4 * 4;
-}
+inline int pair_window(const Dims& d, const PairShape& s) { return (int)((64 * s.PW + pair_reach(d) + 3) / 4 * 4); }
 // LDS: notes, the channels' exponents and biases, the positions' outputs and the window's words (head); then one
 // window buffer, or two where there is more than one round of channels; the waves' sums meet in the same place.
 inline int pair_head_bytes(const PairShape& s) { return 64 + 8 * 64 * s.MW + 4 * 64 * s.PW; }
@@ -34,7 +38,7 @@ inline uint64_t pair_weight_bytes(const Dims& d) {
 }
 inline uint64_t pair_bytes(const Dims& d) { return pair_weight_bytes(d) + mfma_rowptr_bytes(d); }  // with the rows' exponents
 
-bool pair_planned(const Dims& d, long long nnz, int WS);
+bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h);
 bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape);
 bool pair_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out);
 int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& shape, const char* d_plan, const float* d_in, float* d_out,

@@ -18,37 +18,45 @@ constexpr double kLeastJobs = 64;
 
 // Microseconds that a batch of N images takes in one of the layouts.  A workgroup takes 12000 clocks to begin and to
 // end (17000 in a launch of several rounds of them) and, with another one beside it or not, 900 a step (1180 with eight
-// waves) and 250 a staging task, where filters are three wide; with others 1400 and, staged without overlap, 2500.  The last workgroups to run count for more than their share.  2 GHz,
+// waves) and 250 a staging task, where filters are three wide; with others 1150 a step and, for
+// a round, staged without overlap, 2700 and 750 a task.  The last workgroups to run count for more than their share.  2 GHz,
 // as measured over launches of this length.  That is 157, 33, 31, 26 and 96 us where 162, 37, 33, 30 and 100 were measured (28x28
 // with 256 channels, 56x56 with 64, 7x7 with 512, 14x14 with 256, 13x13 with 384) and 18, 10 and 12 where 19, 11 and 12
 // were (13 of 15x15 with 240, one of 41x44 with 24, 5 of 7x7 with 69).
 static double pair_time(const Dims& d, double N, const PairShape& s) {
     const int waves = s.MW * s.PW * s.KW, lds = pair_lds_bytes(d, s), RS = d.R * d.S;
     if (lds > kPairLdsBytes) return INFINITY;
-    const double jobs = ceil(N * (d.H + d.pad) * (d.W + d.pad) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW));
+    const double jobs = ceil(N * (double)pair_plane(d) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW));
     if (jobs < kLeastJobs) return INFINITY;
     const double slots = waves == 4 && 2 * lds <= kPairLdsBytes ? 512 : 256;
     const int chunks = (int)mfma_chunks(d), rounds = (chunks + s.KW - 1) / s.KW;
     const double steps = ceil((double)chunks * RS / s.KW), tasks = ceil(2.0 * s.KW * ((pair_window(d, s) + 63) / 64) / waves);
-    double job = (jobs > slots ? 17000 : 12000) + steps * (d.S != 3 ? 1400 : waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * (d.S == 3 ? 250 : 2500);
+    double job = jobs > slots ? 17000 : 12000;
+    if (d.S == 3) job += steps * (waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * 250;
+    else job += steps * 1150 + (rounds - 1) * (2700 + tasks * 750);
     const double full = floor(jobs / slots), rest = jobs / slots - full;
     return 2.0 + std::max(1.0, full + (rest > 0 ? 0.5 + 0.5 * rest : 0.0)) * job / 2000.0;
 }
 
-// The tiled kernel's, at its better: 8 us and 36 TFLOP/s on the nonzeros.
-static double tiled_time(const Dims& d, double N, long long nnz) { return 8.0 + 2e-6 * (double)nnz * N * d.E * d.F / 36.0; }
+// The tiled kernel's, from its tiling: rounds of workgroups over 8 x 32 compute units; a workgroup's 4 us and half a us a chunk, and the
+// LDS reads of its records, 4.6 clocks of 2.1 GHz for each position run and half of that for the record itself.  That is 48, 48, 56,
+// 58, 188 and 107 us where 48, 47, 55, 59, 177 and 111 were measured (56x56 with 64 channels, 28x28 with 128, 14x14 with 256, 7x7 with 512,
+// 28x28 with 256 at 90 and 95 %), 11 and 12 where 11 and 15 were (16 channels, 5x5; 192 channels, 1x1).
+static double tiled_time(const Dims& d, double N, const PlanHeader& h) {
+    const double jobs = (double)h.n_tiles * ceil(N / h.NB) * h.n_mgroups * h.CS;
+    const double job = 4.0 + 0.5 * h.n_chunks / h.CS + (double)h.n_records / h.n_mgroups / h.CS * h.WQ * (h.Q + 0.5) * 4.6 / 2100.0;
+    return ceil(ceil(jobs / 8) / 32) * job;
+}
 
-// How much faster it has to look: the tiled kernel beats its estimate by up to a seventh on small layers (32x16x28x28, 5x5:
-// 11.2 us, put at 13.4).
+// How much faster it has to look, as the estimates are off by a tenth now and then.
 constexpr double kMargin = 0.9;
 
 // The shapes the kernel takes.
 static bool pair_takes(const Dims& d) {
     if (d.stride != 1 || d.R <= d.pad || d.S <= d.pad || d.C < 16 || d.M < 32) return false;
-    const long long pitch = d.W + d.pad, plane = (d.H + d.pad) * pitch;
-    if ((d.R - 1) * pitch + d.S - 1 > kPairReach || pair_weight_bytes(d) > (64ull << 20)) return false;
+    if (pair_reach(d) > kPairReach || pair_weight_bytes(d) > (64ull << 20)) return false;
     // positions, and the offsets inside the images that a workgroup's window may touch, in 32 bits
-    const long long images = (128 + kPairReach) / plane + 2;
+    const long long plane = pair_plane(d), images = (128 + kPairReach) / plane + 2;
     return plane < (1 << 21) && images * d.C * d.H * d.W * 4 < (1ll << 31) && images * d.M * d.E * d.F < (1ll << 31);
 }
 
@@ -62,25 +70,27 @@ static double pair_error(double n, const PairShape& s) { return 0.81 + n * (s.KW
 static double tiled_error(double n, int WS) { return 0.0154 * n / WS; }
 static double mfma_error(double n) { return 0.00195 * n; }
 
-// Whether a plan, whose tiled form splits rows over WS waves, carries the section: a layer that some batch is faster with,
-// and no less exact.
-bool pair_planned(const Dims& d, long long nnz, int WS) {
-    const double n = (double)nnz / d.M, N = 64.0 * 8192 / ((double)(d.H + d.pad) * (d.W + d.pad));
+// Whether a plan with this tiled form carries the section: a layer that some batch is faster with, and no less exact.
+bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h) {
+    const double n = (double)nnz / d.M;
     if (!pair_takes(d)) return false;
     for (const PairShape& s : kShapes)
-        if (pair_error(n, s) < 0.95 * tiled_error(n, WS) && pair_time(d, N, s) < kMargin * tiled_time(d, N, nnz)) return true;
+        for (double positions = 8192; pair_error(n, s) < 0.95 * tiled_error(n, h.WS) && positions <= 8192 * 64; positions *= 4) {
+            const double N = ceil(positions / (double)pair_plane(d));
+            if (pair_time(d, N, s) < kMargin * tiled_time(d, N, h)) return true;
+        }
     return false;
 }
 
 // Whether a forward call on this batch takes the section of a plan made for this layer, and in which layout: one that is
 // faster and no less exact than the kernel the call would take else.
 bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
-    if (h.pair != 1 || !pair_planned(d, h.pair_nnz, h.WS)) return false;
-    const long long total = (long long)d.N * (d.H + d.pad) * (d.W + d.pad);
+    if (h.pair != 1 || !pair_planned(d, h.pair_nnz, h)) return false;
+    const long long total = (long long)d.N * pair_plane(d);
     if (total > (1ll << 30) || total / 64 * (long long)mfma_row_blocks(d) > (1ll << 30)) return false;
     const bool bf16 = mfma_taken(d, h);
     const double n = (double)h.pair_nnz / d.M, error = bf16 ? mfma_error(n) : 0.95 * tiled_error(n, h.WS);
-    double best = kMargin * (bf16 ? mfma_time(d, d.N) : tiled_time(d, d.N, h.pair_nnz));
+    double best = kMargin * (bf16 ? mfma_time(d, d.N) : tiled_time(d, d.N, h));
     bool taken = false;
     for (const PairShape& s : kShapes) {
         if (pair_error(n, s) > error) continue;

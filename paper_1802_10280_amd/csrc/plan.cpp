@@ -688,17 +688,21 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
     off = align_up64(off + 64, 256);
     // A plan whose tiling the caller fixed is for the tiled kernel alone.
     const bool with_mfma = !tuned && mfma_planned(d, rowptr[d.M]);
-    h.mfma = h.mfma_nnz = 0;
+    bool with_pair = !tuned && pair_planned(d, rowptr[d.M], h);
+    h.mfma = h.mfma_nnz = h.pair = h.pair_nnz = 0;
     h.off_mfma = off;
-    // the split weights and, behind the first of the two kinds, the nonzeros
-    const bool with_pair = !tuned && pair_planned(d, rowptr[d.M], h.WS);
-    if (with_mfma) off += mfma_weight_bytes(d);
-    else if (with_pair) off += pair_bytes(d);
-    h.off_nz = off;
-    if (with_mfma || with_pair) off = align_up64(off + nz_bytes(d, rowptr[d.M]), 256);
-    h.pair = h.pair_nnz = 0;
-    h.off_pair = with_mfma ? off : h.off_mfma;
-    if (with_mfma && with_pair) off = align_up64(off + pair_bytes(d), 256);
+    for (;; with_pair = false) {
+        // the split weights and, behind the first of the two kinds, the nonzeros
+        off = h.off_mfma;
+        if (with_mfma) off += mfma_weight_bytes(d);
+        else if (with_pair) off += pair_bytes(d);
+        h.off_nz = off;
+        if (with_mfma || with_pair) off = align_up64(off + nz_bytes(d, rowptr[d.M]), 256);
+        h.off_pair = with_mfma ? off : h.off_mfma;
+        if (with_mfma && with_pair) off = align_up64(off + pair_bytes(d), 256);
+        // (the size query has no values: with explicit zeros it may have seen another tiling, and asked for less)
+        if (!out || off <= out_bytes || !with_pair) break;
+    }
     h.total_bytes = off;
     *bytes = (size_t)off;
     if (!out) return ESCOIN_OK;
@@ -788,7 +792,7 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
     }
     // room is made by the stored entries (the size query has no values); explicit zeros cost the tiled
     // kernel nothing, so whether the section is worth having is asked again without them
-    const bool mfma = with_mfma && mfma_planned(d, nnz_total), pair = with_pair && pair_planned(d, nnz_total, h.WS);
+    const bool mfma = with_mfma && mfma_planned(d, nnz_total), pair = with_pair && pair_planned(d, nnz_total, h);
     if ((mfma || pair) && nz_write(d, rowptr, stretched, value, base + h.off_nz)) {
         const int32_t* rp = (const int32_t*)(base + h.off_nz);
         const MfmaNz* nz = (const MfmaNz*)(base + h.off_nz + mfma_rowptr_bytes(d));

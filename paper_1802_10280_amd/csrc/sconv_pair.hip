@@ -197,6 +197,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     // Every round but the last gives each wave RS steps, so none is empty before the last; there, a wave without
     // steps only helps with the staging.
     Task ta, tb, tc;
+    const bool three_ahead = a.S != 3;  // of the next round's tasks; filters three wide ask for them on the way
     {
         Task t[8];
 #pragma unroll
@@ -246,6 +247,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     if (n_rounds > 1) {
         fetch(ta, 1);
         fetch(tb, 1);
+        if (three_ahead) fetch(tc, 1);
     }
 #pragma unroll
     for (int p = 0; p < 2; ++p)
@@ -390,10 +392,11 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
             }
         }
         if (more) {
-            // the one or two tasks left over have been asked for (all of them have not, where a round has few steps)
+            // the tasks left over: two or three of them have been asked for
             if (task < my_tasks) commit(ta, buf ^ 1);
             if (task + 1 < my_tasks) commit(tb, buf ^ 1);
-            for (task += 2; task < my_tasks; ++task) {
+            if (three_ahead && 2 < my_tasks) commit(tc, buf ^ 1);
+            for (task += three_ahead ? 3 : 2; task < my_tasks; ++task) {
                 locate(ta, task);
                 fetch(ta, round + 1);
                 commit(ta, buf ^ 1);
@@ -404,6 +407,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
             if (round + 2 < n_rounds) {
                 fetch(ta, round + 2);
                 fetch(tb, round + 2);
+                if (three_ahead) fetch(tc, round + 2);
             }
         }
         __syncthreads();
@@ -613,8 +617,8 @@ int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& s, co
     a.rowptr = (const int32_t*)(d_plan + h.off_nz);
     a.nz = (const MfmaNz*)(d_plan + h.off_nz + mfma_rowptr_bytes(d));
     a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad;
-    a.pitch = d.W + d.pad;
-    a.plane = (d.H + d.pad) * a.pitch;
+    a.pitch = pair_pitch(d);
+    a.plane = (int)pair_plane(d);
     a.n_chunks = (int)mfma_chunks(d);
     const int layout = 100 * s.MW + 10 * s.PW + s.KW;
     if (layout == 114) return start<1, 1, 4>(a, d, stream);
