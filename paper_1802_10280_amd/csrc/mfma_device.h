@@ -24,19 +24,20 @@ struct MfmaArgs {
 
 constexpr float kTinyInput = 0x1p-70f, kTinySum = 0x1p-58f;
 
-// An output's place: row and column of its first tap, and that tap's word in the input's channel 0.
+// An output's place: row and column of its first tap, and that tap's word in channel 0, counted from the first image
+// that the workgroup touches (an offset from the batch's start would need 64 bits).
 struct Place {
     int y, x, first;
 };
 
 // Every step-th nonzero from `j` on, for T positions of a lane.  Eight loads (sixteen for four positions) at a
 // time and no branches, so that they are on their way together: past the end the last nonzero is read again,
-// beside the image the input's first word, and neither counts.  Words: the nonzeros as MfmaNz is laid out; in the
+// beside the image the first word of `input`, and neither counts.  Words: the nonzeros as MfmaNz is laid out; in the
 // constant address space, where `j` is the same for the whole wave, they come through scalar loads.
 template <int T, class Words>
-__device__ inline void walk(const MfmaArgs& a, Words nz, int j, int end, int step, const Place (&at)[T], float (&v)[T]) {
+__device__ inline void walk(const MfmaArgs& a, const float* input, Words nz, int j, int end, int step, const Place (&at)[T], float (&v)[T]) {
     constexpr int kBatch = T == 1 ? 8 : 4;
-    const uint32_t* __restrict__ in = (const uint32_t*)a.in;
+    const uint32_t* __restrict__ in = (const uint32_t*)input;
     for (; j < end; j += kBatch * step) {
         uint32_t c[kBatch], rs[kBatch], w[kBatch], keep[kBatch][T], x[kBatch][T];
 #pragma unroll
@@ -77,7 +78,8 @@ static_assert(sizeof(MfmaNz) == 12, "walk() reads three words a nonzero");
 template <int RUNS>
 __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], int t0, int m0, int rows, int waves, int wave, int lane) {
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
-    const int EF = a.E * a.F, HW = a.H * a.W;
+    const int EF = a.E * a.F, HW = a.H * a.W, n_first = t0 / a.plane;
+    const float* const in = a.in + (size_t)n_first * a.C * HW;
     const auto shared_nz = (const __attribute__((address_space(4))) uint32_t*)a.nz;
     int total = 0;
 #pragma unroll
@@ -90,7 +92,7 @@ __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], in
     };
     const auto place = [&](int u) -> Place {
         const int n = u / a.plane, rem = u - n * a.plane, y = rem / a.pitch - a.pad, x = rem % a.pitch - a.pad;
-        return {y, x, n * a.C * HW + y * a.W + x};
+        return {y, x, (n - n_first) * a.C * HW + y * a.W + x};
     };
     // More than half of them: a lane takes its position of every run at once, and a nonzero is read for all
     // (run by run those two last calls took 4.3 and 12.5 ms).
@@ -104,7 +106,7 @@ __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], in
         for (int k = wave; k < rows && m0 + k < a.M; k += waves) {
             const int m = m0 + k;
             float v[RUNS] = {};
-            walk(a, shared_nz, __builtin_amdgcn_readfirstlane(a.rowptr[m]), __builtin_amdgcn_readfirstlane(a.rowptr[m + 1]), 1, at, v);
+            walk(a, in, shared_nz, __builtin_amdgcn_readfirstlane(a.rowptr[m]), __builtin_amdgcn_readfirstlane(a.rowptr[m + 1]), 1, at, v);
 #pragma unroll
             for (int run = 0; run < RUNS; ++run)
                 if (lists[run] >> lane & 1) store(v[run], m, t0 + run * 64 + lane);
@@ -125,8 +127,8 @@ __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], in
         for (int k = wave; k < rows && m0 + k < a.M; k += waves) {
             const int m = m0 + k, begin = __builtin_amdgcn_readfirstlane(a.rowptr[m]), end = __builtin_amdgcn_readfirstlane(a.rowptr[m + 1]);
             float v[1] = {};
-            if (step == 1) walk(a, shared_nz, begin, end, 1, at, v);
-            else walk(a, (const uint32_t*)a.nz, begin + part, end, step, at, v);
+            if (step == 1) walk(a, in, shared_nz, begin, end, 1, at, v);
+            else walk(a, in, (const uint32_t*)a.nz, begin + part, end, step, at, v);
             for (int s = 1; s < step; s <<= 1) v[0] += __shfl_xor(v[0], s);
             if (active && part == 0) store(v[0], m, u);
         }
