@@ -38,6 +38,41 @@ inline uint64_t pair_weight_bytes(const Dims& d) {
 }
 inline uint64_t pair_bytes(const Dims& d) { return pair_weight_bytes(d) + mfma_rowptr_bytes(d); }  // with the rows' exponents
 
+// Where a wave's weights are, and where the next step's: a step is one tap of 16 input channels, a round's steps (chunk by chunk, tap
+// by tap) are shared evenly by its KW waves, whole chunks where every wave has one.  A wave asks for two steps more than it
+// has; those lie behind its last ones, never past the section.
+#define ESCOIN_HD __host__ __device__ inline __attribute__((always_inline))
+struct PairWalk {
+    int KW, RS, n_chunks, n_rounds, block_bytes;  // block: 32 output channels
+    int last_skip, last_more;                     // of the last round, which need not be whole
+    int round, at, left;                          // at: byte offset of the first of the wave's two blocks
+
+    ESCOIN_HD static int least(int a, int b) { return a < b ? a : b; }
+    ESCOIN_HD int first_step(int r, int k) const { return least(KW, n_chunks - r * KW) * RS * k / KW; }
+    // The first block of a wave: `mg` of the workgroups over the channels, wave `wm` of its MW; M: output channels.  A wave
+    // past the last channel, of a workgroup that reaches over it, multiplies the last two blocks as well and stores nothing.
+    ESCOIN_HD static int row_block(int mg, int MW, int wm, int M) { return least(mg * MW + wm, (M - 1) / 64) * 2; }
+    ESCOIN_HD PairWalk(int kw, int rs, int chunks, int row_blk, int kg)
+        : KW(kw), RS(rs), n_chunks(chunks), n_rounds((chunks + kw - 1) / kw), block_bytes(chunks * rs * kPairStepBytes) {
+        const int regular_at = ((n_rounds - 1) * KW + kg) * RS * kPairStepBytes;  // of the last round, were it a whole one
+        const int last_begin = first_step(n_rounds - 1, kg);
+        last_skip = ((n_rounds - 1) * KW * RS + last_begin) * kPairStepBytes - regular_at;
+        // three more than the last round has: what is asked for beyond its end does not turn to another round
+        last_more = first_step(n_rounds - 1, kg + 1) - last_begin - RS + 3;
+        const int only = n_rounds == 1 ? 1 : 0;
+        round = 0;
+        at = row_blk * block_bytes + kg * RS * kPairStepBytes + only * last_skip;
+        left = RS + only * last_more;
+    }
+    ESCOIN_HD void next() {
+        const int turn = --left <= 0 ? 1 : 0;
+        round += turn;
+        const int last = round >= n_rounds - 1 ? turn : 0;
+        at += kPairStepBytes + turn * (KW - 1) * RS * kPairStepBytes + last * last_skip;
+        left += turn * RS + last * last_more;
+    }
+};
+
 bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h);
 bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape);
 bool pair_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out);

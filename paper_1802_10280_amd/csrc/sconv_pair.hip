@@ -113,9 +113,9 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     const uint32_t* const tab = room.tab();
     Notes<PW>* const notes = room.notes();
     const int HW4 = a.H * a.W * 4, last_channel = (a.C - 1) * HW4, RS = a.R * a.S;
-    const int n_rounds = (a.n_chunks + KW - 1) / KW;
-    // a round's steps (chunk, tap) are shared evenly: whole chunks where every wave has one
-    auto first_step = [&](int round, int k) ESCOIN_INLINE { return min(KW, a.n_chunks - round * KW) * RS * k / KW; };
+    // What the steps ask for runs two steps ahead of them, through the rounds.
+    PairWalk ask(KW, RS, a.n_chunks, PairWalk::row_block(mg, MW, wm, a.M), kg);
+    const int n_rounds = ask.n_rounds;
 
     // ---- staging: a task is one 8-channel half of a chunk and 64 window positions (the last 64 overlap the ones
     // before); one past the last stands for the last, so that every wave has the same number of them.  Channels past
@@ -167,31 +167,15 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
 
     f16v big[2][2], small[2][2];
     struct Weights { u4 p[2][2]; } w0, w1, w2;
-    const int row_blk = (mg * MW + wm) * 2;
-    const int blk_bytes = a.n_chunks * RS * kStepBytes;
-    // What the steps ask for runs two steps ahead of them, through the rounds.
-    const int regular_at = ((n_rounds - 1) * KW + kg) * RS * kStepBytes;  // of the last round, were it a whole one
-    const int last_begin = first_step(n_rounds - 1, kg);
-    const int last_skip = ((n_rounds - 1) * KW * RS + last_begin) * kStepBytes - regular_at;
-    const int last_more = first_step(n_rounds - 1, kg + 1) - last_begin - RS;
-    const int only = n_rounds == 1 ? 1 : 0;
-    int pf_round = 0, pf_at = row_blk * blk_bytes + kg * RS * kStepBytes + only * last_skip, pf_left = RS + only * last_more;
     auto weights = [&](Weights& o, int k, int p, int further = 0) ESCOIN_INLINE {
-        o.p[p][k] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16 + k * 1024 + further, p ? pf_at + blk_bytes : pf_at, 0);
-    };
-    auto weights_next = [&]() ESCOIN_INLINE {
-        const int turn = --pf_left <= 0 ? 1 : 0;
-        pf_round += turn;
-        const int last = pf_round >= n_rounds - 1 ? turn : 0;
-        pf_at += kStepBytes + turn * (KW - 1) * RS * kStepBytes + last * last_skip;
-        pf_left += turn * RS + last * last_more;
+        o.p[p][k] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16 + k * 1024 + further, p ? ask.at + ask.block_bytes : ask.at, 0);
     };
     auto all_weights = [&](Weights& o) ESCOIN_INLINE {
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int p = 0; p < 2; ++p) weights(o, k, p);
-        weights_next();
+        ask.next();
     };
 
     // Every round but the last gives each wave RS steps, so none is empty before the last; there, a wave without
@@ -257,7 +241,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     for (int round = 0; round < n_rounds; ++round) {
         const bool more = round + 1 < n_rounds;
         const int buf = round & 1;
-        const int begin = first_step(round, kg), end = first_step(round, kg + 1);
+        const int begin = ask.first_step(round, kg), end = ask.first_step(round, kg + 1);
         int sub = begin / RS, tap = begin - sub * RS, r = tap / a.S, s = tap - r * a.S;
         const char* row = win + buf * buf_bytes + sub * sub_bytes + ((lane >> 5) * WR + wp * 64 + (lane & 31) + r * a.pitch + s) * 16;
         h8 xh0, xh1;
@@ -296,7 +280,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
             weights(cn, 1, 0);
             ESCOIN_MFMA(small, 1, xh, 1, 1)
             weights(cn, 1, 1);
-            weights_next();
+            ask.next();
             xh0 = read(0, 0);  // the next step's; after the last one what lies behind is read and not used
             xh1 = read(0, 1);
             __builtin_amdgcn_sched_barrier(0);  // a task is not looked at before this
@@ -353,11 +337,11 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
             const char* const next_row = row + (++r == a.R ? sub_bytes - (a.R - 1) * a.pitch * 16 : a.pitch * 16);
             if (r == a.R) r = 0;
             ESCOIN_STEP(0, w0, w2, 0, ta, tc, row + 16)
-            weights_next();
+            ask.next();
             ESCOIN_STEP(1, w1, w0, 0, tb, ta, row + 32)
             ESCOIN_STEP(2, w2, w1, kStepBytes, tc, tb, next_row)
-            pf_at += 2 * kStepBytes;
-            pf_left -= 2;
+            ask.at += 2 * kStepBytes;
+            ask.left -= 2;
             row = next_row;
             i += 3;
 #undef ESCOIN_STEP
@@ -583,7 +567,9 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
 #pragma unroll
     for (int run = 0; run < PW; ++run) lists[run] = notes->again[run];
     __syncthreads();  // those stores before the ones of redo()
-    redo(a, lists, t0, mg * TM, TM, kWaves, wave, lane);
+    int start = t0;
+    asm volatile("" : "+s"(start));  // nor what the beginning made of this
+    redo(a, lists, start, mg * TM, TM, kWaves, wave, lane);
 }
 
 template <int MW, int PW, int KW>

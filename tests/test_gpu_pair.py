@@ -22,6 +22,8 @@ SHAPES = [
     (16, 250, 14, 14, 250, 3, 3, 1, 0.80, 118),
     (60, 90, 28, 28, 250, 2, 2, 0, 0.60, 212),     # fewer steps a round than staging tasks
     (30, 100, 27, 31, 180, 3, 3, 1, 0.70, 122),
+    (20, 196, 20, 20, 284, 3, 3, 1, 0.75, 212),   # 64 channels more than whole workgroups: a wave of the last ones has none
+    (16, 192, 28, 28, 192, 3, 3, 1, 0.80, 212),    # ... and no remainder
 ]
 SMALL = SHAPES[1]
 
