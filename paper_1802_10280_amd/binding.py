@@ -230,7 +230,9 @@ class _PlanHeader(ctypes.Structure):
                     "CS", "pitch1", "VW", "WW", "WS", "CC0", "zero_floats", "max_regions", "MB", "n_dma")]
                 + [("off_dma", ctypes.c_uint64), ("off_zero", ctypes.c_uint64),
                    ("mfma", ctypes.c_int32), ("mfma_nnz", ctypes.c_int32), ("off_mfma", ctypes.c_uint64),
-                   ("pair", ctypes.c_int32), ("pair_nnz", ctypes.c_int32), ("off_pair", ctypes.c_uint64), ("off_nz", ctypes.c_uint64)])
+                   ("pair", ctypes.c_int32), ("pair_nnz", ctypes.c_int32), ("off_pair", ctypes.c_uint64), ("off_nz", ctypes.c_uint64),
+                   ("pair_least", ctypes.c_int32), ("pair_few2", ctypes.c_int32), ("pair_few4", ctypes.c_int32),
+                   ("pair_few8", ctypes.c_int32)])
 
 
 def plan_header(plan: np.ndarray) -> dict:

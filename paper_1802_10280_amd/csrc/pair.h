@@ -11,10 +11,13 @@ constexpr int kPairReach = 127;            // taps reach at most so many window 
 constexpr int kPairStepBytes = 2048;       // of 32 channels' weights for one tap of 16 input channels: two parts of 1024
 constexpr int kPairLdsBytes = 160 * 1024;
 
-// How a workgroup's waves are laid out: over 64 output channels each, 64 positions each, 16 input channels each.
+// How a workgroup's waves are laid out: over 64 output channels each, 64 positions each, 16 input channels each.  Channels with
+// fewer than `few` nonzeros are computed from those.
 struct PairShape {
-    int MW, PW, KW;
+    int MW, PW, KW, few = 0;
 };
+constexpr int kFewBatch = 16;              // that many of their nonzeros at a time
+constexpr int kFewChains = 4;              // in so many chains of sums
 
 // The flat padded map whose positions are numbered through the batch, the padding between rows and images shared: columns a
 // row, positions an image, and how far the taps reach.
@@ -75,6 +78,7 @@ struct PairWalk {
 
 bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h);
 bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape);
+void pair_note_rows(const Dims& d, const int32_t* rp, PlanHeader* h);
 bool pair_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out);
 int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& shape, const char* d_plan, const float* d_in, float* d_out,
                       const float* d_bias, uint32_t flags, hipStream_t stream);

@@ -23,7 +23,9 @@ constexpr double kLeastJobs = 64;
 // as measured over launches of this length.  That is 157, 33, 31, 26 and 96 us where 162, 37, 33, 30 and 100 were measured (28x28
 // with 256 channels, 56x56 with 64, 7x7 with 512, 14x14 with 256, 13x13 with 384) and 18, 10 and 12 where 19, 11 and 12
 // were (13 of 15x15 with 240, one of 41x44 with 24, 5 of 7x7 with 69).
-static double pair_time(const Dims& d, double N, const PairShape& s) {
+//
+// `few`: batches of nonzeros of all short rows.  A batch takes a wave 1600 clocks for 64 positions (the L1, shared by all of them).
+static double pair_time(const Dims& d, double N, const PairShape& s, double few = 0) {
     const int waves = s.MW * s.PW * s.KW, lds = pair_lds_bytes(d, s), RS = d.R * d.S;
     if (lds > kPairLdsBytes) return INFINITY;
     const double jobs = ceil(N * (double)pair_plane(d) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW));
@@ -34,6 +36,7 @@ static double pair_time(const Dims& d, double N, const PairShape& s) {
     double job = jobs > slots ? 17000 : 12000;
     if (d.S == 3) job += steps * (waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * 250;
     else job += steps * 1150 + (rounds - 1) * (2700 + tasks * 750);
+    job += few / ceil(d.M / (64.0 * s.MW)) / waves * s.PW * 1600;
     const double full = floor(jobs / slots), rest = jobs / slots - full;
     return 2.0 + std::max(1.0, full + (rest > 0 ? 0.5 + 0.5 * rest : 0.0)) * job / 2000.0;
 }
@@ -63,41 +66,69 @@ static bool pair_takes(const Dims& d) {
 // Relative errors against 64 bits, squared, times 1e14 (2-norm; n nonzeros a row, activations half zeros).  Two fp16
 // numbers hold 22 to 23 bits: with the product left out that makes 0.9e-7 whatever n is; the sums add to it, the less the more
 // waves share them.  The tiled kernel's chains of fp32 roundings are n / WS long, the kernel of three bf16 parts
-// rounds once per 16 channels.  Measured and (in brackets) by these, in 1e-7: pairs in two shares, n = 115: 1.15 (1.15), 461: 1.70
-// (1.68); in four, 461: 1.32 (1.32); in eight, 922: 1.37 (1.37), 1152: 1.39 (1.46).  Tiled, 115: 1.37 (1.33), 461: 2.64 (2.66).
-// bf16, 691: 1.16 (1.16), 1210: 1.55 (1.54).
-static double pair_error(double n, const PairShape& s) { return 0.81 + n * (s.KW == 2 ? 0.0044 : s.KW == 4 ? 0.0020 : 0.00116); }
-static double tiled_error(double n, int WS) { return 0.0154 * n / WS; }
-static double mfma_error(double n) { return 0.00195 * n; }
+// rounds once per 16 channels.  Measured and (in brackets) by these, in 1e-7: pairs in two shares, n = 115: 1.12 (1.15), 460: 1.75
+// (1.68); in four, 60: 0.97 (0.96), 460: 1.37 (1.32); in eight, 60: 0.99 (0.99), 920: 1.39 (1.37), 1210: 1.47 (1.48).  Tiled,
+// 60: 0.99 (0.96), 115: 1.36 (1.33), 460: 2.64 (2.66).  bf16, 691: 1.16 (1.16), 1210: 1.54 (1.54).
+static double pair_base(const PairShape& s) { return s.KW == 8 ? 0.92 : 0.81; }
+static double pair_slope(const PairShape& s) { return s.KW == 2 ? 0.0044 : s.KW == 4 ? 0.0020 : 0.00105; }
+static double tiled_slope(int WS) { return 0.0154 / WS; }
+constexpr double kTiledRowSlope = 0.0163, kMfmaSlope = 0.00195;  // the first: a row of 36 to 90 nonzeros, WS = 1
+static double pair_error(double n, const PairShape& s) { return pair_base(s) + pair_slope(s) * n; }
+
+// A row of fewer nonzeros is less exact as pairs than in a kernel of that slope.
+static int least_row(const PairShape& s, double slope) {
+    const double gain = slope - pair_slope(s);
+    return (int)std::min(ceil(pair_base(s) / std::max(gain, 1e-9)), 1e9);
+}
 
 // Whether a plan with this tiled form carries the section: a layer that some batch is faster with, and no less exact.
 bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h) {
     const double n = (double)nnz / d.M;
     if (!pair_takes(d)) return false;
     for (const PairShape& s : kShapes)
-        for (double positions = 8192; pair_error(n, s) < 0.95 * tiled_error(n, h.WS) && positions <= 8192 * 64; positions *= 4) {
+        for (double positions = 8192; pair_error(n, s) < 0.95 * tiled_slope(h.WS) * n && positions <= 8192 * 64; positions *= 4) {
             const double N = ceil(positions / (double)pair_plane(d));
             if (pair_time(d, N, s) < kMargin * tiled_time(d, N, h)) return true;
         }
     return false;
 }
 
+// Notes of the rows what pair_taken() asks.
+void pair_note_rows(const Dims& d, const int32_t* rp, PlanHeader* h) {
+    h->pair_least = INT32_MAX;
+    for (int m = 0; m < d.M; ++m) h->pair_least = std::min(h->pair_least, rp[m + 1] - rp[m]);
+    for (const PairShape& s : kShapes) {
+        const int least = least_row(s, kTiledRowSlope / h->WS);
+        long long batches = 0;
+        for (int m = 0; m < d.M; ++m)
+            if (rp[m + 1] - rp[m] < least) batches += (rp[m + 1] - rp[m] + kFewBatch - 1) / kFewBatch;
+        (s.KW == 2 ? h->pair_few2 : s.KW == 4 ? h->pair_few4 : h->pair_few8) = (int32_t)batches;
+    }
+}
+
 // Whether a forward call on this batch takes the section of a plan made for this layer, and in which layout: one that is
-// faster and no less exact than the kernel the call would take else.
+// faster and no less exact than the kernel the call would take else, row by row.  Rows too short for the pairs are computed from their
+// nonzeros in kFewChains chains, so where the tiled kernel has no more than those.  (Which kernel that is goes with the batch, and
+// so does whether the pairs are exact enough: the results of a layer may change in their last bits from batch to batch, but
+// no call's are less exact than without the pairs.)
 bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
-    if (h.pair != 1 || !pair_planned(d, h.pair_nnz, h)) return false;
+    if (h.pair != 1 || h.pair_least <= 0 || !pair_planned(d, h.pair_nnz, h)) return false;
     const long long total = (long long)d.N * pair_plane(d);
     if (total > (1ll << 30) || total / 64 * (long long)mfma_row_blocks(d) > (1ll << 30)) return false;
     const bool bf16 = mfma_taken(d, h);
-    const double n = (double)h.pair_nnz / d.M, error = bf16 ? mfma_error(n) : 0.95 * tiled_error(n, h.WS);
+    const double n = (double)h.pair_nnz / d.M, slope = bf16 ? kMfmaSlope : tiled_slope(h.WS);
     double best = kMargin * (bf16 ? mfma_time(d, d.N) : tiled_time(d, d.N, h));
     bool taken = false;
     for (const PairShape& s : kShapes) {
-        if (pair_error(n, s) > error) continue;
-        const double t = pair_time(d, d.N, s);
+        if (pair_error(n, s) > (bf16 ? 1.0 : 0.95) * slope * n) continue;
+        const int least = least_row(s, bf16 ? kMfmaSlope : kTiledRowSlope / h.WS);
+        const bool few = h.pair_least < least;
+        if (few && (bf16 || h.WS > kFewChains)) continue;
+        const double t = pair_time(d, d.N, s, !few ? 0 : s.KW == 2 ? h.pair_few2 : s.KW == 4 ? h.pair_few4 : h.pair_few8);
         if (t < best) {
             best = t;
             *shape = s;
+            shape->few = few ? least : 0;
             taken = true;
         }
     }

@@ -689,7 +689,7 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
     // A plan whose tiling the caller fixed is for the tiled kernel alone.
     const bool with_mfma = !tuned && mfma_planned(d, rowptr[d.M]);
     bool with_pair = !tuned && pair_planned(d, rowptr[d.M], h);
-    h.mfma = h.mfma_nnz = h.pair = h.pair_nnz = 0;
+    h.mfma = h.mfma_nnz = h.pair = h.pair_nnz = h.pair_least = h.pair_few2 = h.pair_few4 = h.pair_few8 = 0;
     h.off_mfma = off;
     for (;; with_pair = false) {
         // the split weights and, behind the first of the two kinds, the nonzeros
@@ -799,7 +799,10 @@ int build_plan_once(const Dims& d, const int32_t* rowptr, const int32_t* stretch
         h.mfma = mfma && mfma_write(d, rp, nz, base + h.off_mfma) ? 1 : 0;
         if (h.mfma) h.mfma_nnz = (int32_t)nnz_total;
         h.pair = pair && pair_write(d, rp, nz, base + h.off_pair) ? 1 : 0;
-        if (h.pair) h.pair_nnz = (int32_t)nnz_total;
+        if (h.pair) {
+            h.pair_nnz = (int32_t)nnz_total;
+            pair_note_rows(d, rp, &h);
+        }
     }
     std::memcpy(base, &h, sizeof(h));  // the header once more, now with WW, n_dma, mfma and pair
     std::memcpy(base + h.off_lanes, lanes.data(), lanes.size() * sizeof(LaneSlot));

@@ -108,6 +108,10 @@ struct PlanHeader {
     int32_t pair_nnz;    // nonzero values in that section
     uint64_t off_pair;   // weights, row exponents
     uint64_t off_nz;     // row pointers, nonzeros, for both sections
+    int32_t pair_least;  // least nonzero values of a row; 0 in plans from before rows were looked at, whose pairs
+                         // are not taken
+    int32_t pair_few2, pair_few4, pair_few8;  // batches of nonzeros in rows too short for the layouts of 2, 4
+                         // and 8 shares of the input channels
 };
 static_assert(sizeof(PlanHeader) <= 512, "the sections start 512 bytes into the blob");
 

@@ -56,6 +56,7 @@ struct PairArgs : MfmaArgs {
     int WR;          // window positions a channel takes in LDS
     int groups;      // of 64 window positions
     uint32_t w_bytes;
+    int few;         // channels with fewer nonzeros are computed from those
 };
 
 #define ESCOIN_INLINE __attribute__((always_inline))
@@ -454,6 +455,67 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     return any;
 }
 
+// The channels that are too short for pairs to be as exact as fp32 sums, from their nonzeros in fp32; the waves take them in turn.  A
+// position's word for a tap stands in the window's table, so that a nonzero costs an LDS read, a load and a multiply-add; kFewBatch of
+// them are in flight at once, and the L1 bounds it (some 1600 clocks a batch of a wave, with all of them at it).  64x256x28x28, 80 %,
+// rows of 55 to 2304 nonzeros: 185 us, with the short rows as pairs 150 and 1 to 2 % less exact than the tiled kernel, which takes 317.
+template <int MW, int PW, int KW>
+__device__ inline void few_rows(const PairArgs& a, const Room<MW, PW> room, Rsrc in, int lane, int wave, int mg, int t0) {
+    constexpr int kWaves = MW * PW * KW, TM = 64 * MW;
+    const int EF = a.E * a.F, HW4 = a.H * a.W * 4, n_first = t0 / a.plane;
+    const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
+    const uint32_t* const tab = room.tab() + lane;
+    int turn = 0;
+    for (int m0 = mg * TM; m0 < min((mg + 1) * TM, a.M); m0 += 64) {
+        int begin = 0, end = 0;
+        if (m0 + lane < a.M) {
+            begin = a.rowptr[m0 + lane];
+            end = a.rowptr[m0 + lane + 1];
+        }
+        for (uint64_t list = __ballot(m0 + lane < a.M && end - begin < a.few); list != 0; list &= list - 1) {
+            if (turn++ % kWaves != wave) continue;
+            const int k = __ffsll((unsigned long long)list) - 1, m = m0 + k;
+            const int last = __builtin_amdgcn_readlane(end, k);
+            float v[PW][kFewChains] = {};
+            for (int j = __builtin_amdgcn_readlane(begin, k); j < last; j += 64) {
+                const int here = min(last - j, 64);
+                const uint32_t* const p = (const uint32_t*)a.nz + 3 * (j + min(lane, here - 1));  // a nonzero a lane
+                const uint32_t rs = p[1];
+                const int channel = (int)p[0] * HW4, reach = (int)((rs & 0xffffu) * a.pitch + (rs >> 16));
+                const int w = lane < here ? (int)p[2] : 0;
+                for (int i = 0; i < here; i += kFewBatch) {
+                    uint32_t src[kFewBatch][PW];
+                    float x[kFewBatch][PW];
+#pragma unroll
+                    for (int b = 0; b < kFewBatch; ++b)
+#pragma unroll
+                        for (int run = 0; run < PW; ++run) src[b][run] = tab[__builtin_amdgcn_readlane(reach, i + b) + 64 * run];
+#pragma unroll
+                    for (int b = 0; b < kFewBatch; ++b)
+#pragma unroll
+                        for (int run = 0; run < PW; ++run)  // past the end zeros meet
+                            x[b][run] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in, i + b < here ? src[b][run] : kNowhere,
+                                                                                             __builtin_amdgcn_readlane(channel, i + b), 0));
+                    __builtin_amdgcn_sched_barrier(0);  // all on their way before the first is waited for
+#pragma unroll
+                    for (int b = 0; b < kFewBatch; ++b)
+#pragma unroll
+                        for (int run = 0; run < PW; ++run)
+                            v[run][b % kFewChains] = fmaf(__int_as_float(__builtin_amdgcn_readlane(w, i + b)), x[b][run], v[run][b % kFewChains]);
+                }
+            }
+#pragma unroll
+            for (int run = 0; run < PW; ++run) {
+                const int at = room.out_at()[64 * run + lane];
+                float y = (v[run][0] + v[run][1]) + (v[run][2] + v[run][3]);
+                y += has_bias ? a.bias[m] : 0.0f;
+                if (relu) y = y > 0.0f ? y : 0.0f;
+                if (at >= 0) a.out[((size_t)n_first * a.M + m) * EF + at] = y;
+            }
+        }
+    }
+}
+
 // MW, PW: waves over channels and positions, 64 each; KW: over the input channels, 16 each a round.
 template <int MW, int PW, int KW>
 __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const PairArgs a) {
@@ -541,6 +603,10 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
         const uint64_t any = pass<MW, PW, KW, false>(a, room, in, wr, lane, wave, mg, v, &ex);
         if (any == 0) {
             store(v, ex);
+            if (a.few != 0) {
+                __syncthreads();  // those stores before the ones of few_rows()
+                few_rows<MW, PW, KW>(a, room, in, lane, wave, mg, t0);
+            }
             return;
         }
     }
@@ -562,14 +628,19 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     asm volatile("" : "+v"(lane2));  // what the first pass made of it is not worth keeping for this one
     const uint64_t any = pass<MW, PW, KW, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
     store(v, ex);
-    if (any == 0) return;
-    uint64_t lists[PW];
-#pragma unroll
-    for (int run = 0; run < PW; ++run) lists[run] = notes->again[run];
-    __syncthreads();  // those stores before the ones of redo()
     int start = t0;
     asm volatile("" : "+s"(start));  // nor what the beginning made of this
-    redo(a, lists, start, mg * TM, TM, kWaves, wave, lane);
+    if (any != 0) {
+        uint64_t lists[PW];
+#pragma unroll
+        for (int run = 0; run < PW; ++run) lists[run] = notes->again[run];
+        __syncthreads();  // those stores before the ones of redo()
+        redo(a, lists, start, mg * TM, TM, kWaves, wave, lane);
+    }
+    if (a.few != 0) {
+        __syncthreads();  // and these
+        few_rows<MW, PW, KW>(a, room, in, lane, wave, mg, start);
+    }
 }
 
 template <int MW, int PW, int KW>
@@ -606,6 +677,7 @@ int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& s, co
     a.pitch = pair_pitch(d);
     a.plane = (int)pair_plane(d);
     a.n_chunks = (int)mfma_chunks(d);
+    a.few = s.few;
     const int layout = 100 * s.MW + 10 * s.PW + s.KW;
     if (layout == 114) return start<1, 1, 4>(a, d, stream);
     if (layout == 118) return start<1, 1, 8>(a, d, stream);

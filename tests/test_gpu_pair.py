@@ -108,6 +108,72 @@ def test_what_the_pairs_cannot_hold_stays_off_them():
     assert held(twice, L.value) == 0
 
 
+# Layers of which some rows are cut to so many nonzeros: too few for pairs to be as exact as fp32 sums, about the batches of 16
+# that those are computed in; the last layer's chains are split over two waves, so that the line lies higher.
+SHORT = [SHAPES[2], SHAPES[5], SHAPES[6], SHAPES[10], (44, 272, 10, 10, 64, 3, 3, 1, 0.50, 118)]
+
+
+def short_layer(shape, N=None):
+    """The layer, and which of its rows were cut."""
+    L = layer(shape, N=N, seed=99)
+    M, rows = L.spec.M, np.diff(L.rowptr)
+    lengths = [32, 33, 47, 48, 49, 56] if shape[1] != 272 else [33, 63, 64, 65, 100, 128]
+    cut = np.unique(np.linspace(0, M - 1, 6).astype(int))
+    rows[cut] = lengths
+    keep = np.concatenate([np.arange(b - a) < k for a, b, k in zip(L.rowptr, L.rowptr[1:], rows)])
+    L.colidx, L.value = L.colidx[keep], L.value[keep]
+    L.rowptr = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    return L, cut
+
+
+def plan_of(L, N):
+    s = L.spec
+    d = esc.make_desc(N, s.C, s.H, s.W, s.M, s.R, s.S, 1, s.pad)
+    return d, esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+
+
+@pytest.mark.parametrize("shape", SHORT, ids=str)
+def test_short_rows_are_known(shape):
+    """What the plan says of them: the least, and the batches of those below each layout's line."""
+    L, cut = short_layer(shape, N=1)
+    d, plan = plan_of(L, shape[0])
+    h = esc.plan_header(plan)
+    n, WS = np.diff(L.rowptr), h["WS"]
+    assert h["pair"] == 1 and h["pair_least"] == n.min() and esc.escoin_sconv_tiled_kernel(d, plan) > 1
+    for KW, base, slope in ((2, 0.81, 0.0044), (4, 0.81, 0.0020), (8, 0.92, 0.00105)):
+        line = base / (0.0163 / WS - slope)
+        assert h[f"pair_few{KW}"] == sum(-(-int(k) // 16) for k in n if k < line), KW
+        assert (n[cut] < line).all()
+
+
+def test_short_rows_before_three_bf16_parts():
+    """Beside the kernel of three bf16 parts, which is the more exact below 1023 nonzeros, a layer with a shorter row stays off the pairs."""
+    shape = SHAPES[7]
+    L = layer(shape, N=1)
+    for left, kernel in ((1023, 118), (1022, 1)):
+        L.value[L.rowptr[7] + left:L.rowptr[8]] = 0
+        d, plan = plan_of(L, 32)
+        assert esc.plan_header(plan)["pair_least"] == left and esc.escoin_sconv_tiled_kernel(d, plan) == kernel
+
+
+def test_plans_saved_before_keep_off_the_pairs():
+    """A plan whose header does not tell of pairs, or of its shortest row, is for the other kernels."""
+    for fields in (("pair", "pair_nnz", "off_pair", "off_nz", "pair_least"), ("pair_least",)):
+        for shape, N, without in ((SHAPES[1], 48, 0), (SHAPES[7], 32, 1)):
+            L = layer(shape, N=1)
+            d, plan = plan_of(L, N)
+            assert esc.escoin_sconv_tiled_kernel(d, plan) == shape[-1]
+            forget(plan, fields)
+            assert esc.escoin_sconv_tiled_kernel(d, plan) == without
+
+
+def forget(plan, fields):
+    from paper_1802_10280_amd.binding import _PlanHeader
+    for f in fields:
+        at = getattr(_PlanHeader, f)
+        plan[at.offset:at.offset + at.size] = 0
+
+
 @gpu
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_against_the_oracle(oracle, shape):
@@ -285,3 +351,41 @@ def test_outputs_from_the_nonzeros_past_four_giga_words(oracle):
     bad = ~np.isfinite(bound)
     assert bad.any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
     assert (np.abs(got[~bad] - ref[~bad]) <= 1e-4 * bound[~bad]).all()
+
+
+@gpu
+@pytest.mark.parametrize("shape", SHORT, ids=str)
+def test_short_rows_are_as_exact_as_fp32_sums(oracle, shape):
+    print("pair short rows", shape, flush=True)
+    L, cut = short_layer(shape)
+    L.input[1, 3, 2, 4] = np.inf                   # the window's other outputs, and its second pass
+    L.input[2, :, 5] *= np.float32(2.0 ** 12)
+    dl, one = DeviceLayer(esc, L), DeviceLayer(esc, L, tuning=dict(B=2))
+    for flags in (0, esc.F_BIAS | esc.F_RELU):
+        got, chain = dl.forward_tiled(flags), one.forward_tiled(flags)
+        assert esc.escoin_sconv_tiled_kernel(dl.desc, dl.plan) > 1 and esc.escoin_sconv_tiled_kernel(one.desc, one.plan) == 0
+        with np.errstate(invalid="ignore", over="ignore"):
+            ref, bound = oracle_full(oracle, L, flags)
+        bad = ~np.isfinite(bound)
+        assert bad.any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
+        assert (np.abs(got[~bad] - ref[~bad]) <= limit(L, bound)[~bad]).all()
+        # four chains of a row's products, their sum and the bias: n / 4 + 5 roundings; as a whole no further off than one chain
+        n = np.diff(L.rowptr)[cut]
+        ok = ~bad[:, cut]
+        err, roundings = np.abs(got[:, cut][ok] - ref[:, cut][ok]), np.broadcast_to((n / 4 + 5)[:, None, None], ok.shape)[ok]
+        assert (err <= roundings * 2.0 ** -24 * bound[:, cut][ok] + 2.0 ** -149).all()
+        if flags == 0:
+            assert np.linalg.norm(err) <= np.linalg.norm(chain[:, cut][ok] - ref[:, cut][ok])
+
+
+@gpu
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[7]], ids=str)
+def test_plans_saved_before_give_the_same_layer(oracle, shape):
+    print("pair old plan", shape, flush=True)
+    L = layer(shape)
+    dl = pair_layer(L, shape[-1])
+    ref, bound = oracle_full(oracle, L)
+    forget(dl.plan, ("pair", "pair_nnz", "off_pair", "off_nz", "pair_least"))
+    dl.d_plan = to_dev(dl.plan)
+    assert esc.escoin_sconv_tiled_kernel(dl.desc, dl.plan) < 2
+    assert_within_bound(dl.forward_tiled(), ref, bound, shape)
