@@ -5,7 +5,8 @@
 // sconv_mfma.hip.  There an operand is three bf16 parts and a product six matrix instructions, here two fp16
 // parts and three:
 //   x = h + l / 2^11,  h = fp16(x), l = fp16((x - h) * 2^11),   x*w = hh + (hl + lh) / 2^11.
-// h and l hold 22 bits and l's sign; l is scaled so that its exponent ends where h's does.  The product left out and the bits
+// (A published method: Ootomo and Yokota, "Recovering single precision accuracy from Tensor Cores while surpassing the FP32
+// theoretical peak performance", 2022.)  h and l hold 22 bits and l's sign; l is scaled so that its exponent ends where h's does.  The product left out and the bits
 // lost make a product uncertain by 2^-21 at most, 0.7e-7 in the mean: more than one fp32 rounding, less than a chain of
 // some fifty.  hh has an accumulator of its own, and the channels are shared by several waves, whose sums meet at the end: the
 // shorter chains are more exact (the rule in pair_plan.cpp weighs the forms' errors).
@@ -21,10 +22,12 @@
 // too slowly to keep a matrix core busy (a tap took 1100 clocks where what lies around its instructions was in one
 // place): the rest of a step is strung out between them and, for filters three wide, a row of taps is one block without
 // address arithmetic.  Staging the next chunks goes along in the same way.
-// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312); 64x384x13x13, 384 filters, 65 %: 118 (three
-// bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy a third to a half of
-// the time (76 us of the first one's, at 2.4 GHz); the rest is the workgroups' beginnings and ends, 12000-17000 clocks each, which only
-// the other workgroup of a compute unit hides, and the first two rounds, when all of them ask for their inputs at once.
+// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312); 64x384x13x13, 384 filters, 65 %: 119 (three
+// bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy half of the time in the first
+// one (76 us at 2.4 GHz) and a third where eight waves share the channels (counters, first call after others); the rest is the workgroups'
+// beginnings and ends, 12000-17000 clocks each, which only the other workgroup of a compute unit hides (there is none beside eight
+// waves), and the first two rounds, when all of them ask for their inputs at once.  Scalar and, in three layouts, a few vector
+// registers are spilled, outside the loops over the steps.
 #include <float.h>
 #include <algorithm>
 
@@ -211,7 +214,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
         }
         __syncthreads();
         const uint32_t peak = __builtin_amdgcn_readfirstlane(notes->peak);
-        // 2^7 of room above the first ones, where the second pass knows the largest
+        // 2^6 of room above the first ones, where the second pass knows the largest
         ex = (peak ? 127 - (int)(peak >> 23) : 0) + (AGAIN ? 14 : 9);
         low = (uint32_t)max(0, 127 - 13 - ex) << 24;
 #pragma unroll

@@ -167,6 +167,21 @@ def test_plans_saved_before_keep_off_the_pairs():
             assert esc.escoin_sconv_tiled_kernel(d, plan) == without
 
 
+def test_no_batch_is_less_exact_than_without_the_pairs():
+    """Which kernel the pairs stand in for goes with the batch; in place of three bf16 parts only eight shares of rows long enough do."""
+    L = layer((1, 256, 28, 28, 256, 3, 3, 1, 0.78, 0))
+    _, plan = plan_of(L, 64)
+    old = plan.copy()
+    forget(old, ("pair_least",))
+    seen = set()
+    for N in range(1, 129):
+        d = esc.make_desc(N, 256, 28, 28, 256, 3, 3, 1, 1)
+        taken, without = esc.escoin_sconv_tiled_kernel(d, plan), esc.escoin_sconv_tiled_kernel(d, old)
+        assert without in (0, 1) and (taken == without or without == 0)
+        seen.add((taken > 1, without))
+    assert seen == {(False, 0), (True, 0), (False, 1)}
+
+
 def forget(plan, fields):
     from paper_1802_10280_amd.binding import _PlanHeader
     for f in fields:
@@ -389,3 +404,28 @@ def test_plans_saved_before_give_the_same_layer(oracle, shape):
     dl.d_plan = to_dev(dl.plan)
     assert esc.escoin_sconv_tiled_kernel(dl.desc, dl.plan) < 2
     assert_within_bound(dl.forward_tiled(), ref, bound, shape)
+
+
+@gpu
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[5], SHAPES[6], SHAPES[10]], ids=str)
+def test_outputs_of_few_products(oracle, shape):
+    """Sparse inputs: an output of k products is off by 2^-21 of each at most, and by a rounding of the sum for each of them and of the
+    waves' shares; where the input is a power of two, by the weight's own pair alone, 2^-23 of it."""
+    print("pair few products", shape, flush=True)
+    L = layer(shape, seed=100)
+    N, C, H, W = L.input.shape
+    rng = np.random.default_rng(100)
+    L.input *= rng.random(L.input.shape) < 0.01
+    L.input[0] = L.input[1] = 0
+    for y in range(1, H, 5):  # one input in reach of any output
+        for x in range(1, W, 5):
+            L.input[0, rng.integers(C), y, x] = 1.0
+            L.input[1, rng.integers(C), y, x] = -2.0 ** rng.integers(0, 8)
+    got = pair_layer(L, shape[-1]).forward_tiled().astype(np.float64)
+    ref, bound = oracle_full(oracle, L)
+    s = L.spec
+    kept = oracle.csr_to_dense(s.M, s.C, s.R, s.S, L.rowptr, L.colidx, (L.value != 0).astype(np.float32))
+    k, _ = oracle.conv((L.input != 0).astype(np.float32), kept, s.stride, s.pad)
+    one = k[:2] <= 1
+    assert one.mean() > 0.9 and (np.abs(got - ref)[:2] <= 2.0 ** -23 * bound[:2])[one].all() and not got[k == 0].any()
+    assert (np.abs(got - ref) <= (2.0 ** -21 + 2.0 ** -24 * (k + shape[-1] % 10)) * bound).all()
