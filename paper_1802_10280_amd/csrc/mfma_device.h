@@ -73,8 +73,9 @@ static_assert(sizeof(MfmaNz) == 12, "walk() reads three words a nonzero");
 // The marked positions once more from the nonzeros, for the channels m0 .. m0 + rows - 1 of a workgroup whose
 // `waves` waves share the channels.  `lists`: which of the RUNS * 64 positions from t0 on.
 // Bound by the gathers' latency where few workgroups come here and by their address arithmetic where all
-// do.  64x256x28x28 at 50 %, when each lane redid its own outputs -> now: one NaN in the batch 6.4 -> 0.5 ms,
-// one image of them 11.6 -> 2.3, nothing else 32 -> 7.0 (the tiled kernel takes 0.72 whatever the input).
+// do.  64x256x28x28 at 50 % in three bf16 parts, when each lane redid its own outputs -> now: one NaN in the batch 6.4 -> 0.5 ms,
+// one image of them 11.6 -> 2.3, nothing else 32 -> 7.0 (the tiled kernel takes 0.72 whatever the input).  Pairs, whose
+// workgroups have 64 positions, not 256, to a nonzero: 0.26, 2.3 and 16.0 (0.25 without any); two by 64 channels, at 80 %: 0.30, 1.6 and 6.4 (0.18).
 template <int RUNS>
 __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], int t0, int m0, int rows, int waves, int wave, int lane) {
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;

@@ -22,7 +22,7 @@
 // too slowly to keep a matrix core busy (a tap took 1100 clocks where what lies around its instructions was in one
 // place): the rest of a step is strung out between them and, for filters three wide, a row of taps is one block without
 // address arithmetic.  Staging the next chunks goes along in the same way.
-// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312); 64x384x13x13, 384 filters, 65 %: 119 (three
+// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312), at 50 % 219-240 (323); 64x384x13x13, 384 filters, 65 %: 109-119 (three
 // bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy half of the time in the first
 // one (76 us at 2.4 GHz) and a third where eight waves share the channels (counters, first call after others); the rest is the workgroups'
 // beginnings and ends, 12000-17000 clocks each, which only the other workgroup of a compute unit hides (there is none beside eight
