@@ -24,10 +24,9 @@ constexpr double kLeastJobs = 64;
 // with 256 channels, 56x56 with 64, 7x7 with 512, 14x14 with 256, 13x13 with 384) and 18, 10 and 12 where 19, 11 and 12
 // were (13 of 15x15 with 240, one of 41x44 with 24, 5 of 7x7 with 69).
 //
-// `few`: batches of nonzeros of all short rows.  A batch takes a wave 1600 clocks for 64 positions (the L1, shared by all of them); counted
-// as 2500, since a whole row falls to one wave.  With 1600, 25 random layers of uneven rows took 0.43 to 1.05 of the tiled kernel's time (57 of
-// 10x12, 97 -> 166 channels, 234 batches: 45.0 us, 42.6); with 2500 that one stays there, and 51 others take 0.42 to 0.95, one 1.11 (26
-// of 25x25, 34 -> 51, 5x5: 31.0 without its short rows, 35.0 with them, 30.5 tiled).
+// `few`: batches of nonzeros of all short rows.  A batch takes a wave 1200 clocks for 64 positions, with all of them at it; counted as 1900, since
+// a whole row falls to one wave.  105 random layers of uneven rows that take the pairs by this need 0.39 to 0.96 of the tiled kernel's time, one
+// 1.09 (26 of 25x25, 34 -> 51 channels, 5x5: 22.4 us and 31.3, but 34.0 for inputs that send one workgroup through its second pass).
 static double pair_time(const Dims& d, double N, const PairShape& s, double few = 0) {
     const int waves = s.MW * s.PW * s.KW, lds = pair_lds_bytes(d, s), RS = d.R * d.S;
     if (lds > kPairLdsBytes) return INFINITY;
@@ -39,7 +38,7 @@ static double pair_time(const Dims& d, double N, const PairShape& s, double few 
     double job = jobs > slots ? 17000 : 12000;
     if (d.S == 3) job += steps * (waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * 250;
     else job += steps * 1150 + (rounds - 1) * (2700 + tasks * 750);
-    job += few / ceil(d.M / (64.0 * s.MW)) / waves * s.PW * 2500;
+    job += few / ceil(d.M / (64.0 * s.MW)) / waves * s.PW * 1900;
     const double full = floor(jobs / slots), rest = jobs / slots - full;
     return 2.0 + std::max(1.0, full + (rest > 0 ? 0.5 + 0.5 * rest : 0.0)) * job / 2000.0;
 }

@@ -458,16 +458,24 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     return any;
 }
 
+// Behind the window's table, in the dead window: a run of positions that read as zero.
+template <int PW, class R>
+__device__ inline void nowhere_past_the_table(const R& room, int lane, int wave) {
+    if (wave < PW) room.tab()[room.WR + 64 * wave + lane] = kNowhere;
+}
+
 // The channels that are too short for pairs to be as exact as fp32 sums, from their nonzeros in fp32; the waves take them in turn.  A
 // position's word for a tap stands in the window's table, so that a nonzero costs an LDS read, a load and a multiply-add; kFewBatch of
-// them are in flight at once, and the L1 bounds it (some 1600 clocks a batch of a wave, with all of them at it).  64x256x28x28, 80 %,
-// rows of 55 to 2304 nonzeros: 185 us, with the short rows as pairs 150 and 1 to 2 % less exact than the tiled kernel, which takes 317.
+// them are in flight at once, a batch of a wave takes some 1200 clocks with all of them at it.  Bound by its instructions and the L1: with a test for
+// the row's end and a lane number worked out for every nonzero a batch took 1600 (3x107x59x59, 388 channels, 170 batches: 77 -> 65 us, 41 without
+// any), a batch fetched while the last one is summed made it no faster.  64x256x28x28, 80 %, rows of 55 to 2304 nonzeros: 184 us, with
+// the short rows as pairs 148 and 1 to 2 % less exact than the tiled kernel, which takes 314.
 template <int MW, int PW, int KW>
 __device__ inline void few_rows(const PairArgs& a, const Room<MW, PW> room, Rsrc in, int lane, int wave, int mg, int t0) {
     constexpr int kWaves = MW * PW * KW, TM = 64 * MW;
     const int EF = a.E * a.F, HW4 = a.H * a.W * 4, n_first = t0 / a.plane;
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
-    const uint32_t* const tab = room.tab() + lane;
+    const char* const tab = (const char*)(room.tab() + lane);
     int turn = 0;
     for (int m0 = mg * TM; m0 < min((mg + 1) * TM, a.M); m0 += 64) {
         int begin = 0, end = 0;
@@ -483,22 +491,26 @@ __device__ inline void few_rows(const PairArgs& a, const Room<MW, PW> room, Rsrc
             for (int j = __builtin_amdgcn_readlane(begin, k); j < last; j += 64) {
                 const int here = min(last - j, 64);
                 const uint32_t* const p = (const uint32_t*)a.nz + 3 * (j + min(lane, here - 1));  // a nonzero a lane
-                const uint32_t rs = p[1];
-                const int channel = (int)p[0] * HW4, reach = (int)((rs & 0xffffu) * a.pitch + (rs >> 16));
-                const int w = lane < here ? (int)p[2] : 0;
-                for (int i = 0; i < here; i += kFewBatch) {
+                const uint32_t c = p[0], rs = p[1], value = p[2];
+                const bool there = lane < here;  // past the end zeros meet
+                const uint32_t reach = there ? ((rs & 0xffffu) * a.pitch + (rs >> 16)) * 4u : 4u * a.WR;
+                const int channel = there ? (int)c * HW4 : 0, w = there ? (int)value : 0;
+#pragma unroll
+                for (int i = 0; i < 64; i += kFewBatch) {  // lane numbers are constants, which saves an instruction each
+                    if (i >= here) break;
                     uint32_t src[kFewBatch][PW];
                     float x[kFewBatch][PW];
 #pragma unroll
+                    for (int b = 0; b < kFewBatch; ++b) {
+                        const char* const t = tab + __builtin_amdgcn_readlane(reach, i + b);
+#pragma unroll
+                        for (int run = 0; run < PW; ++run) src[b][run] = *(const uint32_t*)(t + 256 * run);
+                    }
+#pragma unroll
                     for (int b = 0; b < kFewBatch; ++b)
 #pragma unroll
-                        for (int run = 0; run < PW; ++run) src[b][run] = tab[__builtin_amdgcn_readlane(reach, i + b) + 64 * run];
-#pragma unroll
-                    for (int b = 0; b < kFewBatch; ++b)
-#pragma unroll
-                        for (int run = 0; run < PW; ++run)  // past the end zeros meet
-                            x[b][run] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in, i + b < here ? src[b][run] : kNowhere,
-                                                                                             __builtin_amdgcn_readlane(channel, i + b), 0));
+                        for (int run = 0; run < PW; ++run)
+                            x[b][run] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in, src[b][run], __builtin_amdgcn_readlane(channel, i + b), 0));
                     __builtin_amdgcn_sched_barrier(0);  // all on their way before the first is waited for
 #pragma unroll
                     for (int b = 0; b < kFewBatch; ++b)
@@ -607,7 +619,8 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
         if (any == 0) {
             store(v, ex);
             if (a.few != 0) {
-                __syncthreads();  // those stores before the ones of few_rows()
+                nowhere_past_the_table<PW>(room, lane, wave);
+                __syncthreads();  // and those stores before the ones of few_rows()
                 few_rows<MW, PW, KW>(a, room, in, lane, wave, mg, t0);
             }
             return;
@@ -641,6 +654,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
         redo(a, lists, start, mg * TM, TM, kWaves, wave, lane);
     }
     if (a.few != 0) {
+        nowhere_past_the_table<PW>(room, lane, wave);
         __syncthreads();  // and these
         few_rows<MW, PW, KW>(a, room, in, lane, wave, mg, start);
     }

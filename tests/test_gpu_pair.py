@@ -148,8 +148,8 @@ def test_short_rows_are_known(shape):
 
 @pytest.mark.parametrize("cut, kernel", [(8, 114), (32, 114), (47, 0)])
 def test_many_short_rows_stay_with_the_tiled_kernel(cut, kernel):
-    """Every short row costs the pairs' workgroups a walk over its nonzeros: with 8, 32 and 47 of
-    166 rows such a call takes 23, 34 and 37 us on pairs and 41, 37 and 37 on the tiled kernel."""
+    """Every short row costs the pairs' workgroups a walk over its nonzeros: with 8 and 32 of 166 rows such a call takes 22 and 30 us, 41
+    and 37 on the tiled kernel; with 47 the two come out nearly even and it stays there."""
     L = layer((57, 97, 10, 12, 166, 3, 3, 1, 0.53, 0), N=1, seed=5)
     rows = np.diff(L.rowptr)
     rows[np.linspace(0, len(rows) - 1, cut).astype(int)] = 50
