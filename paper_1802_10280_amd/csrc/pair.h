@@ -12,9 +12,10 @@ constexpr int kPairStepBytes = 2048;       // of 32 channels' weights for one ta
 constexpr int kPairLdsBytes = 160 * 1024;
 
 // How a workgroup's waves are laid out: over 64 output channels each, 64 positions each, 16 input channels each.  Channels with
-// fewer than `few` nonzeros are computed from those.
+// fewer than `few` nonzeros are computed from those.  `flush`: after so many rounds a wave adds its sums to the workgroup's in LDS and
+// starts again from zero, which makes the chains shorter and so more exact; 0: never.
 struct PairShape {
-    int MW, PW, KW, few = 0;
+    int MW, PW, KW, few = 0, flush = 0;
 };
 constexpr int kFewBatch = 16;              // that many of their nonzeros at a time
 constexpr int kFewChains = 4;              // in so many chains of sums
@@ -28,11 +29,12 @@ inline long long pair_reach(const Dims& d) { return (long long)(d.R - 1) * pair_
 // window positions a channel takes in LDS
 inline int pair_window(const Dims& d, const PairShape& s) { return (int)((64 * s.PW + pair_reach(d) + 3) / 4 * 4); }
 // LDS: notes, the channels' exponents and biases, the positions' outputs and the window's words (head); then one
-// window buffer, or two where there is more than one round of channels; the waves' sums meet in the same place.
+// window buffer, or two where there is more than one round of channels; the waves' sums meet in the same place.  Behind them
+// the workgroup's sums, where they are flushed.
 inline int pair_head_bytes(const PairShape& s) { return 64 + 8 * 64 * s.MW + 4 * 64 * s.PW; }
 inline int pair_lds_bytes(const Dims& d, const PairShape& s) {
     const int WR = pair_window(d, s), buffers = (int)mfma_chunks(d) > s.KW ? 2 : 1;
-    return pair_head_bytes(s) + 4 * WR + std::max(buffers * s.KW * 64 * WR, s.MW * s.PW * (s.KW - 1) * 64 * 256);
+    return pair_head_bytes(s) + 4 * WR + std::max(buffers * s.KW * 64 * WR, s.MW * s.PW * (s.KW - 1) * 64 * 256) + (s.flush ? s.MW * s.PW * 64 * 256 : 0);
 }
 
 // two steps to ask for ahead

@@ -38,6 +38,7 @@ static double pair_time(const Dims& d, double N, const PairShape& s, double few 
     double job = jobs > slots ? 17000 : 12000;
     if (d.S == 3) job += steps * (waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * 250;
     else job += steps * 1150 + (rounds - 1) * (2700 + tasks * 750);
+    if (s.flush) job += rounds / s.flush * 700;
     job += few / ceil(d.M / (64.0 * s.MW)) / waves * s.PW * 1900;
     const double full = floor(jobs / slots), rest = jobs / slots - full;
     return 2.0 + std::max(1.0, full + (rest > 0 ? 0.5 + 0.5 * rest : 0.0)) * job / 2000.0;
@@ -77,11 +78,22 @@ static bool pair_takes(const Dims& d) {
 // the pairs' share stays (0.8e-7 at 3 %) while the chains' falls: they are even at 43 % where the pairs stand in for three bf16 parts and at 7
 // to 30 % where they do for the tiled kernel, and at 3 % a layer of 115 is at 0.84 and 0.42.  The kernel sees the inputs too late, so who has
 // such inputs, and needs those bits, fixes a tuning.
-static double pair_base(const PairShape& s) { return s.KW == 8 ? 0.92 : 0.81; }
-static double pair_slope(const PairShape& s) { return s.KW == 2 ? 0.0044 : s.KW == 4 ? 0.0020 : 0.00105; }
+// Two shares whose sums are flushed as often as flush_rounds() says are taken for eight, whose chains are as long: measured 1.33 and 1.38 (256
+// channels, 3x3, 50 %), 1.39 and 1.44 (384, 65 %).
+static double pair_base(const PairShape& s) { return s.KW == 8 || s.flush ? 0.92 : 0.81; }
+static double pair_slope(const PairShape& s) { return s.KW == 8 || s.flush ? 0.00105 : s.KW == 4 ? 0.0020 : 0.0044; }
 static double tiled_slope(int WS) { return 0.0154 / WS; }
 constexpr double kTiledRowSlope = 0.0163, kMfmaSlope = 0.00195;  // the first: a row of 36 to 90 nonzeros, WS = 1
 static double pair_error(double n, const PairShape& s) { return pair_base(s) + pair_slope(s) * n; }
+
+// Rounds between a wave's flushes: such that its chains are as long as with eight shares, and as exact.  0 where the wave and its partner would not
+// both have had a turn by then, and for launches that do not fill every compute unit twice, where eight shares are as fast (32 images of
+// 13x13, 512 channels, 384 filters at 50 %: 93.4 us both ways).
+static int flush_rounds(const Dims& d, const PairShape& s) {
+    if (s.KW != 2 || ceil(d.N * (double)pair_plane(d) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW)) < 512) return 0;
+    const int flush = (int)mfma_chunks(d) / 8;
+    return flush >= 2 ? flush : 0;
+}
 
 // A row of fewer nonzeros is less exact as pairs than in a kernel of that slope.
 static int least_row(const PairShape& s, double slope) {
@@ -127,11 +139,13 @@ bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
     const double n = (double)h.pair_nnz / d.M, slope = bf16 ? kMfmaSlope : tiled_slope(h.WS);
     double best = kMargin * (bf16 ? mfma_time(d, d.N) : tiled_time(d, d.N, h));
     bool taken = false;
-    for (const PairShape& s : kShapes) {
-        if (pair_error(n, s) > (bf16 ? 1.0 : 0.95) * slope * n) continue;
+    for (PairShape s : kShapes) {
+        const double most = (bf16 ? 1.0 : 0.95) * slope * n;
+        if (pair_error(n, s) > most) s.flush = flush_rounds(d, s);
+        if (pair_error(n, s) > most) continue;
         const int least = least_row(s, bf16 ? kMfmaSlope : kTiledRowSlope / h.WS);
         const bool few = h.pair_least < least;
-        if (few && (bf16 || h.WS > kFewChains)) continue;
+        if (few && (bf16 || h.WS > kFewChains || s.flush)) continue;
         const double t = pair_time(d, d.N, s, !few ? 0 : s.KW == 2 ? h.pair_few2 : s.KW == 4 ? h.pair_few4 : h.pair_few8);
         if (t < best) {
             best = t;

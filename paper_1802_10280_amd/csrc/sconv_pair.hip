@@ -22,7 +22,7 @@
 // too slowly to keep a matrix core busy (a tap took 1100 clocks where what lies around its instructions was in one
 // place): the rest of a step is strung out between them and, for filters three wide, a row of taps is one block without
 // address arithmetic.  Staging the next chunks goes along in the same way.
-// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312), at 50 % 219-240 (323); 64x384x13x13, 384 filters, 65 %: 109-119 (three
+// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312), at 50 % 172-178 (323); 64x384x13x13, 384 filters, 65 %: 109-111 (three
 // bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy half of the time in the first
 // one (76 us at 2.4 GHz) and a third where eight waves share the channels (counters, first call after others); the rest is the workgroups'
 // beginnings and ends, 12000-17000 clocks each, which only the other workgroup of a compute unit hides (there is none beside eight
@@ -60,6 +60,8 @@ struct PairArgs : MfmaArgs {
     int groups;      // of 64 window positions
     uint32_t w_bytes;
     int few;         // channels with fewer nonzeros are computed from those
+    int total_at;    // of the flushed sums, behind the window
+    int flush;       // rounds between a wave's flushes, 0: none
 };
 
 #define ESCOIN_INLINE __attribute__((always_inline))
@@ -106,8 +108,8 @@ struct Room {
 };
 
 // One pass over all channels: the wave's share of the sums, scaled by 2^-(ex + the row's exponent) in `v`, and which
-// positions have one that cannot be used.  AGAIN: with the scale for notes.peak, not one guessed from the first inputs.
-template <int MW, int PW, int KW, bool AGAIN>
+// positions have one that cannot be used.  FLUSH: with the sums flushed now and then (PairShape).  AGAIN: with the scale for notes.peak, not one guessed from the first inputs.
+template <int MW, int PW, int KW, bool FLUSH, bool AGAIN>
 __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> room, Rsrc in, Rsrc wr, int lane, int wave, int mg, float (&v)[64 / KW],
                                          int* scale) {
     constexpr int kWaves = MW * PW * KW, TM = 64 * MW;
@@ -115,6 +117,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     const int WR = room.WR, sub_bytes = 4 * 16 * WR, buf_bytes = KW * sub_bytes;
     char* const win = room.win();
     const uint32_t* const tab = room.tab();
+    f4* const total = (f4*)(win + a.total_at) + (wm * PW + wp) * 16 * 64 + lane;  // as `big` lies, four values at a time
     Notes<PW>* const notes = room.notes();
     const int HW4 = a.H * a.W * 4, last_channel = (a.C - 1) * HW4, RS = a.R * a.S;
     // What the steps ask for runs two steps ahead of them, through the rounds.
@@ -398,6 +401,27 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
                 if (three_ahead) fetch(tc, round + 2);
             }
         }
+        // Long chains: the sums so far join the workgroup's in LDS (no registers are left for them), which makes two shares as exact as eight with
+        // half their workgroups' beginnings (64x256x28x28 at 50 %: 224-240 -> 172-178 us; a flush costs some 600 clocks, all of them 4 %).
+        // Half of a wave's channels at a time: the two waves that share them take one half each and change over, with a round's
+        // barrier between, so neither waits for the other (a wave at a time: 178 us for 174).
+        if (FLUSH && more) {
+            const int turn = (round + 1) % a.flush;
+            const bool first = round + 1 < a.flush;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                if (turn != ((p ^ kg) & 1)) continue;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    f4 s = first ? (f4)(0.0f) : total[(8 * p + i) * 64];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) s[b] += big[p][i >> 2][4 * (i & 3) + b];
+                    total[(8 * p + i) * 64] = s;
+                }
+                big[p][0] = (f16v)(0.0f);
+                big[p][1] = (f16v)(0.0f);
+            }
+        }
         __syncthreads();
     }
     if (lost) atomicAdd(&notes->lost, lost);
@@ -429,6 +453,14 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
 #pragma unroll
         for (int i = 0; i < kShare / 4; ++i) {
             const f4 s = o[i * 64];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[4 * i + b] += s[b];
+        }
+    }
+    if (FLUSH) {
+#pragma unroll
+        for (int i = 0; i < kShare / 4; ++i) {
+            const f4 s = total[(kg * (kShare / 4) + i) * 64];
 #pragma unroll
             for (int b = 0; b < 4; ++b) v[4 * i + b] += s[b];
         }
@@ -532,7 +564,7 @@ __device__ inline void few_rows(const PairArgs& a, const Room<MW, PW> room, Rsrc
 }
 
 // MW, PW: waves over channels and positions, 64 each; KW: over the input channels, 16 each a round.
-template <int MW, int PW, int KW>
+template <int MW, int PW, int KW, bool FLUSH>
 __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const PairArgs a) {
     constexpr int kWaves = MW * PW * KW, kThreads = 64 * kWaves, TP = 64 * PW, TM = 64 * MW;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -615,7 +647,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     {
         float v[kShare];
         int ex;
-        const uint64_t any = pass<MW, PW, KW, false>(a, room, in, wr, lane, wave, mg, v, &ex);
+        const uint64_t any = pass<MW, PW, KW, FLUSH, false>(a, room, in, wr, lane, wave, mg, v, &ex);
         // Said so that the usual way out is one piece of code (32x64x56x56: 33.9 -> 33.6 us); said for certain, the second pass is
         // compiled as one that never runs, with 150-200 registers spilled (inputs that need it: 0.42 -> 0.56 ms at 64x256x28x28).
         if (__builtin_expect_with_probability(any == 0, 1, 0.9)) {
@@ -644,7 +676,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     float v[kShare];
     int ex, lane2 = lane, wave2 = wave;
     asm volatile("" : "+v"(lane2));  // what the first pass made of it is not worth keeping for this one
-    const uint64_t any = pass<MW, PW, KW, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
+    const uint64_t any = pass<MW, PW, KW, FLUSH, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
     store(v, ex);
     int start = t0;
     asm volatile("" : "+s"(start));  // nor what the beginning made of this
@@ -662,9 +694,9 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     }
 }
 
-template <int MW, int PW, int KW>
+template <int MW, int PW, int KW, bool FLUSH = false>
 int start(PairArgs& a, const Dims& d, hipStream_t stream) {
-    constexpr PairShape shape = {MW, PW, KW};
+    const PairShape shape = {MW, PW, KW, a.few, a.flush};
     static_assert(sizeof(Notes<PW>) <= 64, "");
     a.n_mgroups = (d.M + 64 * MW - 1) / (64 * MW);
     a.n_tiles = (int)(((long long)d.N * a.plane + 64 * PW - 1) / (64 * PW));
@@ -672,12 +704,13 @@ int start(PairArgs& a, const Dims& d, hipStream_t stream) {
     a.groups = (a.WR + 63) / 64;
     const int lds = pair_lds_bytes(d, shape);
     if (lds > kPairLdsBytes) return ESCOIN_ERANGE;
+    a.total_at = lds - MW * PW * 64 * 256 - pair_head_bytes(shape) - 4 * a.WR;
     if (lds > 64 * 1024) {
-        const int rc = allow_dynamic_lds((const void*)sconv_pair_kernel<MW, PW, KW>, lds);
+        const int rc = allow_dynamic_lds((const void*)sconv_pair_kernel<MW, PW, KW, FLUSH>, lds);
         if (rc != ESCOIN_OK) return rc;
     }
     const unsigned blocks = (unsigned)(((long long)a.n_tiles * a.n_mgroups + 7) / 8 * 8);
-    return launch(sconv_pair_kernel<MW, PW, KW>, dim3(blocks), dim3(64 * MW * PW * KW), (size_t)lds, stream, a);
+    return launch(sconv_pair_kernel<MW, PW, KW, FLUSH>, dim3(blocks), dim3(64 * MW * PW * KW), (size_t)lds, stream, a);
 }
 
 }  // namespace
@@ -697,11 +730,12 @@ int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& s, co
     a.plane = (int)pair_plane(d);
     a.n_chunks = (int)mfma_chunks(d);
     a.few = s.few;
+    a.flush = s.flush;
     const int layout = 100 * s.MW + 10 * s.PW + s.KW;
     if (layout == 114) return start<1, 1, 4>(a, d, stream);
     if (layout == 118) return start<1, 1, 8>(a, d, stream);
-    if (layout == 122) return start<1, 2, 2>(a, d, stream);
-    if (layout == 212) return start<2, 1, 2>(a, d, stream);
+    if (layout == 122) return a.flush ? start<1, 2, 2, true>(a, d, stream) : start<1, 2, 2>(a, d, stream);
+    if (layout == 212) return a.flush ? start<2, 1, 2, true>(a, d, stream) : start<2, 1, 2>(a, d, stream);
     return ESCOIN_EINVAL;
 }
 

@@ -221,6 +221,35 @@ def test_against_the_oracle(oracle, shape):
     assert np.linalg.norm(got - ref) <= np.linalg.norm(chain - ref)
 
 
+# In place of three bf16 parts, in launches that fill the compute units: two shares, flushed every other round or so.
+FLUSHED = [
+    (74, 384, 14, 14, 250, 3, 3, 1, 0.55, 212),    # every third of twelve rounds
+    (74, 272, 14, 14, 250, 3, 3, 1, 0.45, 212),    # nine rounds, the last of one chunk that two waves share
+    (62, 496, 17, 17, 250, 2, 2, 0, 0.30, 212),    # filters two wide, every third round of sixteen
+    (240, 250, 16, 16, 64, 3, 3, 1, 0.40, 122),    # two waves by positions
+]
+
+
+@gpu
+@pytest.mark.parametrize("shape", FLUSHED, ids=str)
+def test_flushed_sums(oracle, shape):
+    print("pair flushed", shape, flush=True)
+    L = layer(shape, seed=101)
+    L.input[1, 7, 3, 4] = np.inf                    # ends in a sum that was flushed, and leads to the second pass
+    dl, old = pair_layer(L, shape[-1]), DeviceLayer(esc, L)
+    old.forward_tiled()
+    forget(old.plan, ("pair_least",))
+    old.d_plan = to_dev(old.plan)
+    assert esc.escoin_sconv_tiled_kernel(old.desc, old.plan) == 1  # so unflushed pairs would not do
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, bound = oracle_full(oracle, L)
+        got, parts = dl.forward_tiled().astype(np.float64), old.forward_tiled().astype(np.float64)
+        off, parts_off = got - ref, parts - ref
+    ok = np.isfinite(bound)
+    assert not ok.all() and np.array_equal(got[~ok], ref[~ok], equal_nan=True)
+    assert (np.abs(off[ok]) <= limit(L, bound)[ok]).all() and np.linalg.norm(off[ok]) <= np.linalg.norm(parts_off[ok])
+
+
 @gpu
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[4]], ids=str)
 def test_unaligned_buffers_guards_and_one_plan_for_two_batches(oracle, shape):
