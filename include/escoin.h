@@ -169,16 +169,17 @@ int escoin_sconv_plan_build(const escoin_conv_desc *desc, const int32_t *rowptr,
  * additions, and with it the last bits of the result, may differ from run to run), and, with
  * ESCOIN_F_RELU, the clamp as a pass of its own.
  *
- * A plan made without tuning for a layer of stride 1 may also hold its weights for the matrix cores, and a call on a
+ * A plan made without tuning for a layer of stride 1 or 2 may also hold its weights for the matrix cores, and a call on a
  * batch large enough to be faster there multiplies all of them, zeros too.  Two forms:
  *   - pairs of fp16 numbers, for layers of up to some 90 % sparsity whose rows have 32 nonzeros or more, 60 to some hundred on
- *     the average, and whose filters reach at most 127 positions of the flat padded map (two rows of 62, four of 30).  Inputs are scaled by a
+ *     the average, and whose filters reach at most 127 positions of the flat padded map (two rows of 62, four of 30; at
+ *     stride 2 of the outputs' map).  Inputs are scaled by a
  *     power of two, the same for a workgroup's window, weights by one a row.  A pair holds 22 to 23 bits: an output of n
  *     products is off by up to 2^-21 of sum|w*x|, 0.8e-7 to 1.5e-7 of the result in the mean.  Where half of the inputs are zeros that is
  *     less than a chain of fp32 sums is off by from about 60 nonzeros on, and shorter rows are summed in fp32; an output that meets
  *     fewer than some 30 inputs other than zero is less exact than in fp32 (a single product by up to 2^-21, not 2^-24).  A plan made
  *     with a tuning keeps to fp32 multiply-adds.  Weights of a row more than 2^27 apart keep a layer from the pairs;
- *   - three bf16 parts each, for layers pruned little (roughly 50-70 %) where the sums are too short for the pairs or the filters
+ *   - three bf16 parts each, for layers of stride 1 pruned little (roughly 50-70 %) where the sums are too short for the pairs or the filters
  *     reach further.  Results stay within fp32 rounding of the sums over the nonzeros.  Weights outside 2^-50 .. 2^30 keep a layer
  *     from it.
  * In both, tiny inputs, Inf and NaN behave as in the sums over the nonzeros: outputs that meet an Inf or a NaN, or whose

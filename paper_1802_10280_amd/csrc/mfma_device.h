@@ -16,7 +16,7 @@ struct MfmaArgs {
     const b8* w;              // [32-row block][chunk of 16 channels][tap][split][lane]
     const int32_t* rowptr;    // the nonzeros once more, for sums that cannot be used
     const MfmaNz* nz;
-    int N, C, H, W, M, E, F, R, S, pad;
+    int N, C, H, W, M, E, F, R, S, pad, stride;
     int pitch, plane;         // of the flat padded array: columns per row, positions per image
     int n_chunks, n_mgroups, n_tiles;
     uint32_t flags;
@@ -92,7 +92,7 @@ __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], in
         a.out[((size_t)n * a.M + m) * EF + h * a.F + x] = v;
     };
     const auto place = [&](int u) -> Place {
-        const int n = u / a.plane, rem = u - n * a.plane, y = rem / a.pitch - a.pad, x = rem % a.pitch - a.pad;
+        const int n = u / a.plane, rem = u - n * a.plane, y = rem / a.pitch * a.stride - a.pad, x = rem % a.pitch * a.stride - a.pad;
         return {y, x, (n - n_first) * a.C * HW + y * a.W + x};
     };
     // More than half of them: a lane takes its position of every run at once, and a nonzero is read for all

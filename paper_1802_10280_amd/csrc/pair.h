@@ -20,20 +20,34 @@ struct PairShape {
 constexpr int kFewBatch = 16;              // that many of their nonzeros at a time
 constexpr int kFewChains = 4;              // in so many chains of sums
 
-// The flat padded map whose positions are numbered through the batch, the padding between rows and images shared: columns a
-// row, positions an image, and how far the taps reach.
-inline int pair_pitch(const Dims& d) { return d.W + d.pad; }
-inline long long pair_plane(const Dims& d) { return (long long)(d.H + d.pad) * pair_pitch(d); }
-inline long long pair_reach(const Dims& d) { return (long long)(d.R - 1) * pair_pitch(d) + d.S - 1; }
+// The flat padded map whose positions are numbered through the batch: columns a row, positions an image, and how far the taps
+// reach.  At stride 1 the padding between rows and images is shared; at stride 2 the map is that of the outputs, a tap's inputs
+// are those of one evenness of row and column (a phase: 2 * row + column), and each phase is a map of its own beside the others.
+inline int pair_pitch(const Dims& d) { return d.stride == 2 ? d.F + (d.S - 1) / 2 : d.W + d.pad; }
+inline long long pair_plane(const Dims& d) { return (long long)(d.stride == 2 ? d.E + (d.R - 1) / 2 : d.H + d.pad) * pair_pitch(d); }
+inline long long pair_reach(const Dims& d) {
+    return d.stride == 2 ? (long long)((d.R - 1) / 2) * pair_pitch(d) + (d.S - 1) / 2 : (long long)(d.R - 1) * pair_pitch(d) + d.S - 1;
+}
 
+// Stride 2: where a phase's positions start in the window; phase 4: where they end.  A phase reaches as far as its own taps.
+inline int pair_phase_at(const Dims& d, const PairShape& s, int phase) {
+    int at = 0;
+    for (int k = 0; k < phase; ++k) {
+        const int rows = d.R - 1 - k / 2, cols = d.S - 1 - k % 2;
+        if (rows >= 0 && cols >= 0) at += 64 * s.PW + rows / 2 * pair_pitch(d) + cols / 2;
+    }
+    return at;
+}
 // window positions a channel takes in LDS
-inline int pair_window(const Dims& d, const PairShape& s) { return (int)((64 * s.PW + pair_reach(d) + 3) / 4 * 4); }
+inline int pair_window(const Dims& d, const PairShape& s) {
+    return (int)(((d.stride == 2 ? pair_phase_at(d, s, 4) : 64 * s.PW + pair_reach(d)) + 3) / 4 * 4);
+}
 // LDS: notes, the channels' exponents and biases, the positions' outputs and the window's words (head); then one
-// window buffer, or two where there is more than one round of channels; the waves' sums meet in the same place.  Behind them
+// window buffer, or two where there is more than one round of channels (stride 1); the waves' sums meet in the same place.  Behind them
 // the workgroup's sums, where they are flushed.
 inline int pair_head_bytes(const PairShape& s) { return 64 + 8 * 64 * s.MW + 4 * 64 * s.PW; }
 inline int pair_lds_bytes(const Dims& d, const PairShape& s) {
-    const int WR = pair_window(d, s), buffers = (int)mfma_chunks(d) > s.KW ? 2 : 1;
+    const int WR = pair_window(d, s), buffers = d.stride == 1 && (int)mfma_chunks(d) > s.KW ? 2 : 1;
     return pair_head_bytes(s) + 4 * WR + std::max(buffers * s.KW * 64 * WR, s.MW * s.PW * (s.KW - 1) * 64 * 256) + (s.flush ? s.MW * s.PW * 64 * 256 : 0);
 }
 

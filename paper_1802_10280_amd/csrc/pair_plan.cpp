@@ -24,19 +24,27 @@ constexpr double kLeastJobs = 64;
 // with 256 channels, 56x56 with 64, 7x7 with 512, 14x14 with 256, 13x13 with 384) and 18, 10 and 12 where 19, 11 and 12
 // were (13 of 15x15 with 240, one of 41x44 with 24, 5 of 7x7 with 69).
 //
+// At stride 2 the next round is staged when the last one is over.  A workgroup that has a compute unit to itself takes 16800 clocks around its
+// steps and 600 a step, beside another one 26000 and 900; 620 a staging task, and 2300 a round where filters are not three wide.  That is
+// 25, 24, 26, 43, 33, 14 and 104 us where 26, 26, 25, 41, 30, 13 and 100 were measured (32 images of 56x56 with 64 channels, 28x28 with 128 in both layouts,
+// 14x14 with 256 in both; 13 of 63x63 with 30; 64 of 31x31 with 128, 5x5; tiled: 40, 43, 43, 53, 53, 18, 195).
+//
 // `few`: batches of nonzeros of all short rows.  A batch takes a wave 1200 clocks for 64 positions, with all of them at it; counted as 1900, since
 // a whole row falls to one wave.  105 random layers of uneven rows that take the pairs by this need 0.39 to 0.96 of the tiled kernel's time, one
 // 1.09 (26 of 25x25, 34 -> 51 channels, 5x5: 22.4 us and 31.3, but 34.0 for inputs that send one workgroup through its second pass).
 static double pair_time(const Dims& d, double N, const PairShape& s, double few = 0) {
     const int waves = s.MW * s.PW * s.KW, lds = pair_lds_bytes(d, s), RS = d.R * d.S;
-    if (lds > kPairLdsBytes) return INFINITY;
+    if (lds > kPairLdsBytes || (d.stride == 2 && waves > 4)) return INFINITY;
     const double jobs = ceil(N * (double)pair_plane(d) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW));
     if (jobs < kLeastJobs) return INFINITY;
     const double slots = waves == 4 && 2 * lds <= kPairLdsBytes ? 512 : 256;
     const int chunks = (int)mfma_chunks(d), rounds = (chunks + s.KW - 1) / s.KW;
     const double steps = ceil((double)chunks * RS / s.KW), tasks = ceil(2.0 * s.KW * ((pair_window(d, s) + 63) / 64) / waves);
     double job = jobs > slots ? 17000 : 12000;
-    if (d.S == 3) job += steps * (waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * 250;
+    if (d.stride == 2) {
+        const bool shared = jobs > 256 && slots == 512;
+        job = (shared ? 26000 : 16800) + steps * (shared ? 900 : 600) + (rounds - 1) * (tasks * 620 + (d.S == 3 ? 0 : 2300));
+    } else if (d.S == 3) job += steps * (waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * 250;
     else job += steps * 1150 + (rounds - 1) * (2700 + tasks * 750);
     if (s.flush) job += rounds / s.flush * 700;
     job += few / ceil(d.M / (64.0 * s.MW)) / waves * s.PW * 1900;
@@ -47,11 +55,12 @@ static double pair_time(const Dims& d, double N, const PairShape& s, double few 
 // The tiled kernel's, from its tiling: rounds of workgroups over 8 x 32 compute units; a workgroup's 4 us and half a us a chunk, and the
 // LDS reads of its records, 4.6 clocks of 2.1 GHz for each position run and half of that for the record itself.  That is 48, 48, 56,
 // 58, 188 and 107 us where 48, 47, 55, 59, 177 and 111 were measured (56x56 with 64 channels, 28x28 with 128, 14x14 with 256, 7x7 with 512,
-// 28x28 with 256 at 90 and 95 %), 11 and 12 where 11 and 15 were (16 channels, 5x5; 192 channels, 1x1).
+// 28x28 with 256 at 90 and 95 %), 11 and 12 where 11 and 15 were (16 channels, 5x5; 192 channels, 1x1).  At stride 2 it takes a fifth more: 38, 41, 47, 70, 213, 17 where
+// 40, 43, 53, 58, 195 and 18 were (the layers above).
 static double tiled_time(const Dims& d, double N, const PlanHeader& h) {
     const double jobs = (double)h.n_tiles * ceil(N / h.NB) * h.n_mgroups * h.CS;
     const double job = 4.0 + 0.5 * h.n_chunks / h.CS + (double)h.n_records / h.n_mgroups / h.CS * h.WQ * (h.Q + 0.5) * 4.6 / 2100.0;
-    return ceil(ceil(jobs / 8) / 32) * job;
+    return ceil(ceil(jobs / 8) / 32) * job * (d.stride == 2 ? 1.2 : 1.0);
 }
 
 // How much faster it has to look, as the estimates are off by a tenth now and then.
@@ -59,7 +68,7 @@ constexpr double kMargin = 0.9;
 
 // The shapes the kernel takes.
 static bool pair_takes(const Dims& d) {
-    if (d.stride != 1 || d.R <= d.pad || d.S <= d.pad || d.C < 16 || d.M < 32) return false;
+    if (d.stride > 2 || (d.stride == 1 && (d.R <= d.pad || d.S <= d.pad)) || d.C < 16 || d.M < 32) return false;
     if (pair_reach(d) > kPairReach || pair_weight_bytes(d) > (64ull << 20)) return false;
     // positions, and the offsets inside the images that a workgroup's window may touch, in 32 bits
     const long long plane = pair_plane(d), images = (128 + kPairReach) / plane + 2;

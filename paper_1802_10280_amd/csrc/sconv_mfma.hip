@@ -239,7 +239,7 @@ int launch_sconv_mfma(const Dims& d, const PlanHeader& h, const char* d_plan, co
     a.w = (const b8*)(d_plan + h.off_mfma);
     a.rowptr = (const int32_t*)(d_plan + h.off_mfma + mfma_weight_bytes(d));
     a.nz = (const MfmaNz*)(d_plan + h.off_mfma + mfma_weight_bytes(d) + mfma_rowptr_bytes(d));
-    a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad;
+    a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad; a.stride = d.stride;
     a.pitch = d.W + d.pad;
     a.plane = (d.H + d.pad) * a.pitch;
     a.n_chunks = (d.C + 15) / 16;

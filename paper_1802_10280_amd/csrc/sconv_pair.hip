@@ -1,5 +1,5 @@
 // sconv on the matrix cores with fp32 operands as pairs of fp16 numbers, for all but the most heavily pruned layers of
-// stride 1.
+// stride 1 and 2.
 //
 // The layer is one product per filter tap over the flat padded positions of the whole batch, zeros included, as in
 // sconv_mfma.hip.  There an operand is three bf16 parts and a product six matrix instructions, here two fp16
@@ -22,6 +22,11 @@
 // too slowly to keep a matrix core busy (a tap took 1100 clocks where what lies around its instructions was in one
 // place): the rest of a step is strung out between them and, for filters three wide, a row of taps is one block without
 // address arithmetic.  Staging the next chunks goes along in the same way.
+//
+// At stride 2 the positions are the outputs', and a tap reads one of four phases of the input (rows and columns of one evenness),
+// all of which a round stages side by side: the window is four times as large beside the same steps, so it has one buffer and two
+// workgroups to a compute unit hide each other's staging (phase after phase, as rounds of their own: no faster than the tiled kernel).
+// 32x128x56x56, 128 3x3 filters, 80 %: 38 us (tiled 70); 11x78x45x45, 439 5x5 filters, 71 %: 50 (125); 13x89x23x23, 276 3x3, 71 %: 17.5 (24).
 // Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312), at 50 % 172-178 (323); 64x384x13x13, 384 filters, 65 %: 109-111 (three
 // bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy half of the time in the first
 // one (76 us at 2.4 GHz) and a third where eight waves share the channels (counters, first call after others); the rest is the workgroups'
@@ -62,6 +67,7 @@ struct PairArgs : MfmaArgs {
     int few;         // channels with fewer nonzeros are computed from those
     int total_at;    // of the flushed sums, behind the window
     int flush;       // rounds between a wave's flushes, 0: none
+    int phase_at[4]; // stride 2: where the window's rows and columns of each evenness (2 * row + column) start, in positions
 };
 
 #define ESCOIN_INLINE __attribute__((always_inline))
@@ -108,8 +114,9 @@ struct Room {
 };
 
 // One pass over all channels: the wave's share of the sums, scaled by 2^-(ex + the row's exponent) in `v`, and which
-// positions have one that cannot be used.  FLUSH: with the sums flushed now and then (PairShape).  AGAIN: with the scale for notes.peak, not one guessed from the first inputs.
-template <int MW, int PW, int KW, bool FLUSH, bool AGAIN>
+// positions have one that cannot be used.  FLUSH: with the sums flushed now and then (PairShape).  STRIDE 2: on
+// the window's four phases, in one buffer (pair.h).  AGAIN: with the scale for notes.peak, not one guessed from the first inputs.
+template <int MW, int PW, int KW, bool FLUSH, int STRIDE, bool AGAIN>
 __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> room, Rsrc in, Rsrc wr, int lane, int wave, int mg, float (&v)[64 / KW],
                                          int* scale) {
     constexpr int kWaves = MW * PW * KW, TM = 64 * MW;
@@ -172,6 +179,12 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
         o[2 * WR] = l;
     };
 
+    const auto tap_at = [&](int r, int s) ESCOIN_INLINE -> int {
+        if (STRIDE == 1) return r * a.pitch + s;
+        const int even = s & 1 ? a.phase_at[1] : a.phase_at[0], odd = s & 1 ? a.phase_at[3] : a.phase_at[2];
+        return (r & 1 ? odd : even) + (r >> 1) * a.pitch + (s >> 1);
+    };
+
     f16v big[2][2], small[2][2];
     struct Weights { u4 p[2][2]; } w0, w1, w2;
     auto weights = [&](Weights& o, int k, int p, int further = 0) ESCOIN_INLINE {
@@ -188,7 +201,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     // Every round but the last gives each wave RS steps, so none is empty before the last; there, a wave without
     // steps only helps with the staging.
     Task ta, tb, tc;
-    const bool three_ahead = a.S != 3;  // of the next round's tasks; filters three wide ask for them on the way
+    const bool three_ahead = STRIDE == 2 || a.S != 3;  // of the next round's tasks; filters three wide ask for them on the way
     {
         Task t[8];
 #pragma unroll
@@ -247,10 +260,11 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     __syncthreads();
     for (int round = 0; round < n_rounds; ++round) {
         const bool more = round + 1 < n_rounds;
-        const int buf = round & 1;
+        const int buf = STRIDE == 2 ? 0 : round & 1, other = STRIDE == 2 ? 0 : buf ^ 1;
         const int begin = ask.first_step(round, kg), end = ask.first_step(round, kg + 1);
         int sub = begin / RS, tap = begin - sub * RS, r = tap / a.S, s = tap - r * a.S;
-        const char* row = win + buf * buf_bytes + sub * sub_bytes + ((lane >> 5) * WR + wp * 64 + (lane & 31) + r * a.pitch + s) * 16;
+        const char* base = win + buf * buf_bytes + sub * sub_bytes + ((lane >> 5) * WR + wp * 64 + (lane & 31)) * 16;
+        const char* row = base + tap_at(r, s) * 16;
         h8 xh0, xh1;
         const auto read = [&](int k, int q) ESCOIN_INLINE -> h8 { return *(const h8*)(row + (32 * q + 2 * WR * k) * 16); };
         int i = begin, task = 0;
@@ -275,8 +289,10 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
                 if (++r == a.R) {
                     r = 0;
                     row += sub_bytes - a.R * a.pitch * 16;
+                    base += sub_bytes;
                 }
             }
+            if (STRIDE == 2) row = base + tap_at(r, s) * 16;
             ESCOIN_MFMA(big, 0, xh, 1, 0)
             ESCOIN_MFMA(big, 0, xh, 1, 1)
             ESCOIN_MFMA(small, 1, xh, 0, 0)
@@ -309,13 +325,13 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     ESCOIN_FENCE                                                                                                        \
     ACC[P][Q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, SET.p[P][A]), B##Q, ACC[P][Q], 0, 0, 0); \
     ESCOIN_FENCE
-            // T: the tap; SET: its weights; CN: the set that the ones asked for now go to
-#define ESCOIN_STEP(T, SET, CN, FURTHER, NOW, NEXT, NEXT_ROW)                                                         \
+            // ROW: the tap's inputs; SET: its weights; CN: the set that the ones asked for now go to
+#define ESCOIN_STEP(ROW, SET, CN, FURTHER, NOW, NEXT, NEXT_ROW)                                                         \
     __builtin_amdgcn_s_waitcnt(STAGE ? 0x4f74 : 0x0f74);                                                              \
     ESCOIN_MFMA(big, SET, 0, xh, 0, 0)                                                                                \
-    xl0 = *(const h8*)(row + part + 16 * T);                                                                          \
+    xl0 = *(const h8*)(ROW + part);                                                                                   \
     ESCOIN_MFMA(big, SET, 0, xh, 0, 1)                                                                                \
-    xl1 = *(const h8*)(row + part + 16 * T + 512);                                                                    \
+    xl1 = *(const h8*)(ROW + part + 512);                                                                             \
     ESCOIN_MFMA(big, SET, 0, xh, 1, 0)                                                                                \
     weights(CN, 0, 0, FURTHER);                                                                                       \
     ESCOIN_MFMA(big, SET, 0, xh, 1, 1)                                                                                \
@@ -336,17 +352,27 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
     ESCOIN_MFMA(small, SET, 0, xl, 0, 1)                                                                              \
     ESCOIN_MFMA(small, SET, 0, xl, 1, 1)                                                                              \
     if (STAGE) {                                                                                                      \
-        commit(NOW, buf ^ 1);                                                                                         \
+        commit(NOW, other);                                                                                           \
         locate(NOW, ++task + 2);                                                                                      \
     }                                                                                                                 \
     ESCOIN_FENCE
             h8 xl0, xl1;
-            const char* const next_row = row + (++r == a.R ? sub_bytes - (a.R - 1) * a.pitch * 16 : a.pitch * 16);
-            if (r == a.R) r = 0;
-            ESCOIN_STEP(0, w0, w2, 0, ta, tc, row + 16)
+            const char* row1 = row + 16;
+            const char* row2 = row + 32;
+            if (STRIDE == 2) {
+                row1 = base + tap_at(r, 1) * 16;
+                row2 = row + 16;
+            }
+            const char* next_row = row + (++r == a.R ? sub_bytes - (a.R - 1) * a.pitch * 16 : a.pitch * 16);
+            if (r == a.R) {
+                r = 0;
+                base += sub_bytes;
+            }
+            if (STRIDE == 2) next_row = base + tap_at(r, 0) * 16;
+            ESCOIN_STEP(row, w0, w2, 0, ta, tc, row1)
             ask.next();
-            ESCOIN_STEP(1, w1, w0, 0, tb, ta, row + 32)
-            ESCOIN_STEP(2, w2, w1, kStepBytes, tc, tb, next_row)
+            ESCOIN_STEP(row1, w1, w0, 0, tb, ta, row2)
+            ESCOIN_STEP(row2, w2, w1, kStepBytes, tc, tb, next_row)
             ask.at += 2 * kStepBytes;
             ask.left -= 2;
             row = next_row;
@@ -361,7 +387,7 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
             xh0 = read(0, 0);
             xh1 = read(0, 1);
             if (a.S == 3 && s == 0 && (end - begin) % 3 == 0) {
-                if (more && end - i >= in_threes)
+                if (STRIDE == 1 && more && end - i >= in_threes)
                     while (task < in_threes) three(with);
                 while (i < end) three(plain);
             }
@@ -383,14 +409,15 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
             }
         }
         if (more) {
+            if (STRIDE == 2) __syncthreads();  // the only window has been read
             // the tasks left over: two or three of them have been asked for
-            if (task < my_tasks) commit(ta, buf ^ 1);
-            if (task + 1 < my_tasks) commit(tb, buf ^ 1);
-            if (three_ahead && 2 < my_tasks) commit(tc, buf ^ 1);
+            if (task < my_tasks) commit(ta, other);
+            if (task + 1 < my_tasks) commit(tb, other);
+            if (three_ahead && 2 < my_tasks) commit(tc, other);
             for (task += three_ahead ? 3 : 2; task < my_tasks; ++task) {
                 locate(ta, task);
                 fetch(ta, round + 1);
-                commit(ta, buf ^ 1);
+                commit(ta, other);
             }
             locate(ta, 0);
             locate(tb, 1);
@@ -502,7 +529,7 @@ __device__ inline void nowhere_past_the_table(const R& room, int lane, int wave)
 // the row's end and a lane number worked out for every nonzero a batch took 1600 (3x107x59x59, 388 channels, 170 batches: 77 -> 65 us, 41 without
 // any), a batch fetched while the last one is summed made it no faster.  64x256x28x28, 80 %, rows of 55 to 2304 nonzeros: 184 us, with
 // the short rows as pairs 148 and 1 to 2 % less exact than the tiled kernel, which takes 314.
-template <int MW, int PW, int KW>
+template <int MW, int PW, int KW, int STRIDE>
 __device__ inline void few_rows(const PairArgs& a, const Room<MW, PW> room, Rsrc in, int lane, int wave, int mg, int t0) {
     constexpr int kWaves = MW * PW * KW, TM = 64 * MW;
     const int EF = a.E * a.F, HW4 = a.H * a.W * 4, n_first = t0 / a.plane;
@@ -525,7 +552,10 @@ __device__ inline void few_rows(const PairArgs& a, const Room<MW, PW> room, Rsrc
                 const uint32_t* const p = (const uint32_t*)a.nz + 3 * (j + min(lane, here - 1));  // a nonzero a lane
                 const uint32_t c = p[0], rs = p[1], value = p[2];
                 const bool there = lane < here;  // past the end zeros meet
-                const uint32_t reach = there ? ((rs & 0xffffu) * a.pitch + (rs >> 16)) * 4u : 4u * a.WR;
+                const int r = rs & 0xffffu, s = rs >> 16;
+                int tap = r * a.pitch + s;
+                if (STRIDE == 2) tap = a.phase_at[2 * (r & 1) + (s & 1)] + (r >> 1) * a.pitch + (s >> 1);
+                const uint32_t reach = 4u * (there ? tap : a.WR);
                 const int channel = there ? (int)c * HW4 : 0, w = there ? (int)value : 0;
 #pragma unroll
                 for (int i = 0; i < 64; i += kFewBatch) {  // lane numbers are constants, which saves an instruction each
@@ -564,7 +594,7 @@ __device__ inline void few_rows(const PairArgs& a, const Room<MW, PW> room, Rsrc
 }
 
 // MW, PW: waves over channels and positions, 64 each; KW: over the input channels, 16 each a round.
-template <int MW, int PW, int KW, bool FLUSH>
+template <int MW, int PW, int KW, bool FLUSH, int STRIDE>
 __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const PairArgs a) {
     constexpr int kWaves = MW * PW * KW, kThreads = 64 * kWaves, TP = 64 * PW, TM = 64 * MW;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -593,10 +623,17 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     const float one_over_plane = 1.0f / (float)a.plane, one_over_pitch = 1.0f / (float)a.pitch;
     for (int i = tid; i < a.WR; i += kThreads) {
         int rem, col;
-        const int n = divide(u_first + i, a.plane, one_over_plane, &rem), line = divide(rem, a.pitch, one_over_pitch, &col);
-        const int y = line - a.pad, x = col - a.pad;
+        int u = u_first + i, odd_row = 0, odd_col = 0;
+        if (STRIDE == 2) {
+            odd_row = i >= a.phase_at[2] ? 1 : 0;
+            odd_col = i >= (odd_row ? a.phase_at[3] : a.phase_at[1]) ? 1 : 0;
+            u -= odd_row ? (odd_col ? a.phase_at[3] : a.phase_at[2]) : (odd_col ? a.phase_at[1] : 0);
+        }
+        const int n = divide(u, a.plane, one_over_plane, &rem), line = divide(rem, a.pitch, one_over_pitch, &col);
+        const int y = STRIDE * line + odd_row - a.pad, x = STRIDE * col + odd_col - a.pad;
         const bool there = n_first + n < a.N;
-        room.tab()[i] = there && y >= 0 && x >= 0 ? (uint32_t)(n * CHW + y * a.W + x) * 4u : kNowhere;
+        const bool inside = y >= 0 && x >= 0 && (STRIDE == 1 || (y < a.H && x < a.W));
+        room.tab()[i] = there && inside ? (uint32_t)(n * CHW + y * a.W + x) * 4u : kNowhere;
         if (i < TP) room.out_at()[i] = there && line < a.E && col < a.F ? n * a.M * EF + line * a.F + col : -1;
     }
     if (tid < TM) {
@@ -647,7 +684,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     {
         float v[kShare];
         int ex;
-        const uint64_t any = pass<MW, PW, KW, FLUSH, false>(a, room, in, wr, lane, wave, mg, v, &ex);
+        const uint64_t any = pass<MW, PW, KW, FLUSH, STRIDE, false>(a, room, in, wr, lane, wave, mg, v, &ex);
         // Said so that the usual way out is one piece of code (32x64x56x56: 33.9 -> 33.6 us); said for certain, the second pass is
         // compiled as one that never runs, with 150-200 registers spilled (inputs that need it: 0.42 -> 0.56 ms at 64x256x28x28).
         if (__builtin_expect_with_probability(any == 0, 1, 0.9)) {
@@ -655,7 +692,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
             if (__builtin_expect_with_probability(a.few != 0, 0, 0.7)) {
                 nowhere_past_the_table<PW>(room, lane, wave);
                 __syncthreads();  // and those stores before the ones of few_rows()
-                few_rows<MW, PW, KW>(a, room, in, lane, wave, mg, t0);
+                few_rows<MW, PW, KW, STRIDE>(a, room, in, lane, wave, mg, t0);
             }
             return;
         }
@@ -676,7 +713,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     float v[kShare];
     int ex, lane2 = lane, wave2 = wave;
     asm volatile("" : "+v"(lane2));  // what the first pass made of it is not worth keeping for this one
-    const uint64_t any = pass<MW, PW, KW, FLUSH, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
+    const uint64_t any = pass<MW, PW, KW, FLUSH, STRIDE, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
     store(v, ex);
     int start = t0;
     asm volatile("" : "+s"(start));  // nor what the beginning made of this
@@ -690,27 +727,36 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     if (a.few != 0) {
         nowhere_past_the_table<PW>(room, lane, wave);
         __syncthreads();  // and these
-        few_rows<MW, PW, KW>(a, room, in, lane, wave, mg, start);
+        few_rows<MW, PW, KW, STRIDE>(a, room, in, lane, wave, mg, start);
     }
 }
 
-template <int MW, int PW, int KW, bool FLUSH = false>
-int start(PairArgs& a, const Dims& d, hipStream_t stream) {
+template <int MW, int PW, int KW, bool FLUSH, int STRIDE>
+int launch_shape(PairArgs& a, const Dims& d, hipStream_t stream) {
     const PairShape shape = {MW, PW, KW, a.few, a.flush};
     static_assert(sizeof(Notes<PW>) <= 64, "");
     a.n_mgroups = (d.M + 64 * MW - 1) / (64 * MW);
     a.n_tiles = (int)(((long long)d.N * a.plane + 64 * PW - 1) / (64 * PW));
     a.WR = pair_window(d, shape);
     a.groups = (a.WR + 63) / 64;
+    for (int phase = 0; phase < 4; ++phase) a.phase_at[phase] = pair_phase_at(d, shape, phase);
     const int lds = pair_lds_bytes(d, shape);
     if (lds > kPairLdsBytes) return ESCOIN_ERANGE;
     a.total_at = lds - MW * PW * 64 * 256 - pair_head_bytes(shape) - 4 * a.WR;
     if (lds > 64 * 1024) {
-        const int rc = allow_dynamic_lds((const void*)sconv_pair_kernel<MW, PW, KW, FLUSH>, lds);
+        const int rc = allow_dynamic_lds((const void*)sconv_pair_kernel<MW, PW, KW, FLUSH, STRIDE>, lds);
         if (rc != ESCOIN_OK) return rc;
     }
     const unsigned blocks = (unsigned)(((long long)a.n_tiles * a.n_mgroups + 7) / 8 * 8);
-    return launch(sconv_pair_kernel<MW, PW, KW, FLUSH>, dim3(blocks), dim3(64 * MW * PW * KW), (size_t)lds, stream, a);
+    return launch(sconv_pair_kernel<MW, PW, KW, FLUSH, STRIDE>, dim3(blocks), dim3(64 * MW * PW * KW), (size_t)lds, stream, a);
+}
+
+template <int MW, int PW, int KW>
+int start(PairArgs& a, const Dims& d, hipStream_t stream) {
+    if constexpr (KW < 8)
+        if (d.stride == 2) return launch_shape<MW, PW, KW, false, 2>(a, d, stream);
+    if (KW == 2 && a.flush) return launch_shape<MW, PW, KW, KW == 2, 1>(a, d, stream);
+    return launch_shape<MW, PW, KW, false, 1>(a, d, stream);
 }
 
 }  // namespace
@@ -725,7 +771,7 @@ int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& s, co
     a.exps = (const int32_t*)(section + pair_weight_bytes(d));
     a.rowptr = (const int32_t*)(d_plan + h.off_nz);
     a.nz = (const MfmaNz*)(d_plan + h.off_nz + mfma_rowptr_bytes(d));
-    a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad;
+    a.N = d.N; a.C = d.C; a.H = d.H; a.W = d.W; a.M = d.M; a.E = d.E; a.F = d.F; a.R = d.R; a.S = d.S; a.pad = d.pad; a.stride = d.stride;
     a.pitch = pair_pitch(d);
     a.plane = (int)pair_plane(d);
     a.n_chunks = (int)mfma_chunks(d);
@@ -733,9 +779,9 @@ int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& s, co
     a.flush = s.flush;
     const int layout = 100 * s.MW + 10 * s.PW + s.KW;
     if (layout == 114) return start<1, 1, 4>(a, d, stream);
-    if (layout == 118) return start<1, 1, 8>(a, d, stream);
-    if (layout == 122) return a.flush ? start<1, 2, 2, true>(a, d, stream) : start<1, 2, 2>(a, d, stream);
-    if (layout == 212) return a.flush ? start<2, 1, 2, true>(a, d, stream) : start<2, 1, 2>(a, d, stream);
+    if (layout == 118 && d.stride == 1) return start<1, 1, 8>(a, d, stream);
+    if (layout == 122) return start<1, 2, 2>(a, d, stream);
+    if (layout == 212) return start<2, 1, 2>(a, d, stream);
     return ESCOIN_EINVAL;
 }
 

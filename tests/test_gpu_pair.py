@@ -250,6 +250,52 @@ def test_flushed_sums(oracle, shape):
     assert (np.abs(off[ok]) <= limit(L, bound)[ok]).all() and np.linalg.norm(off[ok]) <= np.linalg.norm(parts_off[ok])
 
 
+# Stride 2: maps of odd and even sizes, so that the last row or column of a phase is there or not; filters that leave a phase without taps.
+STRIDED = [
+    (32, 100, 27, 31, 180, 3, 3, 1, 0.70, 212),
+    (26, 250, 14, 13, 500, 3, 3, 1, 0.80, 114),    # rounds of four chunks, the last ragged
+    (60, 60, 31, 31, 64, 4, 3, 3, 0.70, 122),      # padding as wide as the filter; one round
+    (60, 113, 41, 20, 64, 3, 3, 0, 0.70, 114),
+    (20, 64, 33, 30, 96, 5, 5, 2, 0.70, 114),
+    (30, 200, 30, 30, 200, 2, 2, 0, 0.60, 114),
+    (64, 200, 50, 30, 250, 1, 3, 1, 0.50, 212),    # one row of taps: two phases
+    (64, 256, 40, 40, 40, 3, 1, 1, 0.50, 114),
+    (64, 500, 28, 28, 256, 1, 1, 0, 0.50, 212),    # one tap: one phase
+]
+
+
+@gpu
+@pytest.mark.parametrize("shape", STRIDED, ids=str)
+def test_stride_two(oracle, shape):
+    print("pair stride 2", shape, flush=True)
+    N, C, H, W, M, R, S, pad, sparsity, layout = shape
+    L = wl.custom_layer(N, C, H, W, M, R, S, 2, pad, sparsity, seed=102, dist="normal")
+    dl, one = pair_layer(L, layout), DeviceLayer(esc, L, tuning=dict(B=2))
+    for flags in (0, esc.F_BIAS | esc.F_RELU):
+        got, chain = dl.forward_tiled(flags), one.forward_tiled(flags)
+        ref, bound = oracle_full(oracle, L, flags)
+        assert_within_bound(got, ref, bound, (shape, flags))
+        assert (np.abs(got - ref) <= limit(L, bound)).all()
+        if flags == 0:
+            assert np.linalg.norm(got - ref) <= np.linalg.norm(chain - ref)
+    # the second pass, the way back to the nonzeros, and rows too short for the pairs
+    rows, cut = np.diff(L.rowptr), [1, M // 2, M - 1]
+    rows[cut] = [33, 48, 40]
+    keep = np.concatenate([np.arange(b - a) < k for a, b, k in zip(L.rowptr, L.rowptr[1:], rows)])
+    L.colidx, L.value, L.rowptr = L.colidx[keep], L.value[keep], np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    L.input[N - 1, :, H // 2] *= np.float32(2.0 ** 12)
+    L.input[1, 3, 2, 4] = np.inf
+    L.input[2] = np.nan
+    dl = DeviceLayer(esc, L)
+    got = dl.forward_tiled(esc.F_BIAS)
+    assert esc.escoin_sconv_tiled_kernel(dl.desc, dl.plan) > 1
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, bound = oracle_full(oracle, L, esc.F_BIAS)
+    bad = ~np.isfinite(bound)
+    assert bad.any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
+    assert (np.abs(got[~bad] - ref[~bad]) <= limit(L, bound)[~bad]).all()
+
+
 @gpu
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[4]], ids=str)
 def test_unaligned_buffers_guards_and_one_plan_for_two_batches(oracle, shape):
