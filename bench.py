@@ -72,7 +72,7 @@ def algorithmic_bytes(L, two_kernel: bool) -> int:
 def kernel_source_hash() -> str:
     """Identifies the code the recorded HBM counters were taken with."""
     h = hashlib.sha256()
-    for f in ("sconv_tiled.hip", "sconv_mfma.hip", "sconv_pair.hip", "plan.cpp", "mfma_plan.cpp", "pair_plan.cpp", "plan.h", "mfma.h",
+    for f in ("sconv_tiled.hip", "sconv_mfma.hip", "sconv_pair.hip", "sconv_first.hip", "plan.cpp", "mfma_plan.cpp", "pair_plan.cpp", "plan.h", "mfma.h",
               "mfma_device.h", "pair.h"):
         h.update(open(os.path.join(ROOT, "paper_1802_10280_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]

@@ -173,7 +173,7 @@ int escoin_sconv_plan_build(const escoin_conv_desc *desc, const int32_t *rowptr,
  * batch large enough to be faster there multiplies all of them, zeros too.  Two forms:
  *   - pairs of fp16 numbers, for layers of up to some 90 % sparsity whose rows have 32 nonzeros or more, 60 to some hundred on
  *     the average, and whose filters reach at most 127 positions of the flat padded map (two rows of 62, four of 30; at
- *     stride 2 of the outputs' map).  Inputs are scaled by a
+ *     stride 2 of the outputs' map), or with fewer than 16 input channels and an even stride.  Inputs are scaled by a
  *     power of two, the same for a workgroup's window, weights by one a row.  A pair holds 22 to 23 bits: an output of n
  *     products is off by up to 2^-21 of sum|w*x|, 0.8e-7 to 1.5e-7 of the result in the mean.  Where half of the inputs are zeros that is
  *     less than a chain of fp32 sums is off by from about 60 nonzeros on, and shorter rows are summed in fp32; an output that meets
@@ -192,7 +192,7 @@ int escoin_sconv_plan_build(const escoin_conv_desc *desc, const int32_t *rowptr,
  * aligned d_plan takes: 1 for the matrix cores, 0 for the tiled kernel, or an error code as the call itself would return.
  * escoin_sconv_tiled_kernel tells it further: 0 for the tiled kernel, 1 for the one of three bf16 parts,
  * 100*a + 10*b + c for the one of pairs with workgroups of a*b*c waves over a*64 output channels, b*64 positions and c
- * shares of the input channels.
+ * shares of the input channels (141: the form for fewer than 16 input channels and an even stride).
  *
  * d_in and d_plan that are 16-byte aligned let the kernel stage with 16-byte loads (or with
  * global -> LDS copies); any 4-byte aligned pointer is accepted.

@@ -51,8 +51,22 @@ inline int pair_lds_bytes(const Dims& d, const PairShape& s) {
     return pair_head_bytes(s) + 4 * WR + std::max(buffers * s.KW * 64 * WR, s.MW * s.PW * (s.KW - 1) * 64 * 256) + (s.flush ? s.MW * s.PW * 64 * 256 : 0);
 }
 
+// Layers of fewer channels than a chunk have a kernel of their own (sconv_first.hip), whose weights lie in groups of 8 columns of a filter row of a
+// channel: groups to a filter row, and steps of two groups.  It takes tiles of the outputs of an image in their order; in LDS lie, for each channel, so many rows and
+// columns of the padded input, in two parts, and where each group starts.
+constexpr int kFirstPositions = 256, kFirstLoads = 24, kFirstLdsBytes = 63 * 1024;
+inline bool first_layer(const Dims& d) { return d.C < 16; }
+inline int first_width(const Dims& d) { return (d.S + 7) / 8; }
+inline int first_steps(const Dims& d) { return (d.C * d.R * first_width(d) + 3) / 4 * 2; }  // an even number
+inline int first_in_rows(const Dims& d) { return (std::min(d.E, (kFirstPositions - 2 + d.F) / d.F + 1) - 1) * d.stride + d.R; }
+inline int first_columns(const Dims& d) { return (d.F - 1) * d.stride + 8 * first_width(d); }
+inline int first_together(const Dims& d) { return 8 / ((first_columns(d) + 63) / 64); }  // rows that 8 waves of 64 columns read at a time
+inline int first_loads(const Dims& d) { return first_together(d) ? (d.C * first_in_rows(d) + first_together(d) - 1) / first_together(d) : 1 << 30; }
+inline int first_lds_bytes(const Dims& d) { return d.C * first_in_rows(d) * first_columns(d) * 4 + first_steps(d) * 8 + 4; }
+
 // two steps to ask for ahead
 inline uint64_t pair_weight_bytes(const Dims& d) {
+    if (first_layer(d)) return mfma_row_blocks(d) * first_steps(d) * kPairStepBytes;
     return (mfma_row_blocks(d) * mfma_chunks(d) * d.R * d.S + 2) * kPairStepBytes;
 }
 inline uint64_t pair_bytes(const Dims& d) { return pair_weight_bytes(d) + mfma_rowptr_bytes(d); }  // with the rows' exponents
@@ -96,6 +110,8 @@ bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h);
 bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape);
 void pair_note_rows(const Dims& d, const int32_t* rp, PlanHeader* h);
 bool pair_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out);
+int launch_sconv_first(const Dims& d, const PlanHeader& h, int few, const char* d_plan, const float* d_in, float* d_out, const float* d_bias,
+                       uint32_t flags, hipStream_t stream);
 int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& shape, const char* d_plan, const float* d_in, float* d_out,
                       const float* d_bias, uint32_t flags, hipStream_t stream);
 

@@ -110,8 +110,25 @@ static int least_row(const PairShape& s, double slope) {
     return (int)std::min(ceil(pair_base(s) / std::max(gain, 1e-9)), 1e9);
 }
 
+// Layers of few channels: the shapes their kernel takes, its time and its error (the pairs' own, and a rounding for each 8 products of two chains;
+// inputs as of an image, none of them zero, make the chains of the tiled kernel twice as long as those this is weighed against).
+static bool first_takes(const Dims& d) {
+    return d.stride % 2 == 0 && d.M >= 32 && (long long)d.C * d.H * d.W * 4 < (1ll << 31) && (long long)d.E * d.F < (1ll << 30) && first_columns(d) < (1 << 12) && first_in_rows(d) < (1 << 12) &&
+           first_loads(d) <= kFirstLoads && first_lds_bytes(d) <= kFirstLdsBytes && first_steps(d) < 256;
+}
+static double first_error(const Dims& d) { return 0.5 + 0.0308 * (first_steps(d) + 2); }
+// A row of fewer nonzeros is less exact as pairs (measured where half of the inputs are zeros: 0.93e-7 and 0.97e-7 at 59 a row, 0.92 and 0.90 at 50).
+static int first_line(const Dims& d) { return (int)ceil(first_error(d) / kTiledRowSlope); }
+// Microseconds: 17, 78, 17 and 29 where 17.5, 77, 16 and 29 were measured (5 and 32 images of 3x224x224, 64 7x7 filters; 20 of 4x61x61, 128
+// 6x6; the first with three short rows; tiled: 41, 153, 25, 41).  `few`: short rows.
+static double first_time(const Dims& d, double N, int few) {
+    const double jobs = N * ceil((double)d.E * d.F / kFirstPositions) * ceil(d.M / 64.0);
+    return 3.0 + std::max(1.15, jobs / 256) * (7.5 + 0.4 * first_steps(d)) + 12.0 * ceil(few / ceil(d.M / 64.0) / 8) * std::max(1.0, jobs / 512);
+}
+
 // Whether a plan with this tiled form carries the section: a layer that some batch is faster with, and no less exact.
 bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h) {
+    if (first_layer(d)) return first_takes(d) && first_error(d) < 0.95 * tiled_slope(h.WS) * (double)nnz / d.M;
     const double n = (double)nnz / d.M;
     if (!pair_takes(d)) return false;
     for (const PairShape& s : kShapes)
@@ -126,6 +143,11 @@ bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h) {
 void pair_note_rows(const Dims& d, const int32_t* rp, PlanHeader* h) {
     h->pair_least = INT32_MAX;
     for (int m = 0; m < d.M; ++m) h->pair_least = std::min(h->pair_least, rp[m + 1] - rp[m]);
+    if (first_layer(d)) {
+        h->pair_few2 = 0;
+        for (int m = 0; m < d.M; ++m) h->pair_few2 += rp[m + 1] - rp[m] < first_line(d) ? 1 : 0;
+        return;
+    }
     for (const PairShape& s : kShapes) {
         const int least = least_row(s, kTiledRowSlope / h->WS);
         long long batches = 0;
@@ -144,6 +166,12 @@ bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
     if (h.pair != 1 || h.pair_least <= 0 || !pair_planned(d, h.pair_nnz, h)) return false;
     const long long total = (long long)d.N * pair_plane(d);
     if (total > (1ll << 30) || total / 64 * (long long)mfma_row_blocks(d) > (1ll << 30)) return false;
+    if (first_layer(d)) {
+        const double jobs = (double)d.N * ceil((double)d.E * d.F / kFirstPositions) * ceil(d.M / 64.0);
+        *shape = {1, kFirstPositions / 64, 1, h.pair_least < first_line(d) ? first_line(d) : 0};
+        if (h.WS > 1 && h.pair_least < first_line(d) * h.WS) return false;  // the tiled kernel's chains are shorter than those of short rows here
+        return jobs < (1 << 30) && first_time(d, d.N, h.pair_few2) < kMargin * tiled_time(d, d.N, h);
+    }
     const bool bf16 = mfma_taken(d, h);
     const double n = (double)h.pair_nnz / d.M, slope = bf16 ? kMfmaSlope : tiled_slope(h.WS);
     double best = kMargin * (bf16 ? mfma_time(d, d.N) : tiled_time(d, d.N, h));
@@ -218,9 +246,15 @@ bool pair_write(const Dims& d, const int32_t* rp, const MfmaNz* nz, char* out) {
             part[0] = to_half(v, &high);
             part[1] = to_half((v - high) * 2048.0f, &rest);
             const int c = nz[j].c;
-            const size_t step = ((size_t)(m / 32) * chunks + c / 16) * RS + (size_t)nz[j].r * d.S + nz[j].s;
-            const size_t lane = m % 32 + 32 * (size_t)(c % 16 / 8);
-            for (int k = 0; k < 2; ++k) w[((step * 2 + k) * 64 + lane) * 8 + c % 8] = part[k];
+            size_t step = ((size_t)(m / 32) * chunks + c / 16) * RS + (size_t)nz[j].r * d.S + nz[j].s;
+            size_t lane = m % 32 + 32 * (size_t)(c % 16 / 8), place = c % 8;
+            if (first_layer(d)) {
+                const size_t group = ((size_t)c * d.R + nz[j].r) * first_width(d) + nz[j].s / 8;
+                step = (size_t)(m / 32) * first_steps(d) + group / 2;
+                lane = m % 32 + 32 * (group % 2);
+                place = nz[j].s % 8;
+            }
+            for (int k = 0; k < 2; ++k) w[((step * 2 + k) * 64 + lane) * 8 + place] = part[k];
         }
     }
     return true;

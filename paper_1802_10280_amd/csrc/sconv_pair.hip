@@ -763,6 +763,7 @@ int start(PairArgs& a, const Dims& d, hipStream_t stream) {
 
 int launch_sconv_pair(const Dims& d, const PlanHeader& h, const PairShape& s, const char* d_plan, const float* d_in, float* d_out,
                       const float* d_bias, uint32_t flags, hipStream_t stream) {
+    if (first_layer(d)) return launch_sconv_first(d, h, s.few, d_plan, d_in, d_out, d_bias, flags, stream);
     PairArgs a;
     const char* const section = d_plan + h.off_pair;
     a.in = d_in; a.out = d_out; a.bias = d_bias; a.flags = flags;

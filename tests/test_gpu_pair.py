@@ -279,10 +279,7 @@ def test_stride_two(oracle, shape):
         if flags == 0:
             assert np.linalg.norm(got - ref) <= np.linalg.norm(chain - ref)
     # the second pass, the way back to the nonzeros, and rows too short for the pairs
-    rows, cut = np.diff(L.rowptr), [1, M // 2, M - 1]
-    rows[cut] = [33, 48, 40]
-    keep = np.concatenate([np.arange(b - a) < k for a, b, k in zip(L.rowptr, L.rowptr[1:], rows)])
-    L.colidx, L.value, L.rowptr = L.colidx[keep], L.value[keep], np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    L.colidx, L.value, L.rowptr = cut_rows(L, [1, M // 2, M - 1], [33, 48, 40])
     L.input[N - 1, :, H // 2] *= np.float32(2.0 ** 12)
     L.input[1, 3, 2, 4] = np.inf
     L.input[2] = np.nan
@@ -294,6 +291,75 @@ def test_stride_two(oracle, shape):
     bad = ~np.isfinite(bound)
     assert bad.any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
     assert (np.abs(got[~bad] - ref[~bad]) <= limit(L, bound)[~bad]).all()
+
+
+# N, C, H, W, M, R, S, pad, stride, sparsity: few channels and an even stride.
+FIRST = [
+    (6, 3, 224, 224, 64, 7, 7, 3, 2, 0.50),     # whole tiles
+    (60, 4, 61, 61, 128, 6, 6, 2, 2, 0.40),     # ragged last tiles; two columns of a group without weights
+    (60, 1, 64, 200, 100, 9, 9, 4, 4, 0.10),    # two groups to a filter row; channels over
+    (100, 7, 50, 61, 33, 4, 7, 0, 2, 0.40),     # no padding, 28 groups
+    (60, 4, 50, 61, 45, 4, 8, 0, 2, 0.30),      # whole groups
+    (40, 2, 70, 150, 140, 5, 11, 2, 2, 0.20),   # padding smaller than the reach
+    (150, 3, 33, 40, 100, 7, 7, 3, 2, 0.45),    # a tile of nearly all rows; an odd number of groups
+]
+
+
+def cut_rows(L, cut, lengths):
+    rows = np.diff(L.rowptr)
+    rows[cut] = lengths
+    keep = np.concatenate([np.arange(b - a) < k for a, b, k in zip(L.rowptr, L.rowptr[1:], rows)])
+    return L.colidx[keep], L.value[keep], np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+
+
+def first_layer(shape):
+    N, C, H, W, M, R, S, pad, stride, sparsity = shape
+    return wl.custom_layer(N, C, H, W, M, R, S, stride, pad, sparsity, seed=103, dist="normal")
+
+
+@gpu
+@pytest.mark.parametrize("shape", FIRST, ids=str)
+def test_few_channels(oracle, shape):
+    print("pair few channels", shape, flush=True)
+    L = first_layer(shape)
+    L.input[:] = np.random.default_rng(104).standard_normal(L.input.shape, dtype=np.float32)
+    dl, one = pair_layer(L, 141), DeviceLayer(esc, L, tuning=dict(B=2))
+    for flags in (0, esc.F_BIAS | esc.F_RELU):
+        got, chain = dl.forward_tiled(flags), one.forward_tiled(flags)
+        ref, bound = oracle_full(oracle, L, flags)
+        assert_within_bound(got, ref, bound, (shape, flags))
+        assert (np.abs(got - ref) <= limit(L, bound)).all()
+        if flags == 0:
+            assert np.linalg.norm(got - ref) <= np.linalg.norm(chain - ref)
+    # rows too short for the pairs; inputs past what the others' scale leaves bits for, inputs that lose them, Inf and NaN
+    L.input[0, :, shape[2] // 2] *= np.float32(2.0 ** 90)
+    L.input[1] *= np.float32(2.0 ** -60)
+    L.input[1, 0, 9, 7] = 1.0
+    L.input[1, 0, 30:] = 0
+    L.input[2, 0, 5, 8] = -np.inf
+    L.input[2, 0, 25] = np.nan
+    L.colidx, L.value, L.rowptr = cut_rows(L, [1, shape[4] // 2, shape[4] - 1], [33, 40, 48])
+    dl = pair_layer(L, 141)
+    got = dl.forward_tiled(esc.F_BIAS)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, bound = oracle_full(oracle, L, esc.F_BIAS)
+    bad = ~np.isfinite(bound)
+    assert bad.any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
+    assert (np.abs(got[~bad] - ref[~bad]) <= limit(L, bound)[~bad]).all()
+    short = np.zeros(shape[4], bool)
+    short[[1, shape[4] // 2, shape[4] - 1]] = True  # chains of 48 products at most, and the bias
+    assert (np.abs(got - ref)[:, short][~bad[:, short]] <= 49 * 2.0 ** -24 * bound[:, short][~bad[:, short]] + 2.0 ** -149).all()
+
+
+def test_what_few_channels_leave_to_the_tiled_kernel():
+    """Odd strides, rows too short for the pairs to be as exact, single images, tuned plans."""
+    for shape, N, kernel in ((FIRST[0], 3, 141), (FIRST[0], 1, 0), (FIRST[6][:-1] + (0.8,), 60, 0), (FIRST[6][:8] + (1, 0.45), 60, 0)):
+        L = first_layer((1,) + shape[1:])
+        s = L.spec
+        d = esc.make_desc(N, s.C, s.H, s.W, s.M, s.R, s.S, s.stride, s.pad)
+        stretched = esc.escoin_sconv_pack(d, L.rowptr, L.colidx)
+        assert esc.escoin_sconv_tiled_kernel(d, esc.escoin_sconv_plan_build(d, L.rowptr, stretched, L.value)) == kernel
+        assert esc.escoin_sconv_tiled_kernel(d, esc.escoin_sconv_plan_build(d, L.rowptr, stretched, L.value, esc.make_tuning(B=2))) == 0
 
 
 @gpu
