@@ -71,13 +71,14 @@ __device__ inline void walk(const MfmaArgs& a, const float* input, Words nz, int
 static_assert(sizeof(MfmaNz) == 12, "walk() reads three words a nonzero");
 
 // The marked positions once more from the nonzeros, for the channels m0 .. m0 + rows - 1 of a workgroup whose
-// `waves` waves share the channels.  `lists`: which of the RUNS * 64 positions from t0 on.
+// `waves` waves share the channels; `only`: those with a bit there, where it is given.  `lists`: which of the RUNS * 64 positions from t0 on.
 // Bound by the gathers' latency where few workgroups come here and by their address arithmetic where all
 // do.  64x256x28x28 at 50 % in three bf16 parts, when each lane redid its own outputs -> now: one NaN in the batch 6.4 -> 0.5 ms,
 // one image of them 11.6 -> 2.3, nothing else 32 -> 7.0 (the tiled kernel takes 0.72 whatever the input).  Pairs, whose
 // workgroups have 64 positions, not 256, to a nonzero: 0.26, 2.3 and 16.0 (0.25 without any); two by 64 channels, at 80 %: 0.30, 1.6 and 6.4 (0.18).
 template <int RUNS>
-__device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], int t0, int m0, int rows, int waves, int wave, int lane) {
+__device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], int t0, int m0, int rows, int waves, int wave, int lane,
+                            const uint64_t* only = nullptr) {
     const bool relu = a.flags & ESCOIN_F_RELU, has_bias = a.flags & ESCOIN_F_BIAS;
     const int EF = a.E * a.F, HW = a.H * a.W, n_first = t0 / a.plane;
     const float* const in = a.in + (size_t)n_first * a.C * HW;
@@ -106,6 +107,7 @@ __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], in
         }
         for (int k = wave; k < rows && m0 + k < a.M; k += waves) {
             const int m = m0 + k;
+            if (only && !(only[k >> 6] >> (k & 63) & 1)) continue;
             float v[RUNS] = {};
             walk(a, in, shared_nz, __builtin_amdgcn_readfirstlane(a.rowptr[m]), __builtin_amdgcn_readfirstlane(a.rowptr[m + 1]), 1, at, v);
 #pragma unroll
@@ -126,6 +128,7 @@ __device__ inline void redo(const MfmaArgs& a, const uint64_t (&lists)[RUNS], in
         const int u = t0 + run * 64 + __ffsll((unsigned long long)list) - 1;
         const Place at[1] = {place(u)};
         for (int k = wave; k < rows && m0 + k < a.M; k += waves) {
+            if (only && !(only[k >> 6] >> (k & 63) & 1)) continue;
             const int m = m0 + k, begin = __builtin_amdgcn_readfirstlane(a.rowptr[m]), end = __builtin_amdgcn_readfirstlane(a.rowptr[m + 1]);
             float v[1] = {};
             if (step == 1) walk(a, in, shared_nz, begin, end, 1, at, v);

@@ -31,8 +31,8 @@
 // bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy half of the time in the first
 // one (76 us at 2.4 GHz) and a third where eight waves share the channels (counters, first call after others); the rest is the workgroups'
 // beginnings and ends, 12000-17000 clocks each, which only the other workgroup of a compute unit hides (there is none beside eight
-// waves), and the first two rounds, when all of them ask for their inputs at once.  Scalar and, in three layouts, a few vector
-// registers are spilled, outside the loops over the steps.
+// waves), and the first two rounds, when all of them ask for their inputs at once.  Scalar registers are spilled outside the loops over
+// the steps.
 #include <float.h>
 #include <algorithm>
 
@@ -72,6 +72,7 @@ struct PairArgs : MfmaArgs {
 
 #define ESCOIN_INLINE __attribute__((always_inline))
 constexpr int kStepBytes = kPairStepBytes;
+constexpr int kFewBad = 8;  // positions
 
 // x / d and what is left, for x and d below 2^22 (one_over: 1 / d, rounded): the product is off by less than one.
 __device__ inline int divide(int x, int d, float one_over, int* rest) {
@@ -94,6 +95,8 @@ __device__ inline uint32_t wave_max(uint32_t x) {
 template <int PW>
 struct Notes {
     uint64_t again[PW];  // positions that have a sum that cannot be used
+    uint64_t rows[2];    // channels that have one
+    int over;            // not 0: one of them is not finite
     int lost;            // eights of inputs with one that loses bits, zeros apart
     uint32_t peak;       // bits of the largest finite |x| that the scale is made for
 };
@@ -506,8 +509,20 @@ __device__ __forceinline__ uint64_t pass(const PairArgs& a, const Room<MW, PW> r
         for (int i = 0; i < kEach; ++i)
             bad |= m + 8 * (i / 4) + i % 4 < a.M && !(fabsf(v[t * kEach + i]) <= FLT_MAX && fabsf(v[t * kEach + i]) >= small_sum);
         const uint64_t lanes = __ballot(bad && inside);
-        if (lanes != 0 && lane == 0)
-            atomicOr((unsigned long long*)&notes->again[wp], ((lanes | lanes >> 32) & 0xffffffffu) << (32 * (tile & 1)));
+        if (__builtin_expect(lanes != 0, 0)) {
+            if (lane == 0) atomicOr((unsigned long long*)&notes->again[wp], ((lanes | lanes >> 32) & 0xffffffffu) << (32 * (tile & 1)));
+            uint64_t rows = 0;
+            bool over = false;
+#pragma unroll
+            for (int i = 0; i < kEach; ++i) {
+                const int k = m + 8 * (i / 4) + i % 4;
+                const bool finite = fabsf(v[t * kEach + i]) <= FLT_MAX;
+                rows |= k < a.M && !(finite && fabsf(v[t * kEach + i]) >= small_sum) ? 1ull << ((k - mg * TM) & 63) : 0ull;
+                over |= k < a.M && !finite;
+            }
+            if (inside && rows != 0) atomicOr((unsigned long long*)&notes->rows[wm], rows);
+            if (inside && over) notes->over = 1;
+        }
     }
     __syncthreads();  // before the stores: nothing waits for those unless some outputs are computed again
     uint64_t any = 0;
@@ -643,6 +658,8 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
     if (tid < PW) notes->again[tid] = 0;
     if (tid == PW) notes->lost = 0;
     if (tid == PW + 1) notes->peak = 0;
+    if (tid == PW + 2) notes->over = 0;
+    if (tid >= PW + 3 && tid < PW + 5) notes->rows[tid - PW - 3] = 0;
     const size_t left = (size_t)(a.N - n_first) * CHW * 4;
     const Rsrc in = rsrc_of(a.in + (size_t)n_first * CHW, (uint32_t)min(left, (size_t)kNowhere));
     const Rsrc wr = rsrc_of(a.w, a.w_bytes);
@@ -681,6 +698,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
             }
         }
     };
+    int once_more;
     {
         float v[kShare];
         int ex;
@@ -696,33 +714,44 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
             }
             return;
         }
+        int count = 0;
+#pragma unroll
+        for (int run = 0; run < PW; ++run) count += __popcll(notes->again[run]);
+        once_more = __builtin_amdgcn_readfirstlane(notes->over != 0 || count > kFewBad ? 1 : 0);
+        if (once_more == 0) store(v, ex);
     }
-    // Perhaps an input was past the scale that the first ones asked for: once more with the scale of the largest.
-    uint32_t most = 0;
-    for (int i = tid; i < a.C * a.WR; i += kThreads) {
-        const int c = i / a.WR;
-        const uint32_t src = room.tab()[i - c * a.WR];
-        const uint32_t b = __builtin_amdgcn_raw_buffer_load_b32(in, src == kNowhere ? src : src + (uint32_t)(c * HW) * 4u, 0, 0) & 0x7fffffffu;
-        most = max(most, b < 0x7f800000u ? +b : 0u);
-    }
-    __syncthreads();  // every wave has read the notes
-    if (tid < PW) notes->again[tid] = 0;
-    if (tid == PW) notes->lost = 0;
-    atomicMax(&notes->peak, most);
-    __syncthreads();
-    float v[kShare];
-    int ex, lane2 = lane, wave2 = wave;
-    asm volatile("" : "+v"(lane2));  // what the first pass made of it is not worth keeping for this one
-    const uint64_t any = pass<MW, PW, KW, FLUSH, STRIDE, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
-    store(v, ex);
     int start = t0;
-    asm volatile("" : "+s"(start));  // nor what the beginning made of this
+    asm volatile("" : "+s"(start));  // what the first pass made of it is not worth keeping
+    uint64_t any = 1;
+    // Perhaps an input was past the scale that the first ones asked for: once more with the scale of the largest.  Not where a few sums are
+    // only too small for the bits that some input lost, as happens now and then behind a ReLU (one such sum in a launch of 32x128x56x56 at stride
+    // 2: 38 -> 100 us with the second pass and all channels from their nonzeros).
+    if (once_more != 0) {
+        uint32_t most = 0;
+        for (int i = tid; i < a.C * a.WR; i += kThreads) {
+            const int c = i / a.WR;
+            const uint32_t src = room.tab()[i - c * a.WR];
+            const uint32_t b = __builtin_amdgcn_raw_buffer_load_b32(in, src == kNowhere ? src : src + (uint32_t)(c * HW) * 4u, 0, 0) & 0x7fffffffu;
+            most = max(most, b < 0x7f800000u ? +b : 0u);
+        }
+        __syncthreads();  // every wave has read the notes
+        if (tid < PW) notes->again[tid] = 0;
+        if (tid == PW) notes->lost = 0;
+        if (tid >= PW + 3 && tid < PW + 5) notes->rows[tid - PW - 3] = 0;
+        atomicMax(&notes->peak, most);
+        __syncthreads();
+        float v[kShare];
+        int ex, lane2 = lane, wave2 = wave;
+        asm volatile("" : "+v"(lane2));  // what the first pass made of it is not worth keeping for this one
+        any = pass<MW, PW, KW, FLUSH, STRIDE, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
+        store(v, ex);
+    }
     if (any != 0) {
         uint64_t lists[PW];
 #pragma unroll
         for (int run = 0; run < PW; ++run) lists[run] = notes->again[run];
         __syncthreads();  // those stores before the ones of redo()
-        redo(a, lists, start, mg * TM, TM, kWaves, wave, lane);
+        redo(a, lists, start, mg * TM, TM, kWaves, wave, lane, notes->rows);
     }
     if (a.few != 0) {
         nowhere_past_the_table<PW>(room, lane, wave);

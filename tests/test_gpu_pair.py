@@ -351,6 +351,19 @@ def test_few_channels(oracle, shape):
     assert (np.abs(got - ref)[:, short][~bad[:, short]] <= 49 * 2.0 ** -24 * bound[:, short][~bad[:, short]] + 2.0 ** -149).all()
 
 
+@gpu
+@pytest.mark.parametrize("rows", [4, 8])
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[3]], ids=str)
+def test_a_few_sums_of_tiny_inputs(oracle, shape, rows):
+    """Positions all of whose inputs lose bits: up to eight of a workgroup are computed from the nonzeros, more send it through its second pass."""
+    print("pair tiny sums", shape, rows, flush=True)
+    L = layer(shape, seed=105)
+    L.input[1, :, 6:6 + rows, 4:9] *= np.float32(2.0 ** -40)  # (rows - 2) * 3 such positions
+    got = pair_layer(L, shape[-1]).forward_tiled(esc.F_RELU)
+    ref, bound = oracle_full(oracle, L, esc.F_RELU)
+    assert (np.abs(got - ref) <= limit(L, bound)).all()
+
+
 def test_what_few_channels_leave_to_the_tiled_kernel():
     """Odd strides, rows too short for the pairs to be as exact, single images, tuned plans."""
     for shape, N, kernel in ((FIRST[0], 3, 141), (FIRST[0], 1, 0), (FIRST[6][:-1] + (0.8,), 60, 0), (FIRST[6][:8] + (1, 0.45), 60, 0)):
