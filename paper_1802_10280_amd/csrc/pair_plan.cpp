@@ -96,10 +96,11 @@ constexpr double kTiledRowSlope = 0.0163, kMfmaSlope = 0.00195;  // the first: a
 static double pair_error(double n, const PairShape& s) { return pair_base(s) + pair_slope(s) * n; }
 
 // Rounds between a wave's flushes: such that its chains are as long as with eight shares, and as exact.  0 where the wave and its partner would not
-// both have had a turn by then, and for launches that do not fill every compute unit twice, where eight shares are as fast (32 images of
-// 13x13, 512 channels, 384 filters at 50 %: 93.4 us both ways).
+// both have had a turn by then, for launches that do not fill every compute unit twice, where eight shares are as fast (32 images of
+// 13x13, 512 channels, 384 filters at 50 %: 93.4 us both ways), and at stride 2, whose kernels flush nothing: where two shares are not exact
+// enough there, as beside the split rows of a plan made for few images, four are.
 static int flush_rounds(const Dims& d, const PairShape& s) {
-    if (s.KW != 2 || ceil(d.N * (double)pair_plane(d) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW)) < 512) return 0;
+    if (d.stride != 1 || s.KW != 2 || ceil(d.N * (double)pair_plane(d) / (64 * s.PW)) * ceil(d.M / (64.0 * s.MW)) < 512) return 0;
     const int flush = (int)mfma_chunks(d) / 8;
     return flush >= 2 ? flush : 0;
 }

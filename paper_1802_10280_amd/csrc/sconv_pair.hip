@@ -782,6 +782,7 @@ int launch_shape(PairArgs& a, const Dims& d, hipStream_t stream) {
 
 template <int MW, int PW, int KW>
 int start(PairArgs& a, const Dims& d, hipStream_t stream) {
+    if (a.flush && (KW != 2 || d.stride == 2)) return ESCOIN_EINVAL;  // there is no such form
     if constexpr (KW < 8)
         if (d.stride == 2) return launch_shape<MW, PW, KW, false, 2>(a, d, stream);
     if (KW == 2 && a.flush) return launch_shape<MW, PW, KW, KW == 2, 1>(a, d, stream);

@@ -293,6 +293,55 @@ def test_stride_two(oracle, shape):
     assert (np.abs(got[~bad] - ref[~bad]) <= limit(L, bound)[~bad]).all()
 
 
+# Stride 2, a plan for few images (whose tiled kernel splits its rows over waves, for shorter chains) and a call on many.
+# N, C, H, W, M, R, sparsity, images of the plan, waves to a row, workgroup layout
+REPLANNED = [
+    (48, 336, 41, 41, 172, 3, 0.82, 1, 4, 114),    # two shares of the channels would need their sums flushed to be as exact
+    (24, 66, 44, 44, 162, 5, 0.68, 3, 2, 212),
+]
+
+
+def replanned(shape, N):
+    _, C, H, W, M, R, sparsity, few, WS, _ = shape
+    L = wl.custom_layer(N, C, H, W, M, R, R, 2, R // 2, sparsity, seed=106, dist="normal")
+    d = esc.make_desc(few, C, H, W, M, R, R, 2, R // 2)
+    plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+    assert esc.plan_header(plan)["WS"] == WS
+    return L, plan
+
+
+@pytest.mark.parametrize("shape", REPLANNED, ids=str)
+def test_stride_two_is_taken_for_what_it_is_exact_to(shape):
+    """Whatever the batch, the layout's squared error by the rule (nothing is flushed at stride 2) is below the plan's tiled kernel's."""
+    _, C, H, W, M, R, sparsity, few, WS, _ = shape
+    _, plan = replanned(shape, 1)
+    n = esc.plan_header(plan)["pair_nnz"] / M
+    taken = {N: esc.escoin_sconv_tiled_kernel(esc.make_desc(N, C, H, W, M, R, R, 2, R // 2), plan) for N in (1, 2, 4, 8, 16, 24, 32, 48, 64, 100, 128, 256)}
+    assert taken[shape[0]] == shape[-1]
+    for N, kernel in taken.items():
+        base, slope = {2: (0.81, 0.0044), 4: (0.81, 0.0020)}.get(kernel % 10, (0, 0))
+        assert kernel == 0 or base + slope * n <= 0.95 * 0.0154 / WS * n, (N, kernel)
+
+
+@gpu
+@pytest.mark.parametrize("shape", REPLANNED, ids=str)
+def test_stride_two_with_a_plan_for_few_images(oracle, shape):
+    print("pair stride 2, plan for few", shape, flush=True)
+    L, plan = replanned(shape, shape[0])
+    results = []
+    for tiled in (False, True):
+        if tiled:
+            forget(plan, ("pair", "pair_nnz", "off_pair", "off_nz", "pair_least"))
+        dl = DeviceLayer(esc, L)
+        dl.plan, dl.d_plan = plan, to_dev(plan)
+        assert esc.escoin_sconv_tiled_kernel(dl.desc, plan) == (0 if tiled else shape[-1])
+        results.append(dl.forward_tiled())
+    ref, bound = oracle_full(oracle, L)
+    got, chains = results
+    assert (np.abs(got - ref) <= limit(L, bound)).all()
+    assert np.linalg.norm(got - ref) <= np.linalg.norm(chains - ref)
+
+
 # N, C, H, W, M, R, S, pad, stride, sparsity: few channels and an even stride.
 FIRST = [
     (6, 3, 224, 224, 64, 7, 7, 3, 2, 0.50),     # whole tiles
