@@ -70,8 +70,11 @@ constexpr double kMargin = 0.9;
 static bool pair_takes(const Dims& d) {
     if (d.stride > 2 || (d.stride == 1 && (d.R <= d.pad || d.S <= d.pad)) || d.C < 16 || d.M < 32) return false;
     if (pair_reach(d) > kPairReach || pair_weight_bytes(d) > (64ull << 20)) return false;
-    // positions, and the offsets inside the images that a workgroup's window may touch, in 32 bits
+    // positions, and the offsets inside the images that a workgroup's window may touch, in 32 bits; and those of the channels that a round
+    // of four chunks asks for past the last one, before they are held to it (where an image of two million positions at stride 2 has four times as
+    // many inputs; at stride 1 even eight chunks stay below)
     const long long plane = pair_plane(d), images = (128 + kPairReach) / plane + 2;
+    if ((d.C + 63ll) / 64 * 64 * d.H * d.W * 4 >= (1ll << 31)) return false;
     return plane < (1 << 21) && images * d.C * d.H * d.W * 4 < (1ll << 31) && images * d.M * d.E * d.F < (1ll << 31);
 }
 

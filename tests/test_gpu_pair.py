@@ -195,11 +195,15 @@ def test_no_batch_is_less_exact_than_without_the_pairs():
     assert seen == {(False, 0), (True, 0), (False, 1)}
 
 
-def forget(plan, fields):
+def rewrite(plan, **fields):
     from paper_1802_10280_amd.binding import _PlanHeader
-    for f in fields:
+    for f, v in fields.items():
         at = getattr(_PlanHeader, f)
-        plan[at.offset:at.offset + at.size] = 0
+        plan[at.offset:at.offset + at.size] = np.frombuffer(int(v).to_bytes(at.size, "little"), np.uint8)
+
+
+def forget(plan, fields):
+    rewrite(plan, **dict.fromkeys(fields, 0))
 
 
 @gpu
@@ -340,6 +344,22 @@ def test_stride_two_with_a_plan_for_few_images(oracle, shape):
     got, chains = results
     assert (np.abs(got - ref) <= limit(L, bound)).all()
     assert np.linalg.norm(got - ref) <= np.linalg.norm(chains - ref)
+
+
+@pytest.mark.parametrize("H, kernel", [(450001, 114), (491519, 114), (493447, 114), (493449, 0), (524287, 0)])
+def test_stride_two_keeps_a_round_of_channels_in_32_bits(H, kernel):
+    """28 channels of a tall map: a wave asks for the inputs of up to 64 before it holds itself to the last, at byte offsets below 2^31."""
+    C, W, M, R = 28, 17, 64, 2
+    L = wl.custom_layer(1, C, 16, W, M, R, R, 2, 0, 1 - 78 / 112, seed=107, dist="normal")
+    d = esc.make_desc(1, C, 4095, W, M, R, R, 2, 0)
+    plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+    h = esc.plan_header(plan)
+    assert h["pair"] == 1 and esc.escoin_sconv_tiled_kernel(esc.make_desc(100, C, 4095, W, M, R, R, 2, 0), plan) == 114
+    tall = esc.make_desc(1, C, H, W, M, R, R, 2, 0)
+    E, _ = esc.escoin_output_dims(tall)
+    rewrite(plan, H=H, E=E, n_tiles=-(-E // h["TH"]))  # what its own plan, of a gigabyte, says of it
+    assert esc.escoin_sconv_tiled_kernel(tall, plan) == kernel
+    assert kernel == 0 or 64 * H * W * 4 < 1 << 31
 
 
 # N, C, H, W, M, R, S, pad, stride, sparsity: few channels and an even stride.
