@@ -20,6 +20,9 @@ struct Dims {
 // Fills `d` from a checked descriptor; returns an ESCOIN_* code.
 int make_dims(const escoin_conv_desc* desc, Dims* d);
 
+// Whether a launch can have so many workgroups of so many threads: the runtime takes a grid of fewer than 2^32 threads.
+inline bool grid_fits(double blocks, int threads) { return (blocks + 7) * threads < 0x1p32; }
+
 inline int hip_status(hipError_t e) { return e == hipSuccess ? ESCOIN_OK : ESCOIN_EHIP; }
 
 // Launches `kernel` and reports the status of this launch alone: hipLaunchKernel's own return

@@ -174,7 +174,7 @@ bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
         const double jobs = (double)d.N * ceil((double)d.E * d.F / kFirstPositions) * ceil(d.M / 64.0);
         *shape = {1, kFirstPositions / 64, 1, h.pair_least < first_line(d) ? first_line(d) : 0};
         if (h.WS > 1 && h.pair_least < first_line(d) * h.WS) return false;  // the tiled kernel's chains are shorter than those of short rows here
-        return jobs < (1 << 30) && first_time(d, d.N, h.pair_few2) < kMargin * tiled_time(d, d.N, h);
+        return grid_fits(jobs, 2 * kFirstPositions) && first_time(d, d.N, h.pair_few2) < kMargin * tiled_time(d, d.N, h);
     }
     const bool bf16 = mfma_taken(d, h);
     const double n = (double)h.pair_nnz / d.M, slope = bf16 ? kMfmaSlope : tiled_slope(h.WS);
@@ -184,6 +184,7 @@ bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
         const double most = (bf16 ? 1.0 : 0.95) * slope * n;
         if (pair_error(n, s) > most) s.flush = flush_rounds(d, s);
         if (pair_error(n, s) > most) continue;
+        if (!grid_fits(ceil(total / (64.0 * s.PW)) * ceil(d.M / (64.0 * s.MW)), 64 * s.MW * s.PW * s.KW)) continue;
         const int least = least_row(s, bf16 ? kMfmaSlope : kTiledRowSlope / h.WS);
         const bool few = h.pair_least < least;
         if (few && (bf16 || h.WS > kFewChains || s.flush)) continue;

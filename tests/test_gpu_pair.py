@@ -362,6 +362,20 @@ def test_stride_two_keeps_a_round_of_channels_in_32_bits(H, kernel):
     assert kernel == 0 or 64 * H * W * 4 < 1 << 31
 
 
+@pytest.mark.parametrize("shape, kernel, most", [
+    ((3, 16, 18, 508, 8, 2, 1, 0.2), 141, (1 << 20) - 1),     # 8 workgroups of 512 threads an image
+    ((44, 3, 5, 373, 4, 1, 1, 0.5), 212, 14913072),           # 24 positions an image, 64 to each of 3 workgroups of 256
+    ((45, 1, 11, 349, 5, 2, 2, 0.5), 212, 14913072),          # ... and at stride 2
+], ids=str)
+def test_batches_whose_grid_would_not_fit(shape, kernel, most):
+    """A launch of 2^32 threads or more is none the runtime takes: such batches go where they went."""
+    C, H, W, M, R, stride, pad, sparsity = shape
+    L = wl.custom_layer(1, C, H, W, M, R, R, stride, pad, sparsity, seed=108, dist="normal")
+    desc = lambda N: esc.make_desc(N, C, H, W, M, R, R, stride, pad)
+    plan = esc.escoin_sconv_plan_build(desc(1024), L.rowptr, esc.escoin_sconv_pack(desc(1024), L.rowptr, L.colidx), L.value)
+    assert [esc.escoin_sconv_tiled_kernel(desc(N), plan) for N in (most, most + 8)] == [kernel, 0]
+
+
 # N, C, H, W, M, R, S, pad, stride, sparsity: few channels and an even stride.
 FIRST = [
     (6, 3, 224, 224, 64, 7, 7, 3, 2, 0.50),     # whole tiles
