@@ -698,7 +698,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
             }
         }
     };
-    int once_more;
+    enum { kDone, kNonzeros, kOnceMore } then = kDone;  // what some sums still need
     {
         float v[kShare];
         int ex;
@@ -707,32 +707,39 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
         // compiled as one that never runs, with 150-200 registers spilled (inputs that need it: 0.42 -> 0.56 ms at 64x256x28x28).
         if (__builtin_expect_with_probability(any == 0, 1, 0.9)) {
             store(v, ex);
-            if (__builtin_expect_with_probability(a.few != 0, 0, 0.7)) {
-                nowhere_past_the_table<PW>(room, lane, wave);
-                __syncthreads();  // and those stores before the ones of few_rows()
-                few_rows<MW, PW, KW, STRIDE>(a, room, in, lane, wave, mg, t0);
-            }
-            return;
-        }
-        int count = 0;
+            if (__builtin_expect_with_probability(a.few == 0, 1, 0.7)) return;
+        } else {
+            int count = 0;
 #pragma unroll
-        for (int run = 0; run < PW; ++run) count += __popcll(notes->again[run]);
-        once_more = __builtin_amdgcn_readfirstlane(notes->over != 0 || count > kFewBad ? 1 : 0);
-        if (once_more == 0) store(v, ex);
+            for (int run = 0; run < PW; ++run) count += __popcll(notes->again[run]);
+            then = __builtin_amdgcn_readfirstlane(notes->over != 0 || count > kFewBad ? 1 : 0) ? kOnceMore : kNonzeros;
+            if (then == kNonzeros) store(v, ex);
+        }
     }
+    // What comes now is rare.  It reads the kernel's arguments, of which PairArgs is all, once more from where the launch put them, so that none has
+    // to outlive the first pass: with them kept, 64 to 212 scalar registers were spilled, now 38 to 80, and the usual way through is 1-2 % faster
+    // (32x64x56x56: 34.0 -> 33.5 us, 64x384x13x13 at 65 %: 107.2 -> 105.7, 64x256x28x28 at 50 %: 170.4 -> 169.2).  Some of what is rare takes 1-3 % longer
+    // (a second pass at stride 2 everywhere: 132 -> 135 us; one sum from the nonzeros: 70.6 -> 72.9).
     int start = t0;
-    asm volatile("" : "+s"(start));  // what the first pass made of it is not worth keeping
-    uint64_t any = 1;
+    auto from = (const __attribute__((address_space(4))) PairArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(start), "+s"(from));
+    const PairArgs& b = *(const PairArgs*)from;
+    const Room<MW, PW> room2 = {lds, b.WR};
+    // (Said to be the same in all lanes: descriptors that might not be are read lane by lane.)
+    const int n_first2 = __builtin_amdgcn_readfirstlane(start / b.plane), CHW2 = b.C * b.H * b.W;
+    const uint32_t in_bytes = __builtin_amdgcn_readfirstlane((uint32_t)min((size_t)(b.N - n_first2) * CHW2 * 4, (size_t)kNowhere));
+    const Rsrc in2 = rsrc_of(b.in + (size_t)n_first2 * CHW2, in_bytes), wr2 = rsrc_of(b.w, b.w_bytes);
+    uint64_t any = then != kDone ? 1 : 0;
     // Perhaps an input was past the scale that the first ones asked for: once more with the scale of the largest.  Not where a few sums are
     // only too small for the bits that some input lost, as happens now and then behind a ReLU (one such sum in a launch of 32x128x56x56 at stride
     // 2: 38 -> 100 us with the second pass and all channels from their nonzeros).
-    if (once_more != 0) {
+    if (then == kOnceMore) {
         uint32_t most = 0;
-        for (int i = tid; i < a.C * a.WR; i += kThreads) {
-            const int c = i / a.WR;
-            const uint32_t src = room.tab()[i - c * a.WR];
-            const uint32_t b = __builtin_amdgcn_raw_buffer_load_b32(in, src == kNowhere ? src : src + (uint32_t)(c * HW) * 4u, 0, 0) & 0x7fffffffu;
-            most = max(most, b < 0x7f800000u ? +b : 0u);
+        for (int i = tid; i < b.C * b.WR; i += kThreads) {
+            const int c = i / b.WR;
+            const uint32_t src = room2.tab()[i - c * b.WR];
+            const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(in2, src == kNowhere ? src : src + (uint32_t)(c * b.H * b.W) * 4u, 0, 0) & 0x7fffffffu;
+            most = max(most, x < 0x7f800000u ? +x : 0u);
         }
         __syncthreads();  // every wave has read the notes
         if (tid < PW) notes->again[tid] = 0;
@@ -743,7 +750,7 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
         float v[kShare];
         int ex, lane2 = lane, wave2 = wave;
         asm volatile("" : "+v"(lane2));  // what the first pass made of it is not worth keeping for this one
-        any = pass<MW, PW, KW, FLUSH, STRIDE, true>(a, room, in, wr, lane2, wave2, mg, v, &ex);
+        any = pass<MW, PW, KW, FLUSH, STRIDE, true>(b, room2, in2, wr2, lane2, wave2, mg, v, &ex);
         store(v, ex);
     }
     if (any != 0) {
@@ -751,12 +758,12 @@ __global__ __launch_bounds__(64 * MW * PW * KW, 2) void sconv_pair_kernel(const 
 #pragma unroll
         for (int run = 0; run < PW; ++run) lists[run] = notes->again[run];
         __syncthreads();  // those stores before the ones of redo()
-        redo(a, lists, start, mg * TM, TM, kWaves, wave, lane, notes->rows);
+        redo(b, lists, start, mg * TM, TM, kWaves, wave, lane, notes->rows);
     }
-    if (a.few != 0) {
-        nowhere_past_the_table<PW>(room, lane, wave);
+    if (b.few != 0) {
+        nowhere_past_the_table<PW>(room2, lane, wave);
         __syncthreads();  // and these
-        few_rows<MW, PW, KW, STRIDE>(a, room, in, lane, wave, mg, start);
+        few_rows<MW, PW, KW, STRIDE>(b, room2, in2, lane, wave, mg, start);
     }
 }
 
