@@ -56,11 +56,13 @@ static double pair_time(const Dims& d, double N, const PairShape& s, double few 
 // LDS reads of its records, 4.6 clocks of 2.1 GHz for each position run and half of that for the record itself.  That is 48, 48, 56,
 // 58, 188 and 107 us where 48, 47, 55, 59, 177 and 111 were measured (56x56 with 64 channels, 28x28 with 128, 14x14 with 256, 7x7 with 512,
 // 28x28 with 256 at 90 and 95 %), 11 and 12 where 11 and 15 were (16 channels, 5x5; 192 channels, 1x1).  At stride 2 it takes a fifth more: 38, 41, 47, 70, 213, 17 where
-// 40, 43, 53, 58, 195 and 18 were (the layers above).
+// 40, 43, 53, 58, 195 and 18 were (the layers above).  Not with few channels, whose chunks are few: with 2 us for the launch, 52, 194, 125, 28, 136 and 58 where 50, 197, 122, 28,
+// 130 and 57 were (5 and 32 images of 3x224x224, 64 7x7 filters; 12 of 2x236x236, 63 11x11; 20 of 4x61x61, 128 6x6; 40 of 3x182x60, 53 11x11; 64 of 1x64x200, 100
+// 9x9 of stride 4; all at 30 %, but the last at 10).
 static double tiled_time(const Dims& d, double N, const PlanHeader& h) {
     const double jobs = (double)h.n_tiles * ceil(N / h.NB) * h.n_mgroups * h.CS;
     const double job = 4.0 + 0.5 * h.n_chunks / h.CS + (double)h.n_records / h.n_mgroups / h.CS * h.WQ * (h.Q + 0.5) * 4.6 / 2100.0;
-    return ceil(ceil(jobs / 8) / 32) * job * (d.stride == 2 ? 1.2 : 1.0);
+    return ceil(ceil(jobs / 8) / 32) * job * (d.stride == 2 && !first_layer(d) ? 1.2 : 1.0);
 }
 
 // How much faster it has to look, as the estimates are off by a tenth now and then.
@@ -115,7 +117,8 @@ static int least_row(const PairShape& s, double slope) {
 }
 
 // Layers of few channels: the shapes their kernel takes, its time and its error (the pairs' own, and a rounding for each 8 products of two chains;
-// inputs as of an image, none of them zero, make the chains of the tiled kernel twice as long as those this is weighed against).
+// inputs as of an image, none of them zero, make the chains of the tiled kernel twice as long as those this is weighed against).  Over 200 random layers
+// whose inputs are half zeros the error was 0.7 to 1.2 times this, the tiled kernel's 0.9 to 1.15 times its own, so some room is left between them.
 static bool first_takes(const Dims& d) {
     return d.stride % 2 == 0 && d.M >= 32 && (long long)d.C * d.H * d.W * 4 < (1ll << 31) && (long long)d.E * d.F < (1ll << 30) && first_columns(d) < (1 << 12) && first_in_rows(d) < (1 << 12) &&
            first_loads(d) <= kFirstLoads && first_lds_bytes(d) <= kFirstLdsBytes && first_steps(d) < 256;
@@ -123,16 +126,25 @@ static bool first_takes(const Dims& d) {
 static double first_error(const Dims& d) { return 0.5 + 0.0308 * (first_steps(d) + 2); }
 // A row of fewer nonzeros is less exact as pairs (measured where half of the inputs are zeros: 0.93e-7 and 0.97e-7 at 59 a row, 0.92 and 0.90 at 50).
 static int first_line(const Dims& d) { return (int)ceil(first_error(d) / kTiledRowSlope); }
-// Microseconds: 17, 78, 17 and 29 where 17.5, 77, 16 and 29 were measured (5 and 32 images of 3x224x224, 64 7x7 filters; 20 of 4x61x61, 128
-// 6x6; the first with three short rows; tiled: 41, 153, 25, 41).  `few`: short rows.
+// Microseconds; a workgroup beside another one takes three fifths as long again, so the first of a further round of 256 cost more than their share.  17, 85,
+// 49, 22, 17, 43, 26 and 57 where 18, 79, 51, 22, 16, 41, 24 and 53 were measured (the layers named at tiled_time(), the third with 4 images too; 16 of 6x120x120, 235
+// 5x5); without short rows 320 random layers took at most 1.08 times as long as this.
+// `few`: short rows.  One of up to 57 nonzeros keeps its wave for 12 us after all else, in two workgroups of a compute unit at once; many are bound by their
+// gathers, 2 us a row and workgroup of a compute unit, 3 at stride 4.  1, 8 and 32 such rows of 64 take 12, 16 and 64 us more where 12, 19 and 63 were measured
+// (5x3x224x224), 37, 98 and 392 where 40, 79 and 341 were (32 of them), 21, 55 and 220 where 22, 50 and 204 were (12x2x236x236, of 76 nonzeros), 11, 45 and
+// 179 where 14, 45 and 185 were (stride 4).  Counted as 15.5, 3 and 4.5, as short rows do not spread evenly over workgroups, nor those over the XCDs: of
+// 90 random layers with some, taken by this, one was slower than on the tiled kernel, by 3 %.
 static double first_time(const Dims& d, double N, int few) {
-    const double jobs = N * ceil((double)d.E * d.F / kFirstPositions) * ceil(d.M / 64.0);
-    return 3.0 + std::max(1.15, jobs / 256) * (7.5 + 0.4 * first_steps(d)) + 12.0 * ceil(few / ceil(d.M / 64.0) / 8) * std::max(1.0, jobs / 512);
+    const double jobs = N * ceil((double)d.E * d.F / kFirstPositions) * ceil(d.M / 64.0), row = (first_line(d) - 1) / 57.0;
+    const double most = few * std::min(64.0 / d.M, 1.0);  // of a workgroup's channels
+    const double alone = 15.5 * ceil(most / 8) * std::max(1.0, jobs / 512), together = 0.75 * (2 + d.stride) * most * std::max(1.0, jobs / 256);
+    const double full = floor(jobs / 256), rest = jobs / 256 - full;
+    return 3.0 + std::max(1.15, full + (rest > 0 ? 0.6 + 0.4 * rest : 0.0)) * (7.5 + 0.4 * first_steps(d)) + row * std::max(alone, together);
 }
 
 // Whether a plan with this tiled form carries the section: a layer that some batch is faster with, and no less exact.
 bool pair_planned(const Dims& d, long long nnz, const PlanHeader& h) {
-    if (first_layer(d)) return first_takes(d) && first_error(d) < 0.95 * tiled_slope(h.WS) * (double)nnz / d.M;
+    if (first_layer(d)) return first_takes(d) && first_error(d) < 0.92 * tiled_slope(h.WS) * (double)nnz / d.M;
     const double n = (double)nnz / d.M;
     if (!pair_takes(d)) return false;
     for (const PairShape& s : kShapes)
@@ -174,7 +186,7 @@ bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
         const double jobs = (double)d.N * ceil((double)d.E * d.F / kFirstPositions) * ceil(d.M / 64.0);
         *shape = {1, kFirstPositions / 64, 1, h.pair_least < first_line(d) ? first_line(d) : 0};
         if (h.WS > 1 && h.pair_least < first_line(d) * h.WS) return false;  // the tiled kernel's chains are shorter than those of short rows here
-        return grid_fits(jobs, 2 * kFirstPositions) && first_time(d, d.N, h.pair_few2) < kMargin * tiled_time(d, d.N, h);
+        return grid_fits(jobs, 2 * kFirstPositions) && first_time(d, d.N, h.pair_few2) < 2.0 + tiled_time(d, d.N, h);
     }
     const bool bf16 = mfma_taken(d, h);
     const double n = (double)h.pair_nnz / d.M, slope = bf16 ? kMfmaSlope : tiled_slope(h.WS);

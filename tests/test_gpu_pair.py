@@ -458,6 +458,18 @@ def test_what_few_channels_leave_to_the_tiled_kernel():
         assert esc.escoin_sconv_tiled_kernel(d, esc.escoin_sconv_plan_build(d, L.rowptr, stretched, L.value, esc.make_tuning(B=2))) == 0
 
 
+@pytest.mark.parametrize("cut, kernel", [(0, 141), (2, 141), (9, 0), (32, 0)])
+def test_short_rows_of_few_channels_count_for_what_they_cost(cut, kernel):
+    """12 of 2x236x236, 63 11x11 filters of stride 2: 51 us, 82 with two rows of 76 nonzeros, 121 with nine and 255 with 32; the tiled kernel 122."""
+    L = wl.custom_layer(1, 2, 236, 236, 63, 11, 11, 2, 5, 0.3, seed=3, dist="normal")
+    at = np.linspace(0, 62, cut).astype(int)
+    if cut:
+        L.colidx, L.value, L.rowptr = cut_rows(L, at, [76] * cut)
+    d = esc.make_desc(12, 2, 236, 236, 63, 11, 11, 2, 5)
+    plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+    assert esc.plan_header(plan)["pair_few2"] == cut and esc.escoin_sconv_tiled_kernel(d, plan) == kernel
+
+
 @gpu
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[4]], ids=str)
 def test_unaligned_buffers_guards_and_one_plan_for_two_batches(oracle, shape):
