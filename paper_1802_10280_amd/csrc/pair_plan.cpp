@@ -27,11 +27,13 @@ constexpr double kLeastJobs = 64;
 // At stride 2 the next round is staged when the last one is over.  A workgroup that has a compute unit to itself takes 16800 clocks around its
 // steps and 600 a step, beside another one 26000 and 900; 620 a staging task, and 2300 a round where filters are not three wide.  That is
 // 25, 24, 26, 43, 33, 14 and 104 us where 26, 26, 25, 41, 30, 13 and 100 were measured (32 images of 56x56 with 64 channels, 28x28 with 128 in both layouts,
-// 14x14 with 256 in both; 13 of 63x63 with 30; 64 of 31x31 with 128, 5x5; tiled: 40, 43, 43, 53, 53, 18, 195).
+// 14x14 with 256 in both; 13 of 63x63 with 30; 64 of 31x31 with 128, 5x5; tiled: 40, 43, 43, 53, 53, 18, 195).  Where a workgroup leaves no room for another one a last
+// round takes as long as a whole one, however few they are (266 to 342 workgroups with filters five wide: 2.0 to 2.1 times as long as 256).
 //
 // `few`: batches of nonzeros of all short rows.  A batch takes a wave 1200 clocks for 64 positions, with all of them at it; counted as 1900, since
 // a whole row falls to one wave.  105 random layers of uneven rows that take the pairs by this need 0.39 to 0.96 of the tiled kernel's time, one
-// 1.09 (26 of 25x25, 34 -> 51 channels, 5x5: 22.4 us and 31.3, but 34.0 for inputs that send one workgroup through its second pass).
+// 1.09 (26 of 25x25, 34 -> 51 channels, 5x5: 22.4 us and 31.3, but 34.0 for inputs that send one workgroup through its second pass).  At stride 2 a launch of one
+// round is as long as the workgroup that has a short row, of four batches or so (12 of 18x26x26, 371 3x3 filters: 11.7 us by the mean, 16.3 measured).
 static double pair_time(const Dims& d, double N, const PairShape& s, double few = 0) {
     const int waves = s.MW * s.PW * s.KW, lds = pair_lds_bytes(d, s), RS = d.R * d.S;
     if (lds > kPairLdsBytes || (d.stride == 2 && waves > 4)) return INFINITY;
@@ -47,9 +49,10 @@ static double pair_time(const Dims& d, double N, const PairShape& s, double few 
     } else if (d.S == 3) job += steps * (waves == 4 ? 900 : 1180) + (rounds - 1) * tasks * 250;
     else job += steps * 1150 + (rounds - 1) * (2700 + tasks * 750);
     if (s.flush) job += rounds / s.flush * 700;
-    job += few / ceil(d.M / (64.0 * s.MW)) / waves * s.PW * 1900;
+    const double batches = few / ceil(d.M / (64.0 * s.MW)) / waves * 1900;
+    job += s.PW * (d.stride == 2 && few > 0 && jobs <= slots ? std::max(batches, 4 * 1200.0) : batches);
     const double full = floor(jobs / slots), rest = jobs / slots - full;
-    return 2.0 + std::max(1.0, full + (rest > 0 ? 0.5 + 0.5 * rest : 0.0)) * job / 2000.0;
+    return 2.0 + std::max(1.0, full + (rest > 0 ? (d.stride == 2 && slots == 256 ? 1.0 : 0.5 + 0.5 * rest) : 0.0)) * job / 2000.0;
 }
 
 // The tiled kernel's, from its tiling: rounds of workgroups over 8 x 32 compute units; a workgroup's 4 us and half a us a chunk, and the
@@ -200,7 +203,9 @@ bool pair_taken(const Dims& d, const PlanHeader& h, PairShape* shape) {
         const int least = least_row(s, bf16 ? kMfmaSlope : kTiledRowSlope / h.WS);
         const bool few = h.pair_least < least;
         if (few && (bf16 || h.WS > kFewChains || s.flush)) continue;
-        const double t = pair_time(d, d.N, s, !few ? 0 : s.KW == 2 ? h.pair_few2 : s.KW == 4 ? h.pair_few4 : h.pair_few8);
+        // (With filters three wide flushed two shares are some 6 % slower than pair_time() has it, and eight up to 8 % faster: 37 of 377x29x29, 171 filters
+        // took 163 and 157 us.)
+        const double t = (s.flush && d.S == 3 ? 1.1 : 1.0) * pair_time(d, d.N, s, !few ? 0 : s.KW == 2 ? h.pair_few2 : s.KW == 4 ? h.pair_few4 : h.pair_few8);
         if (t < best) {
             best = t;
             *shape = s;

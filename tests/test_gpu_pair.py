@@ -346,6 +346,21 @@ def test_stride_two_with_a_plan_for_few_images(oracle, shape):
     assert np.linalg.norm(got - ref) <= np.linalg.norm(chains - ref)
 
 
+@pytest.mark.parametrize("shape, kernel", [
+    ((32, 18, 42, 42, 75, 5, 2, 0.62), 212),      # 24 us; 266 workgroups of the other kind, one to a compute unit, 35; the tiled kernel 29
+    ((63, 358, 30, 30, 39, 5, 2, 0.67), 122),     # 139; 285 workgroups, one to a compute unit, 154
+    ((12, 18, 26, 26, 371, 3, 2, 0.30), 114),     # 13 and 18
+    ((12, 18, 26, 26, 371, 3, 2, 0.57), 0),       # some rows too short: 16 and 14
+    ((37, 377, 29, 29, 171, 3, 1, 0.59), 118),    # 157; 163 with two flushed shares
+    ((74, 384, 14, 14, 250, 3, 1, 0.55), 212),
+], ids=str)
+def test_layers_take_what_they_are_fastest_with(shape, kernel):
+    N, C, H, W, M, R, stride, sparsity = shape
+    L = wl.custom_layer(1, C, H, W, M, R, R, stride, R // 2, sparsity, seed=3, dist="normal")
+    d = esc.make_desc(N, C, H, W, M, R, R, stride, R // 2)
+    assert esc.escoin_sconv_tiled_kernel(d, esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)) == kernel
+
+
 @pytest.mark.parametrize("H, kernel", [(450001, 114), (491519, 114), (493447, 114), (493449, 0), (524287, 0)])
 def test_stride_two_keeps_a_round_of_channels_in_32_bits(H, kernel):
     """28 channels of a tall map: a wave asks for the inputs of up to 64 before it holds itself to the last, at byte offsets below 2^31."""
