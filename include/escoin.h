@@ -169,11 +169,12 @@ int escoin_sconv_plan_build(const escoin_conv_desc *desc, const int32_t *rowptr,
  * additions, and with it the last bits of the result, may differ from run to run), and, with
  * ESCOIN_F_RELU, the clamp as a pass of its own.
  *
- * A plan made without tuning for a layer of stride 1 or 2 may also hold its weights for the matrix cores, and a call on a
- * batch large enough to be faster there multiplies all of them, zeros too.  Two forms:
+ * A plan made without tuning for a layer of stride 1 or 2, or of few input channels and any even stride, may also hold its
+ * weights for the matrix cores, and a call on a batch large enough to be faster there multiplies all of them, zeros too.  Two forms:
  *   - pairs of fp16 numbers, for layers of up to some 90 % sparsity whose rows have 32 nonzeros or more, 60 to some hundred on
  *     the average, and whose filters reach at most 127 positions of the flat padded map (two rows of 62, four of 30; at
- *     stride 2 of the outputs' map), or with fewer than 16 input channels and an even stride.  Inputs are scaled by a
+ *     stride 2 of the outputs' map), or with fewer than 16 input channels and an even stride, where 256 outputs of an image need
+ *     no more than some 12 000 words of whole padded input rows (3 channels, 7x7 filters, stride 2: up to 250 columns).  Inputs are scaled by a
  *     power of two, the same for a workgroup's window, weights by one a row.  A pair holds 22 to 23 bits: an output of n
  *     products is off by up to 2^-21 of sum|w*x|, 0.8e-7 to 1.5e-7 of the result in the mean.  Where half of the inputs are zeros that is
  *     less than a chain of fp32 sums is off by from about 60 nonzeros on, and shorter rows are summed in fp32; an output that meets

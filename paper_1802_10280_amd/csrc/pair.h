@@ -54,7 +54,7 @@ inline int pair_lds_bytes(const Dims& d, const PairShape& s) {
 // Layers of fewer channels than a chunk have a kernel of their own (sconv_first.hip), whose weights lie in groups of 8 columns of a filter row of a
 // channel: groups to a filter row, and steps of two groups.  It takes tiles of the outputs of an image in their order; in LDS lie, for each channel, so many rows and
 // columns of the padded input, in two parts, and where each group starts.
-constexpr int kFirstPositions = 256, kFirstLoads = 24, kFirstLdsBytes = 63 * 1024;
+constexpr int kFirstPositions = 256, kFirstLoads = 24, kFirstSteps = 255;
 inline bool first_layer(const Dims& d) { return d.C < 16; }
 inline int first_width(const Dims& d) { return (d.S + 7) / 8; }
 inline int first_steps(const Dims& d) { return (d.C * d.R * first_width(d) + 3) / 4 * 2; }  // an even number
@@ -62,6 +62,8 @@ inline int first_in_rows(const Dims& d) { return (std::min(d.E, (kFirstPositions
 inline int first_columns(const Dims& d) { return (d.F - 1) * d.stride + 8 * first_width(d); }
 inline int first_together(const Dims& d) { return 8 / ((first_columns(d) + 63) / 64); }  // rows that 8 waves of 64 columns read at a time
 inline int first_loads(const Dims& d) { return first_together(d) ? (d.C * first_in_rows(d) + first_together(d) - 1) / first_together(d) : 1 << 30; }
+// (its rows are kFirstLoads of eight waves' 64 columns at most)
+static_assert(kFirstLoads * 8 * 64 * 4 + kFirstSteps * 8 + 4 <= 63 * 1024, "beside 1.3 KB of its own");
 inline int first_lds_bytes(const Dims& d) { return d.C * first_in_rows(d) * first_columns(d) * 4 + first_steps(d) * 8 + 4; }
 
 // two steps to ask for ahead

@@ -33,7 +33,7 @@ constexpr double kLeastJobs = 64;
 // `few`: batches of nonzeros of all short rows.  A batch takes a wave 1200 clocks for 64 positions, with all of them at it; counted as 1900, since
 // a whole row falls to one wave.  105 random layers of uneven rows that take the pairs by this need 0.39 to 0.96 of the tiled kernel's time, one
 // 1.09 (26 of 25x25, 34 -> 51 channels, 5x5: 22.4 us and 31.3, but 34.0 for inputs that send one workgroup through its second pass).  At stride 2 a launch of one
-// round is as long as the workgroup that has a short row, of four batches or so (12 of 18x26x26, 371 3x3 filters: 11.7 us by the mean, 16.3 measured).
+// round is as long as the workgroup that has a short row, of four batches or so (12 of 18x26x26, 371 3x3 filters: 13 us by the mean, 16 measured).
 static double pair_time(const Dims& d, double N, const PairShape& s, double few = 0) {
     const int waves = s.MW * s.PW * s.KW, lds = pair_lds_bytes(d, s), RS = d.R * d.S;
     if (lds > kPairLdsBytes || (d.stride == 2 && waves > 4)) return INFINITY;
@@ -124,7 +124,7 @@ static int least_row(const PairShape& s, double slope) {
 // whose inputs are half zeros the error was 0.7 to 1.2 times this, the tiled kernel's 0.9 to 1.15 times its own, so some room is left between them.
 static bool first_takes(const Dims& d) {
     return d.stride % 2 == 0 && d.M >= 32 && (long long)d.C * d.H * d.W * 4 < (1ll << 31) && (long long)d.E * d.F < (1ll << 30) && first_columns(d) < (1 << 12) && first_in_rows(d) < (1 << 12) &&
-           first_loads(d) <= kFirstLoads && first_lds_bytes(d) <= kFirstLdsBytes && first_steps(d) < 256;
+           first_loads(d) <= kFirstLoads && first_steps(d) <= kFirstSteps;
 }
 static double first_error(const Dims& d) { return 0.5 + 0.0308 * (first_steps(d) + 2); }
 // A row of fewer nonzeros is less exact as pairs (measured where half of the inputs are zeros: 0.93e-7 and 0.97e-7 at 59 a row, 0.92 and 0.90 at 50).

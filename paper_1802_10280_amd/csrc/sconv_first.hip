@@ -2,11 +2,13 @@
 // fp16 numbers, as in sconv_pair.hip.
 //
 // With so few channels the 16 factors of a matrix instruction are not channels but neighbouring taps: half of them, 8, are
-// 8 columns of one filter row of one channel (the last of them may be none: their weights are zero), so a 7x7 filter on 3 channels takes 11
-// instructions to a product where 16 channels to a tap would take 49.  In LDS the input lies as it does in memory, padded, its two parts
+// 8 columns of one filter row of one channel (the last of them may be none: their weights are zero), so a 7x7 filter on 3 channels takes 12
+// instructions to a product (21 groups of 8 columns in pairs, an even number of those) where 16 channels to a tap would take 49.  In LDS the input lies as it does in memory, padded, its two parts
 // apart; a lane's 8 columns are 16 bytes of a row from its output's first column on, aligned to 4 bytes as the stride is even.
 // A workgroup takes 64 channels of 256 consecutive outputs of an image, 32 a wave, and all input channels at once: its inputs pass
-// through registers, so that the scale is that of the largest, and there is no second pass.  Two sums by turns halve the chains.
+// through registers (24 words a lane, of whole padded rows: maps of 3 channels with 7x7 filters
+// of stride 2 up to 250 columns wide, but for 123 to 126), so that the scale is that of the
+// largest, and there is no second pass.  Two sums by turns halve the chains.
 //
 // Bound by its chain (inputs, barrier, largest, barrier, conversion, barrier, twelve steps whose weights are asked for one ahead, stores), as the
 // matrix cores need 2 us.  32 positions a wave, not 64, so that two workgroups fit a compute unit without spills (288 registers; 31 us).
@@ -243,7 +245,7 @@ int launch_sconv_first(const Dims& d, const PlanHeader& h, int few, const char* 
     a.together = first_together(d);
     a.few = few;
     const int lds = first_lds_bytes(d);
-    if (lds > kFirstLdsBytes || first_loads(d) > kFirstLoads) return ESCOIN_ERANGE;
+    if (first_loads(d) > kFirstLoads) return ESCOIN_ERANGE;
     const unsigned blocks = (unsigned)(d.N * a.n_tiles_image * a.n_mgroups);
     return launch(sconv_first_kernel, dim3(blocks), dim3(kThreads), (size_t)lds, stream, a);
 }

@@ -450,13 +450,22 @@ def test_few_channels(oracle, shape):
 
 
 @gpu
-@pytest.mark.parametrize("rows", [4, 8])
+@pytest.mark.parametrize("count", [8, 9])
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[3]], ids=str)
-def test_a_few_sums_of_tiny_inputs(oracle, shape, rows):
+def test_a_few_sums_of_tiny_inputs(oracle, shape, count):
     """Positions all of whose inputs lose bits: up to eight of a workgroup are computed from the nonzeros, more send it through its second pass."""
-    print("pair tiny sums", shape, rows, flush=True)
+    print("pair tiny sums", shape, count, flush=True)
     L = layer(shape, seed=105)
-    L.input[1, :, 6:6 + rows, 4:9] *= np.float32(2.0 ** -40)  # (rows - 2) * 3 such positions
+    s = L.spec
+    pitch, plane, positions = s.W + s.pad, (s.H + s.pad) * (s.W + s.pad), 64 * (shape[-1] // 10 % 10)
+    group = lambda n, h, w: (n * plane + h * pitch + w) // positions
+    h, w = next((h, w) for h in range(5, s.H - 1) for w in range(2, s.W - 1 - count) if group(1, h, w) == group(1, h, w + count - 1))
+    L.input[1, :, h - 1:h + 2, w - 1:w + count + 1] *= np.float32(2.0 ** -40)
+    tiny = np.ones((s.N, s.H + 2, s.W + 2), bool)  # what lies outside counts as tiny
+    tiny[:, 1:-1, 1:-1] = False
+    tiny[1, h:h + 3, w:w + count + 2] = True
+    at = np.argwhere(np.lib.stride_tricks.sliding_window_view(tiny, (3, 3), axis=(1, 2)).all(axis=(3, 4)))
+    assert [group(*p) for p in at] == [group(1, h, w)] * count
     got = pair_layer(L, shape[-1]).forward_tiled(esc.F_RELU)
     ref, bound = oracle_full(oracle, L, esc.F_RELU)
     assert (np.abs(got - ref) <= limit(L, bound)).all()
@@ -471,6 +480,31 @@ def test_what_few_channels_leave_to_the_tiled_kernel():
         stretched = esc.escoin_sconv_pack(d, L.rowptr, L.colidx)
         assert esc.escoin_sconv_tiled_kernel(d, esc.escoin_sconv_plan_build(d, L.rowptr, stretched, L.value)) == kernel
         assert esc.escoin_sconv_tiled_kernel(d, esc.escoin_sconv_plan_build(d, L.rowptr, stretched, L.value, esc.make_tuning(B=2))) == 0
+
+
+@pytest.mark.parametrize("shape, loads", [
+    ((3, 224, 224, 7, 3, 2), 20),     # 63 rows of 229 columns, two at a time by eight waves
+    ((3, 240, 240, 7, 3, 2), 20),
+    ((3, 256, 256, 7, 3, 2), 33),     # columns of 262: one at a time
+    ((3, 448, 448, 7, 3, 2), 33),
+    ((4, 224, 224, 7, 3, 2), 26),
+    ((3, 227, 227, 11, 0, 4), 47),
+    ((3, 512, 512, 7, 3, 2), 0),      # more columns than eight waves have
+    ((1, 256, 256, 11, 5, 2), 15),
+    ((6, 120, 120, 5, 2, 2), 23),
+    ((8, 56, 56, 5, 2, 2), 25),
+], ids=str)
+def test_how_much_input_few_channels_may_have(shape, loads):
+    """A tile's padded rows pass through 24 registers a lane, so many words of a row each; layers of more stay with the tiled kernel."""
+    C, H, W, R, pad, stride = shape
+    d = esc.make_desc(32, C, H, W, 64, R, R, stride, pad)
+    E, F = esc.escoin_output_dims(d)
+    rows, columns = (min(E, (254 + F) // F + 1) - 1) * stride + R, (F - 1) * stride + 8 * -(-R // 8)
+    together = 8 // -(-columns // 64)
+    assert loads == (-(-C * rows // together) if together else 0)
+    L = wl.custom_layer(1, C, H, W, 64, R, R, stride, pad, 0.1, seed=109, dist="normal")
+    plan = esc.escoin_sconv_plan_build(d, L.rowptr, esc.escoin_sconv_pack(d, L.rowptr, L.colidx), L.value)
+    assert (esc.escoin_sconv_tiled_kernel(d, plan) == 141) == (0 < loads <= 24)
 
 
 @pytest.mark.parametrize("cut, kernel", [(0, 141), (2, 141), (9, 0), (32, 0)])
