@@ -27,12 +27,12 @@
 // all of which a round stages side by side: the window is four times as large beside the same steps, so it has one buffer and two
 // workgroups to a compute unit hide each other's staging (phase after phase, as rounds of their own: no faster than the tiled kernel).
 // 32x128x56x56, 128 3x3 filters, 80 %: 38 us (tiled 70); 11x78x45x45, 439 5x5 filters, 71 %: 50 (125); 13x89x23x23, 276 3x3, 71 %: 17.5 (24).
-// Measured: 64x256x28x28, 256 3x3 filters: 153-162 us at 80 % (tiled kernel 312), at 50 % 172-178 (323); 64x384x13x13, 384 filters, 65 %: 109-111 (three
-// bf16 parts: 232); 32x64x56x56 at 80 %: 33 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy half of the time in the first
+// Measured: 64x256x28x28, 256 3x3 filters: 149-154 us at 80 % (tiled kernel 312), at 50 % 169-175 (323); 64x384x13x13, 384 filters, 65 %: 105-107 (three
+// bf16 parts: 232); 32x64x56x56 at 80 %: 33.5 (48); 32x512x7x7 at 80 %: 30 (58).  The matrix cores are busy half of the time in the first
 // one (76 us at 2.4 GHz) and a third where eight waves share the channels (counters, first call after others); the rest is the workgroups'
 // beginnings and ends, 12000-17000 clocks each, which only the other workgroup of a compute unit hides (there is none beside eight
-// waves), and the first two rounds, when all of them ask for their inputs at once.  Scalar registers are spilled outside the loops over
-// the steps.
+// waves), and the first two rounds, when all of them ask for their inputs at once.  Scalar registers are spilled (38 to 80),
+// one or two of them read back in the loops over the steps.
 #include <float.h>
 #include <algorithm>
 
